@@ -363,28 +363,28 @@ int enqueue_sweeps(const Work& w, uint32_t n, bool measure, const LatDesc* descs
     return SW_OK;
 }
 
-// One sweep of every lattice in w with its sweep counter bumped at the end,
-// so that a captured step replays as the next sweep each time.  flags as for
+// One sweep of every lattice in w with its sweep counter moved on by the merge
+// (so the flip and the cluster sums after it are sweep counter - 1), so that a
+// captured step replays as the next sweep each time.  flags as for
 // launch_bond_label (bit 0: measure the configuration the bonds are drawn on).
-int enqueue_step(const Work& w, uint32_t flags, const LatDesc* descs, uint32_t count)
+int enqueue_step(const Work& w, uint32_t flags)
 {
+    constexpr uint32_t THIS = 0xFFFFFFFFu;   // counter - 1
     int rc = phase_bonds(w, 0, flags);
     if (rc) return rc;
-    HIP_TRY(launch_merge(w));
-    rc = phase_flip(w, 0);
+    HIP_TRY(launch_merge(w, 1));
+    rc = phase_flip(w, THIS);
     if (rc) return rc;
-    if (w.cluster) HIP_TRY(launch_cluster_sums(w, 0));
-    HIP_TRY(launch_bump(descs, count, nullptr, 1, w.stream));
+    if (w.cluster) HIP_TRY(launch_cluster_sums(w, THIS));
     return SW_OK;
 }
 
-int capture_steps(const Work& w, uint32_t flags, uint32_t steps, const LatDesc* descs, uint32_t count,
-                  hipGraphExec_t* out)
+int capture_steps(const Work& w, uint32_t flags, uint32_t steps, hipGraphExec_t* out)
 {
     hipGraph_t graph;
     HIP_TRY(hipStreamBeginCapture(w.stream, hipStreamCaptureModeThreadLocal));
     int rc = SW_OK;
-    for (uint32_t k = 0; k < steps && rc == SW_OK; ++k) rc = enqueue_step(w, flags, descs, count);
+    for (uint32_t k = 0; k < steps && rc == SW_OK; ++k) rc = enqueue_step(w, flags);
     const hipError_t ec = hipStreamEndCapture(w.stream, &graph);
     if (rc != SW_OK) return rc;
     if (ec != hipSuccess) return fail(SW_EHIP, "graph capture failed: %s", hipGetErrorString(ec));
@@ -396,12 +396,12 @@ int capture_steps(const Work& w, uint32_t flags, uint32_t steps, const LatDesc* 
 
 // n sweeps from the captured steps (built on first use), then the
 // measurement of the last sweep (the one before the bumped counter).
-int run_steps(StepGraphs& G, const Work& w, uint32_t n, bool measure, const LatDesc* descs, uint32_t count)
+int run_steps(StepGraphs& G, const Work& w, uint32_t n, bool measure)
 {
     if (!G.first) {
-        int rc = capture_steps(w, 0u, 1, descs, count, &G.first);
-        if (rc == SW_OK) rc = capture_steps(w, measure ? 1u : 0u, 1, descs, count, &G.next);
-        if (rc == SW_OK) rc = capture_steps(w, measure ? 1u : 0u, STEP_CHUNK, descs, count, &G.chunk);
+        int rc = capture_steps(w, 0u, 1, &G.first);
+        if (rc == SW_OK) rc = capture_steps(w, measure ? 1u : 0u, 1, &G.next);
+        if (rc == SW_OK) rc = capture_steps(w, measure ? 1u : 0u, STEP_CHUNK, &G.chunk);
         if (rc) {
             G.clear();
             return rc;
@@ -512,7 +512,7 @@ int sw_sweep(sw_lattice* h, uint32_t n_sweeps)
     if (h->g.whole) return whole_sweeps(h, n_sweeps);
     const Work w{h->d_desc, nullptr, h->g.ntiles, h->g.ty, h->stream, h->g.csum, h->g.xy};
     // the legacy NULL stream cannot be captured: launch directly
-    const int rc = h->stream ? run_steps(h->graphs, w, n_sweeps, h->g.cap != 0, h->d_desc, 1)
+    const int rc = h->stream ? run_steps(h->graphs, w, n_sweeps, h->g.cap != 0)
                              : enqueue_sweeps(w, n_sweeps, h->g.cap != 0, h->d_desc, 1, nullptr);
     if (rc) return rc;
     h->done += n_sweeps;
@@ -951,12 +951,13 @@ int upload_map(sw_batch* b, const uint32_t* n_each, uint32_t kmax, std::vector<u
     return SW_OK;
 }
 
-// The replicas swept whole: n_each[r] (or n_uniform) sweeps from counter + k0,
-// counters left for the caller to advance.
-int batch_whole(sw_batch* b, uint32_t k0, uint32_t n_uniform, const uint32_t* d_n_each)
+// The replicas swept whole: n_each[r] (or n_uniform) sweeps from their
+// counters, which the kernel advances (bump) or leaves to the caller.
+int batch_whole(sw_batch* b, uint32_t n_uniform, const uint32_t* d_n_each, bool bump)
 {
-    HIP_TRY(launch_whole(b->d_descs, b->d_list, b->n_whole64, 64, k0, n_uniform, d_n_each, 2u, b->ty, b->stream));
-    HIP_TRY(launch_whole(b->d_descs, b->d_list + b->n_whole64, b->n_whole128, WHOLE_LMAX, k0, n_uniform, d_n_each, 2u,
+    const uint32_t flags = bump ? 0u : 2u;
+    HIP_TRY(launch_whole(b->d_descs, b->d_list, b->n_whole64, 64, 0, n_uniform, d_n_each, flags, b->ty, b->stream));
+    HIP_TRY(launch_whole(b->d_descs, b->d_list + b->n_whole64, b->n_whole128, WHOLE_LMAX, 0, n_uniform, d_n_each, flags,
                          b->ty, b->stream));
     return SW_OK;
 }
@@ -971,7 +972,7 @@ int batch_enqueue(sw_batch* b, const uint32_t* n_each)
     if (kall == 0) return SW_OK;
     b->h_n.assign(n_each, n_each + b->n);
     HIP_TRY(hipMemcpyAsync(b->d_n, b->h_n.data(), b->n * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream));
-    int rc = batch_whole(b, 0, 0, b->d_n);
+    int rc = batch_whole(b, 0, b->d_n, false);
     if (rc) return rc;
     std::vector<uint32_t> prefix;
     if (kmax) {
@@ -1118,15 +1119,14 @@ int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps)
     }
     if (b->n_whole64 + b->n_whole128) {
         // the replicas swept whole first, in launches of at most WHOLE_CHUNK
-        // sweeps; their counters advance with everyone's below
+        // sweeps, each advancing their counters
         for (uint32_t done = 0; done < n_sweeps;) {
             const uint32_t k = std::min(WHOLE_CHUNK, n_sweeps - done);
-            const int rc = batch_whole(b, done, k, nullptr);
+            const int rc = batch_whole(b, k, nullptr, true);
             if (rc) return rc;
             done += k;
         }
         if (b->tile_tiles == 0) {
-            HIP_TRY(launch_bump(b->d_descs, b->n, nullptr, n_sweeps, b->stream));
             for (uint32_t r = 0; r < b->n; ++r) b->done[r] += n_sweeps;
             return SW_OK;
         }
@@ -1143,7 +1143,7 @@ int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps)
     }
     const Work w{b->d_descs, b->d_map, (uint32_t)b->tile_tiles, b->ty, b->stream, b->csum};
     // replicas without a ring skip the measurements inside the kernels
-    const int rc = run_steps(b->steps, w, n_sweeps, true, b->d_descs, b->n);
+    const int rc = run_steps(b->steps, w, n_sweeps, true);
     if (rc) return rc;
     for (uint32_t r = 0; r < b->n; ++r) b->done[r] += n_sweeps;
     return SW_OK;

@@ -1,8 +1,8 @@
 // HIP kernels of one Swendsen-Wang sweep for gfx950, plus their launchers.
 //
 // One sweep is three launches over the tiles of the lattice (TX = 64 columns
-// by TY rows; one workgroup per tile, four waves, eight for 128 rows; one
-// column per lane):
+// by TY rows; one workgroup per tile, one column per lane, four waves, eight
+// for 128 rows, up to sixteen for 64 rows when tiles are few):
 //   k_bond_label  bonds (Sec. 2 step (1)) + tile-local cluster labelling
 //                 + measurement of the configuration the bonds were drawn on
 //   k_merge       joins tile-local clusters across tile edges (global union-find
@@ -205,10 +205,9 @@ __device__ void n_hook2(gptr<uint64_t> nodes, uint32_t n, uint64_t (&a)[2], uint
 // Spins of a tile and its halo in LDS: rows 0..h (row h is the row below the
 // tile, periodic), columns 0..w-1 plus column w = the column right of the tile
 // (periodic).  Row stride SPW bytes.
-template <int TY>
+template <int TY, uint32_t NT>
 __device__ __forceinline__ void stage_spins(uint8_t* sp, const LatDesc& d, const TileGeom& g, uint32_t tid)
 {
-    constexpr uint32_t NT = threads_of<TY>();
     const uint32_t L = d.L, w = g.w, h = g.h;
     const uint32_t yb = (g.y0 + h == L) ? 0u : g.y0 + h;          // row below the tile
     const uint32_t xh = (g.x0 + w == L) ? 0u : g.x0 + w;          // column right of the tile
@@ -382,7 +381,7 @@ extern "C" int sw_phase_clocks(unsigned long long* host, int clear)
 // ---------------------------------------------------------------------------
 // Bonds + tile-local labels (+ measurement of the incoming configuration).
 //
-// Each wave owns a strip of TY/4 consecutive rows and labels it two rows at a
+// Each wave owns a strip of TY/NW consecutive rows and labels it two rows at a
 // time; strips are then stitched along their seams through the same LDS
 // union-find, which always hangs the larger label under the smaller, so the
 // final label of every tile-local cluster is its smallest site.
@@ -395,12 +394,13 @@ extern "C" int sw_phase_clocks(unsigned long long* host, int clear)
 // result of the previous sweep, t - 1).
 // PRESET: the bonds are already in the bond plane (drawn by the XY model's own
 // kernel); the kernel then only labels, and measures nothing.
-template <int TY, bool PRESET = false>
-__global__ __launch_bounds__(threads_of<TY>()) __attribute__((amdgpu_waves_per_eu(8))) void k_bond_label(const LatDesc* descs, const WorkItem* map, uint32_t k,
+template <int TY, uint32_t NW, bool PRESET = false>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) void k_bond_label(const LatDesc* descs, const WorkItem* map, uint32_t k,
                                                    uint32_t flags)
 {
-    constexpr uint32_t NW = waves_of<TY>(), NT = threads_of<TY>();
+    constexpr uint32_t NT = 64 * NW;
     constexpr uint32_t RPW = TY / NW;  // rows per wave (even)
+    static_assert(RPW % 2 == 0, "rows are labelled two at a time");
     static_assert(RPW < 32, "per-lane measurement counters hold at most 31 rows");
     constexpr uint32_t QCAP = qcap_of<TY>();
     __shared__ __align__(16) uint16_t P[TY * TX];   // union-find over the tile's sites
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(threads_of<TY>()) __attribute__((amdgpu_waves_per_e
             rb[r][j / TY] = r < h ? bin[j] : 0ull;
         }
     } else {
-        stage_spins<TY>(sp, d, g, tid);
+        stage_spins<TY, NT>(sp, d, g, tid);
     }
     __syncthreads();
     SW_PHASE(pc, 0);   // staging
@@ -794,8 +794,13 @@ __global__ __launch_bounds__(threads_of<TY>()) __attribute__((amdgpu_waves_per_e
 // Join tile-local clusters across tile edges.  One wave per tile handles the
 // crossing bonds of its right and bottom edges (periodic neighbours): each
 // joins the edge-forest nodes of the two sites' tile-local roots.
+//
+// bump: sweeps to advance each lattice's counter by (0: leave it), done by the
+// wave of its tile 0.  This kernel alone does not read the counter, so a
+// captured step needs no launch of its own to move on to the next sweep; the
+// kernels after it in the step see the counter already moved.
 template <int TY>
-__global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkItem* map, uint32_t nitems)
+__global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkItem* map, uint32_t nitems, uint32_t bump)
 {
     const uint32_t wave = wave_id(), lane = threadIdx.x & 63u;
     const uint32_t idx = blockIdx.x * 4 + wave;
@@ -804,6 +809,7 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
     uint32_t tile, lat;
     if (!pick(descs, map, idx, false, d, tile, lat)) return;
     SW_PHASE_START(pc);
+    if (bump && tile == 0 && lane == 0) *glb(d.counter) += bump;
     const TileGeom g = tile_geom(d, tile, TY);
     const uint32_t EW = edge_words(TY), NS = nslot(TY);
     const uint32_t n = d.ntiles * NS;
@@ -884,11 +890,11 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
 // XY: the draw per cluster is a reflection bit instead of a state, and each
 // site of a reflected cluster has its angle reflected across the line
 // perpendicular to the sweep's direction (the others are not touched).
-template <int TY, bool XY = false>
-__global__ __launch_bounds__(threads_of<TY>()) __attribute__((amdgpu_waves_per_eu(8))) void k_flip(
+template <int TY, uint32_t NW, bool XY = false>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) void k_flip(
     const LatDesc* descs, const WorkItem* map, uint32_t k)
 {
-    constexpr uint32_t NW = waves_of<TY>(), NT = threads_of<TY>();
+    constexpr uint32_t NT = 64 * NW;
     constexpr uint32_t PER = TY / NW;       // rows per wave
     constexpr uint32_t RES16 = 0x4000u;     // a resolved root inside the tile
     constexpr uint32_t NKN = 512;           // node table (>= nslot(TY), a power of two)
@@ -1218,7 +1224,7 @@ __global__ __launch_bounds__(threads_of<TY>()) void k_measure(const LatDesc* des
     const uint32_t w = g.w, h = g.h;
     if (tid < 256) hist[tid] = 0;
     if (tid == 0) tot = 0;
-    stage_spins<TY>(sp, d, g, tid);
+    stage_spins<TY, threads_of<TY>()>(sp, d, g, tid);
     __syncthreads();
     const uint32_t x = lane;
     const bool vx = x < w;
@@ -1405,48 +1411,104 @@ uint32_t init_grid(size_t N)
 #define SWMI_FOUR_WAVES(T) 256
 #define SWMI_TY_DISPATCH(TYV, KERNEL, GRID, ...) SWMI_TY_DISPATCH_B(TYV, KERNEL, GRID, SWMI_TILE_BLOCK, __VA_ARGS__)
 
+// Waves of a tile's workgroup.  A wave walks its strip of rows one after another,
+// so with few tiles, where a sweep is one workgroup's latency, shorter strips
+// on more waves are faster; with many tiles they repeat the work at the strips'
+// seams and leave fewer workgroups per CU to cover each other's barriers.
+// Whole sweeps measured at 64-row tiles, q = 2 (us; labelling with 4 / 16 waves,
+// then flip with 4 / 8 / 16 waves):
+//   16 tiles (L = 200)     31.8 / 28.9    31.8 / 29.6 / 28.5
+//   256 tiles (L = 1001)   43.8 / 39.4    43.8 / 41.5 / 40.4
+//   529 tiles (L = 1448)   49.6 / 55.5    49.6 / 47.3 / 48.0
+//   1024 tiles (L = 2048)  59.2 / 69.2    59.2 / 57.9 / 60.2
+//   2116 tiles (L = 2900)  87.9 / 117.4   87.9 / 89.5 / 95.3
+// so the lines lie at one workgroup per CU (256 tiles) and, for the flip, four.
+// (Labelling with 8 waves: 40.5, 50.0 and 60.6 us at 256, 529 and 1024 tiles,
+// between the other two or no better.)
+constexpr uint32_t CUS = 256;
+
+template <int TY, bool PRESET>
+hipError_t start_bond_label(const Work& w, uint32_t k, uint32_t flags)
+{
+    auto go = [&](auto nw) {
+        constexpr uint32_t NW = decltype(nw)::value;
+        hipLaunchKernelGGL((k_bond_label<TY, NW, PRESET>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k,
+                           flags);
+    };
+    if constexpr (TY == 64) {
+        if (w.nitems <= CUS) go(std::integral_constant<uint32_t, 16>{});
+        else go(std::integral_constant<uint32_t, 4>{});
+    } else {
+        go(std::integral_constant<uint32_t, waves_of<TY>()>{});
+    }
+    return hipGetLastError();
+}
+
+template <int TY, bool XY>
+hipError_t start_flip(const Work& w, uint32_t k)
+{
+    auto go = [&](auto nw) {
+        constexpr uint32_t NW = decltype(nw)::value;
+        hipLaunchKernelGGL((k_flip<TY, NW, XY>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k);
+    };
+    if constexpr (TY == 64) {
+        if (w.nitems <= CUS) go(std::integral_constant<uint32_t, 16>{});
+        else if (w.nitems <= 4 * CUS) go(std::integral_constant<uint32_t, 8>{});
+        else go(std::integral_constant<uint32_t, 4>{});
+    } else {
+        go(std::integral_constant<uint32_t, waves_of<TY>()>{});
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_bond_label(const Work& w, uint32_t k, uint32_t flags)
 {
     if (w.nitems == 0) return hipSuccess;
-    SWMI_TY_DISPATCH(w.ty, k_bond_label, w.nitems, w.descs, w.map, k, flags);
-    return hipGetLastError();
+    switch (w.ty) {
+    case 32: return start_bond_label<32, false>(w, k, flags);
+    case 64: return start_bond_label<64, false>(w, k, flags);
+    case 128: return start_bond_label<128, false>(w, k, flags);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_label_preset(const Work& w)
 {
     if (w.nitems == 0) return hipSuccess;
     switch (w.ty) {
-    case 32: hipLaunchKernelGGL((k_bond_label<32, true>), dim3(w.nitems), dim3(threads_of<32>()), 0, w.stream, w.descs, w.map, 0u, 0u); break;
-    case 64: hipLaunchKernelGGL((k_bond_label<64, true>), dim3(w.nitems), dim3(threads_of<64>()), 0, w.stream, w.descs, w.map, 0u, 0u); break;
-    case 128: hipLaunchKernelGGL((k_bond_label<128, true>), dim3(w.nitems), dim3(threads_of<128>()), 0, w.stream, w.descs, w.map, 0u, 0u); break;
+    case 32: return start_bond_label<32, true>(w, 0, 0);
+    case 64: return start_bond_label<64, true>(w, 0, 0);
+    case 128: return start_bond_label<128, true>(w, 0, 0);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+}
+
+hipError_t launch_flip(const Work& w, uint32_t k)
+{
+    if (w.nitems == 0) return hipSuccess;
+    switch (w.ty) {
+    case 32: return start_flip<32, false>(w, k);
+    case 64: return start_flip<64, false>(w, k);
+    case 128: return start_flip<128, false>(w, k);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_flip_xy(const Work& w, uint32_t k)
 {
     if (w.nitems == 0) return hipSuccess;
     switch (w.ty) {
-    case 32: hipLaunchKernelGGL((k_flip<32, true>), dim3(w.nitems), dim3(threads_of<32>()), 0, w.stream, w.descs, w.map, k); break;
-    case 64: hipLaunchKernelGGL((k_flip<64, true>), dim3(w.nitems), dim3(threads_of<64>()), 0, w.stream, w.descs, w.map, k); break;
-    case 128: hipLaunchKernelGGL((k_flip<128, true>), dim3(w.nitems), dim3(threads_of<128>()), 0, w.stream, w.descs, w.map, k); break;
+    case 32: return start_flip<32, true>(w, k);
+    case 64: return start_flip<64, true>(w, k);
+    case 128: return start_flip<128, true>(w, k);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
-hipError_t launch_merge(const Work& w)
+hipError_t launch_merge(const Work& w, uint32_t bump)
 {
     if (w.nitems == 0) return hipSuccess;
-    SWMI_TY_DISPATCH_B(w.ty, k_merge, (w.nitems + 3) / 4, SWMI_FOUR_WAVES, w.descs, w.map, w.nitems);
-    return hipGetLastError();
-}
-
-hipError_t launch_flip(const Work& w, uint32_t k)
-{
-    if (w.nitems == 0) return hipSuccess;
-    SWMI_TY_DISPATCH(w.ty, k_flip, w.nitems, w.descs, w.map, k);
+    SWMI_TY_DISPATCH_B(w.ty, k_merge, (w.nitems + 3) / 4, SWMI_FOUR_WAVES, w.descs, w.map, w.nitems, bump);
     return hipGetLastError();
 }
 

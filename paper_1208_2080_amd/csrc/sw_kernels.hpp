@@ -22,7 +22,9 @@ struct Work {
 };
 
 hipError_t launch_bond_label(const Work& w, uint32_t k, uint32_t flags);
-hipError_t launch_merge(const Work& w);
+// bump: sweeps the merge advances the counter of every lattice in w by (it does
+// not read it; launches after it see the counter moved)
+hipError_t launch_merge(const Work& w, uint32_t bump = 0);
 hipError_t launch_flip(const Work& w, uint32_t k);
 hipError_t launch_measure(const Work& w, uint32_t k);
 // cluster-size sums of the sweep counter + k (after its flip), for the

@@ -19,6 +19,8 @@
 // with an FP32 estimate deciding whenever u is far from the threshold.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "sw_device.hpp"
 #include "sw_kernels.hpp"
 #include "sw_tile.hpp"
@@ -148,11 +150,10 @@ __device__ __forceinline__ int64_t* xy_record(const LatDesc& d, uint32_t sweep, 
 // call (counter (i, 0, t, 4)): words 0, 1 make the 53-bit uniform of the +x
 // bond, words 2, 3 that of the +y bond.  The bond words go to the tile-major
 // bond plane the labeller reads.
-template <int TY>
-__global__ __launch_bounds__(threads_of<TY>()) __attribute__((amdgpu_waves_per_eu(4))) void k_xy_bonds(const LatDesc* descs, const WorkItem* map, uint32_t k,
+template <int TY, uint32_t NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_xy_bonds(const LatDesc* descs, const WorkItem* map, uint32_t k,
                                                                uint32_t flags)
 {
-    constexpr uint32_t NW = waves_of<TY>();
     constexpr uint32_t RPW = TY / NW;
     __shared__ unsigned long long acc[XY_WORDS];   // n_active, Ex, Ey, Ix, Iy, Mx, My
     __shared__ double sedge[TY], cedge[TY];        // sin, cos of the column right of the tile
@@ -270,16 +271,38 @@ __global__ __launch_bounds__(256) void k_xy_init(const LatDesc* descs, uint32_t 
 
 }  // namespace
 
+// Eight waves a tile where there is at most one tile per CU (a wave's strip of
+// rows is then the kernel's latency), four elsewhere: whole XY sweeps at 64-row
+// tiles with 4 / 8 waves take 45.9 / 41.3 us at 16 tiles, 52.1 / 47.7 at 169,
+// 67.7 / 68.3 at 529, 138.8 / 146.8 at 2116 (each strip evaluates one row more
+// than it owns; 16 waves: 41.0 and 47.5 us at 16 and 169 tiles).
+constexpr uint32_t XY_FEW_TILES = 256;
+
+template <int TY>
+static hipError_t start_xy_bonds(const Work& w, uint32_t k, uint32_t flags)
+{
+    auto go = [&](auto nw) {
+        constexpr uint32_t NW = decltype(nw)::value;
+        hipLaunchKernelGGL((k_xy_bonds<TY, NW>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k, flags);
+    };
+    if constexpr (TY == 64) {
+        if (w.nitems <= XY_FEW_TILES) go(std::integral_constant<uint32_t, 8>{});
+        else go(std::integral_constant<uint32_t, 4>{});
+    } else {
+        go(std::integral_constant<uint32_t, waves_of<TY>()>{});
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_xy_bonds(const Work& w, uint32_t k, uint32_t flags)
 {
     if (w.nitems == 0) return hipSuccess;
     switch (w.ty) {
-    case 32: hipLaunchKernelGGL(k_xy_bonds<32>, dim3(w.nitems), dim3(threads_of<32>()), 0, w.stream, w.descs, w.map, k, flags); break;
-    case 64: hipLaunchKernelGGL(k_xy_bonds<64>, dim3(w.nitems), dim3(threads_of<64>()), 0, w.stream, w.descs, w.map, k, flags); break;
-    case 128: hipLaunchKernelGGL(k_xy_bonds<128>, dim3(w.nitems), dim3(threads_of<128>()), 0, w.stream, w.descs, w.map, k, flags); break;
+    case 32: return start_xy_bonds<32>(w, k, flags);
+    case 64: return start_xy_bonds<64>(w, k, flags);
+    case 128: return start_xy_bonds<128>(w, k, flags);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_xy_init(const LatDesc* descs, size_t N, uint32_t random_start, hipStream_t s)

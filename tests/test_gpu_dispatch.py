@@ -1,0 +1,81 @@
+"""GPU parity at the edges of the rules that pick a kernel: sizes on both sides
+of each line, bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1208_2080_amd import binding
+from paper_1208_2080_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+
+def check(L, q, K=None, seed=7, calls=(1, 2), tile_rows=0, random_start=True):
+    """Sweeps in calls of the given lengths; spins, labels and bonds after each
+    call, every row at the end."""
+    K = wl.critical_coupling(q) if K is None else K
+    print(f"case L={L} q={q} K={K} calls={calls} ty={tile_rows}", flush=True)
+    n = sum(calls)
+    lat = binding.Lattice(L, q, K, seed=seed, random_start=random_start, obs_capacity=max(2, n), tile_rows=tile_rows)
+    ref = oracle.OracleLattice(L, q, K, seed, random_start=random_start)
+    rows = []
+    for c in calls:
+        lat.sweep(c)
+        for _ in range(c):
+            out = ref.sweep()
+            rows.append(out["obs"])
+        assert np.array_equal(lat.spins(), ref.s), "spins"
+        bx, by = lat.bonds()
+        assert np.array_equal(bx, oracle.pack_bonds(out["bx"])), "+x bonds"
+        assert np.array_equal(by, oracle.pack_bonds(out["by"])), "+y bonds"
+        assert np.array_equal(lat.labels(), out["labels"]), "labels"
+    assert np.array_equal(lat.measure(0, n), np.array(rows)), "rows"
+    lat.close()
+
+
+@pytest.mark.parametrize("L", [200, 1024, 1025, 2048, 2049])
+def test_waves_per_tile(L):
+    """Sixteen, eight or four waves a tile, by the number of tiles: 256 tiles and
+    289 (the labelling's line), 1024 and 1089 (the flip's)."""
+    check(L, 2)
+
+
+@pytest.mark.parametrize("L", [200, 1024, 1025])
+def test_waves_per_tile_xy(L):
+    print(f"case XY L={L}", flush=True)
+    lat = binding.XYLattice(L, wl.K_KT_XY, seed=5, obs_capacity=4)
+    ref = oracle.XYOracleLattice(L, wl.K_KT_XY, 5)
+    for c in (1, 2):
+        lat.sweep(c)
+        for _ in range(c):
+            out = ref.sweep()
+        assert np.array_equal(lat.angles(), ref.a)
+        assert np.array_equal(lat.labels(), out["labels"])
+    lat.close()
+
+
+@pytest.mark.parametrize("tile_rows", [0, 64])
+def test_sweep_counters_of_a_mixed_batch(tile_rows):
+    """Replicas swept whole and by tiles advance their own counters over calls
+    of sweep_all and sweep, whatever the order."""
+    reps = [dict(L=L, q=q, K=wl.critical_coupling(q), seed=50 + i, random_start=True)
+            for i, (L, q) in enumerate([(64, 2), (300, 3), (100, 2), (129, 2), (33, 4)])]
+    print(f"case mixed batch ty={tile_rows}", flush=True)
+    b = binding.Batch(reps, obs_capacity=64, tile_rows=tile_rows)
+    b.sweep_all(1)
+    b.sweep_all(18)
+    each = [3, 0, 5, 2, 1]
+    b.sweep(each)
+    b.sweep_all(2)
+    for r, rep in enumerate(reps):
+        ref = oracle.OracleLattice(rep["L"], rep["q"], rep["K"], rep["seed"], random_start=True)
+        n = 21 + each[r]
+        rows = ref.run(n)
+        assert b.sweeps_done(r) == n
+        assert np.array_equal(b.measure(r, 0, n), rows), f"rows of replica {r}"
+        assert np.array_equal(b.spins(r), ref.s), f"spins of replica {r}"
+    b.close()
