@@ -31,31 +31,6 @@ namespace {
 constexpr uint32_t UNITE_CAP = 1u << 12;   // cap of union retries in the global forest
 constexpr uint32_t SPW = TX + 4;           // LDS row stride of staged spins (bytes)
 
-// Lane l's bit of a wave-uniform mask, as a lane predicate.
-__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-
-// Sum over the wave of a per-lane value (all 64 lanes active), in vector
-// instructions only: pairs and quads by quad permutes, rows of 16 by half-row
-// and row mirrors, then the rows' sums broadcast into row 3 (row_bcast:15 into
-// rows 1 and 3, row_bcast:31 into rows 2 and 3), so lane 63 holds the total.
-// Where the scalar unit is the busier one this beats a ballot per bit plane.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
-{
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);            // quad_perm [1,0,3,2]
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);            // quad_perm [2,3,0,1]
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);           // row_half_mirror
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);           // row_mirror
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);     // row_bcast:15
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);     // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// Number of set bits of a wave-uniform mask below this lane.
-__device__ __forceinline__ uint32_t lanes_below(uint64_t m)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
 // ------------------------------------------------------ edge forest (global)
 // One node per tile-local cluster that touches a tile edge.  A node's word is
 // (key << 32) | parent: parent is a node id, key the smallest site index of the
@@ -237,30 +212,6 @@ __device__ __forceinline__ void stage_spins(uint8_t* sp, const LatDesc& d, const
     for (uint32_t r = tid; r <= h; r += NT) {
         const uint32_t y = (r < h) ? g.y0 + r : yb;
         sp[r * SPW + w] = glb(d.s)[(size_t)y * L + xh];
-    }
-}
-
-// Per-lane state counters of the measurement for q <= 16: byte (c & 7) of word
-// (c >> 3) counts this lane's sites in state c (at most 31 rows per lane).
-// q <= 8 needs only the first word (count_state_byte).
-__device__ __forceinline__ void count_state_byte(uint64_t (&w)[2], bool valid, uint32_t s)
-{
-    w[0] += (uint64_t)valid << (8u * (s & 7u));
-}
-
-__device__ __forceinline__ void count_state_bytes(uint64_t (&w)[2], bool valid, uint32_t s)
-{
-    const uint64_t one = (uint64_t)valid << (8u * (s & 7u));
-    w[0] += (s < 8u) ? one : 0ull;
-    w[1] += (s < 8u) ? 0ull : one;
-}
-
-// Wave totals of states 1..q-1 from the per-lane bytes, added into hist.
-__device__ __forceinline__ void flush_state_bytes(const uint64_t (&w)[2], uint32_t* hist, uint32_t q, uint32_t lane)
-{
-    for (uint32_t c = 1; c < q; ++c) {
-        const uint32_t n = wave_sum((uint32_t)(w[c >> 3] >> (8u * (c & 7u))) & 0xFFu);
-        if (lane == 0 && n) atomicAdd(&hist[c], n);
     }
 }
 

@@ -21,6 +21,55 @@ __device__ __forceinline__ uint32_t swap_pair(uint32_t v)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
 }
 
+// Lane l's bit of a wave-uniform mask, as a lane predicate.
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// Sum over the wave of a per-lane value (all 64 lanes active), in vector
+// instructions only: pairs and quads by quad permutes, rows of 16 by half-row
+// and row mirrors, then the rows' sums broadcast into row 3 (row_bcast:15 into
+// rows 1 and 3, row_bcast:31 into rows 2 and 3), so lane 63 holds the total.
+// Where the scalar unit is the busier one this beats a ballot per bit plane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);            // quad_perm [1,0,3,2]
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);            // quad_perm [2,3,0,1]
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);           // row_half_mirror
+    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);           // row_mirror
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);     // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);     // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Number of set bits of a wave-uniform mask below this lane.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Per-lane state counters of the measurement for q <= 16: byte (c & 7) of word
+// (c >> 3) counts this lane's sites in state c (at most 31 rows per lane).
+// q <= 8 needs only the first word (count_state_byte).
+__device__ __forceinline__ void count_state_byte(uint64_t (&w)[2], bool valid, uint32_t s)
+{
+    w[0] += (uint64_t)valid << (8u * (s & 7u));
+}
+
+__device__ __forceinline__ void count_state_bytes(uint64_t (&w)[2], bool valid, uint32_t s)
+{
+    const uint64_t one = (uint64_t)valid << (8u * (s & 7u));
+    w[0] += (s < 8u) ? one : 0ull;
+    w[1] += (s < 8u) ? 0ull : one;
+}
+
+// Wave totals of states 1..q-1 from the per-lane bytes, added into hist.
+__device__ __forceinline__ void flush_state_bytes(const uint64_t (&w)[2], uint32_t* hist, uint32_t q, uint32_t lane)
+{
+    for (uint32_t c = 1; c < q; ++c) {
+        const uint32_t n = wave_sum((uint32_t)(w[c >> 3] >> (8u * (c & 7u))) & 0xFFu);
+        if (lane == 0 && n) atomicAdd(&hist[c], n);
+    }
+}
+
 struct TileGeom {
     uint32_t tx, ty, x0, y0, w, h;
 };
@@ -147,7 +196,7 @@ __device__ __forceinline__ void lds_st(uint16_t* p, uint32_t v)
 }
 
 // min(P[i], v) into entry i; returns the entry's value before.
-__device__ __forceinline__ uint32_t lds_min16(uint16_t* P, uint32_t i, uint32_t v, bool& bad)
+__device__ __forceinline__ uint32_t lds_min(uint16_t* P, uint32_t i, uint32_t v, bool& bad)
 {
     uint32_t* const w = reinterpret_cast<uint32_t*>(P) + (i >> 1);
     const uint32_t sh = (i & 1u) * 16u;
@@ -167,7 +216,8 @@ __device__ __forceinline__ uint32_t lds_min16(uint16_t* P, uint32_t i, uint32_t 
 // so that their LDS round trips overlap, with path splitting: every visited
 // node is pointed at its grandparent (a stored value is always an ancestor,
 // so races with other finds and hooks are benign).
-__device__ __forceinline__ void lds_find2(uint16_t* P, uint32_t& a, uint32_t& b, bool& bad)
+template <class T>
+__device__ __forceinline__ void lds_find2(T* P, uint32_t& a, uint32_t& b, bool& bad)
 {
     uint32_t pa = lds_ld(&P[a]), pb = lds_ld(&P[b]);
     while (pa < a || pb < b) {
@@ -188,13 +238,21 @@ __device__ __forceinline__ void lds_find2(uint16_t* P, uint32_t& a, uint32_t& b,
     bad |= pa != a || pb != b;
 }
 
-__device__ void lds_union(uint16_t* P, uint32_t a, uint32_t b, bool& bad)
+// The same over 32-bit entries, where LDS has room for them: one minimum, no
+// compare-and-swap loop.
+__device__ __forceinline__ uint32_t lds_min(uint32_t* P, uint32_t i, uint32_t v, bool&)
+{
+    return __hip_atomic_fetch_min(&P[i], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <class T>
+__device__ void lds_union(T* P, uint32_t a, uint32_t b, bool& bad)
 {
     for (uint32_t it = 0; it < LDS_CAP; ++it) {
         lds_find2(P, a, b, bad);
         if (a == b) return;
         const uint32_t hi = max(a, b), lo = min(a, b);
-        const uint32_t old = lds_min16(P, hi, lo, bad);
+        const uint32_t old = lds_min(P, hi, lo, bad);
         if (old == hi) return;
         // hi was hooked meanwhile: join its new parent with lo instead
         a = old;

@@ -1,29 +1,42 @@
 // Small lattices swept whole in one workgroup's LDS, many sweeps per launch.
 //
 // A lattice of at most 128 x 128 sites fits a workgroup's LDS with its spins,
-// bonds and union-find; one launch then runs any number of sweeps without
+// draws and union-find; one launch then runs any number of sweeps without
 // touching global memory between them (no per-sweep launches, which is what
 // bounds the tile kernels at these sizes).  Each sweep takes the three steps of
 // Sec. 2 with the same random streams and the same cluster keys as the tile
-// kernels, so results are bit-identical to them (and to the oracle):
-//   (1) bonds: one Philox call per site pair (counter (i >> 1, 0, t, 0), the
-//       pair's words 2b, 2b + 1 for site parity b) against the threshold;
-//       with L even a lane pair draws for two rows at once (lane 2m the pair
-//       of row y, lane 2m + 1 that of row y + 1, halves swapped), as in the
-//       tile kernels, so each call is made once;
-//   (2) labels: every wave takes whole rows; within a row (64 columns at a
-//       time) a site points at the first site of its run of +x bonds (a
-//       ballot, no atomics), then union-find joins the runs along the +y
-//       bonds (one bond per pair of runs), across 64-column chunks and across
-//       the periodic edges, the larger root hooked under the smaller, so each
-//       cluster's root is its smallest site;
-//   (3) every root draws its cluster's state (counter (root, 0, t, 1)), the
-//       roots gathered into a per-wave list and drawn 64 at a time, and every
-//       site copies its root's;
-// then the measurement of the new configuration into the ring record of the
-// sweep (written whole into copy 0, with the whole-record flag).  After the
-// last sweep: the spins go back to global memory, and on request the labels
-// (smallest site indices) and the tile-major bond words of that sweep.
+// kernels, so results are bit-identical to them (and to the oracle).
+//
+// What bounds it is one CU: about 400 SIMD cycles of vector, scalar and LDS
+// instructions per 64 sites in the row step below, and in the other steps
+// chains of dependent LDS accesses.  (L = 64, q = 2 at K_c: 9.6 us a sweep, of
+// which the rows take a quarter, the seams a fifth; 25.2 us for the kernel
+// before, which walked every site to its root through the rows' chains and
+// had seven barriers.  L = 128: 27.7 us, before 54.9.)  So the work is cut to keep chains short: sixteen
+// waves own a strip of whole rows each (one column per lane, 64 columns at a
+// time), everything a strip needs is loaded first, and a sweep has four
+// barriers:
+//   1. bonds and runs: the bonds of a row are wave ballots of its spins and
+//      draws; the runs of +x bonds of a row are bit arithmetic on them (no LDS),
+//      and a run's first site is its node in the union-find.  The first +y bond
+//      into a run makes the run's node point at the node above (bit arithmetic
+//      again: a carry through the run's bonds tells first from later ones); the
+//      other +y bonds, and the +x bonds across 64-column passes and the periodic
+//      edge, are queued and joined 64 at a time.  A run hooked like that takes
+//      the label above, so a strip's chains stay one deep.  The configuration the bonds
+//      are drawn on is the previous sweep's result and is measured here;
+//   2. seams: the +y bonds from the row above a strip (the last strip's for the
+//      first: the periodic edge), joined the same way;
+//   3. roots: a label that points at itself draws its cluster's state (Philox
+//      counter (root, 0, t, 1)), gathered per wave and drawn 64 at a time, and
+//      keeps it in its own entry, tagged; the other labels are pointed at
+//      their roots;
+//   4. every site takes the state, two reads from its label; the draws of the next sweep, which
+//      depend on nothing, are made here (one Philox call per pair of sites in
+//      the order of the site index, counter (i >> 1, 0, t, 0), so odd sizes
+//      cost no more than even ones) and kept as two bits per site.
+// After the last sweep the spins go back to global memory, and on request the
+// labels (smallest site indices) and the tile-major bond words of that sweep.
 #include <hip/hip_runtime.h>
 
 #include "sw_device.hpp"
@@ -34,28 +47,16 @@ namespace swmi {
 
 namespace {
 
-template <int LMAX>
-constexpr uint32_t whole_threads() { return LMAX <= 64 ? 512u : 1024u; }
+constexpr uint32_t WHOLE_NT = 1024;               // sixteen waves
+constexpr uint32_t WHOLE_NW = WHOLE_NT / 64;
+constexpr uint32_t TAG = 0x8000u;                 // a root's entry once it holds its state
 
-// The states of the wave's lanes counted into hist (LDS): one pass per
-// distinct state present in the wave.
-__device__ __forceinline__ void count_wave_states(uint32_t* hist, bool valid, uint32_t s)
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ uint64_t uniform64(uint64_t v)
 {
-    uint64_t left = ballot(valid);
-    while (left) {
-        const uint32_t first = (uint32_t)__builtin_ctzll(left);
-        const uint32_t c = __builtin_amdgcn_readlane(s, first);
-        const uint64_t same = ballot(valid && s == c);
-        if ((threadIdx.x & 63u) == 0) atomicAdd(&hist[c], (uint32_t)__popcll(same));
-        left &= ~same;
-    }
-}
-
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += (uint32_t)__shfl_xor((int)v, o);
-    return v;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // Sweeps counter + k0 .. counter + k0 + n - 1.  flags bit 0: write the labels
@@ -63,28 +64,34 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 // advances it), else set it past the last sweep.  ty: tile height of the
 // lattice's bond-word layout.
 template <int LMAX>
-__global__ __launch_bounds__(whole_threads<LMAX>()) void k_whole(const LatDesc* descs, const uint32_t* list,
-                                                                  uint32_t k0, uint32_t n_uniform,
-                                                                  const uint32_t* n_each, uint32_t flags, uint32_t ty)
+__global__ __launch_bounds__(WHOLE_NT) void k_whole(const LatDesc* descs, const uint32_t* list, uint32_t k0,
+                                                    uint32_t n_uniform, const uint32_t* n_each, uint32_t flags,
+                                                    uint32_t ty)
 {
-    constexpr uint32_t NT = whole_threads<LMAX>();
+    constexpr uint32_t NT = WHOLE_NT, NW = WHOLE_NW;
+    constexpr uint32_t CH = LMAX / 64;                // 64-column passes of a row
+    constexpr uint32_t RP = LMAX / NW;                // rows of a strip, at most
     constexpr uint32_t NMAX = LMAX * LMAX;
-    __shared__ uint8_t s[NMAX];
-    __shared__ uint8_t bnd[NMAX];                     // bit 0: +x bond, bit 1: +y bond
-    __shared__ __align__(16) uint16_t P[NMAX];
+    constexpr uint32_t SPS = LMAX + 4;                // row stride of the spins
+    constexpr uint32_t QCAP = 256;
+    __shared__ uint8_t s[LMAX * SPS];                 // spins
+    __shared__ __align__(16) uint8_t D[NMAX + 128];   // per site: bit 0 +x draw below the threshold, bit 1 +y
+    __shared__ uint32_t P[NMAX];                      // union-find over the runs' first sites
+    __shared__ uint32_t UQ[NW][QCAP];                 // per wave: queued unions (two 16-bit sites), then roots
+    __shared__ uint16_t HB[NW][LMAX];                 // per strip: the labels of its last row, by column
+    __shared__ uint16_t LN[NW][CH][RP];               // per strip: the node of the last site of each row's pass
+    __shared__ uint64_t MB[NW][CH][2];                // per strip: its last row's +y bonds and run links
+    __shared__ uint64_t BW[LMAX][CH][2];              // the last sweep's bond words
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t tot[2];                       // n_unsat, n_active
-    constexpr uint32_t QCAP = 256;                    // per wave: queued unions (two 16-bit sites each)
-    __shared__ uint32_t UQ[NT / 64][QCAP];
+    __shared__ uint32_t tot[2];                       // equal pairs, active bonds
 
     const uint32_t lat = list ? list[blockIdx.x] : blockIdx.x;
     const LatDesc d = descs[lat];
     const uint32_t n = n_each ? n_each[lat] : n_uniform;
     if (n == 0) return;
-    constexpr uint32_t NW = NT / 64;
     const uint32_t L = d.L, N = L * L, q = d.q;
-    const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u;
-    if (L > LMAX) {   // (the host sorts lattices by size; never taken)
+    const uint32_t tid = threadIdx.x, wave = wave_id(), lane = tid & 63u;
+    if (L > (uint32_t)LMAX) {   // (the host sorts lattices by size; never taken)
         if (tid == 0) flag_error(d.err);
         return;
     }
@@ -92,220 +99,320 @@ __global__ __launch_bounds__(whole_threads<LMAX>()) void k_whole(const LatDesc* 
     const bool meas = d.cap != 0;
     bool bad = false;
 
-    auto right = [&](uint32_t i, uint32_t x) { return (x + 1 == L) ? i - x : i + 1; };
-    auto down = [&](uint32_t i, uint32_t x, uint32_t y) { return (y + 1 == L) ? x : i + L; };
+    // this wave's strip: rows y0 .. y0 + rows - 1 of ns strips
+    const uint32_t rps = (L + NW - 1) / NW, ns = (L + rps - 1) / rps;
+    const uint32_t y0 = wave * rps, rows = wave < ns ? min(rps, L - y0) : 0u;
+    auto columns = [&](uint32_t c) -> uint64_t {   // valid lanes of pass c
+        const uint32_t w = L > 64 * c ? min(64u, L - 64 * c) : 0u;
+        return w == 64 ? ~0ull : (1ull << w) - 1ull;
+    };
+    const uint32_t last_c = (L - 1) / 64, last_lane = (L - 1) & 63u;
+    auto below = [&](uint32_t y) { return y + 1 == L ? 0u : y + 1; };
+    uint32_t xr[CH];   // the column to the right, per pass
+#pragma unroll
+    for (uint32_t c = 0; c < CH; ++c) xr[c] = 64 * c + lane + 1 == L ? 0u : 64 * c + lane + 1;
+    const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
 
-    for (uint32_t i = tid; i < N; i += NT) s[i] = glb(d.s)[i];
+    for (uint32_t i = tid; i < N; i += NT) {
+        const uint32_t y = div_L(d, i), x = i - y * L;
+        s[y * SPS + x] = glb(d.s)[i];
+    }
+    if (tid < 256) hist[tid] = 0;
+    if (tid < 2) tot[tid] = 0;
+
+    auto draws = [&](uint32_t t) {
+        const uint32_t pairs = (N + 1) >> 1;
+        for (uint32_t p = tid; p < pairs; p += NT) {
+            const u32x4 w = philox4x32_10(p, 0u, t, 0u, d.key0, d.key1);
+            uint32_t b = 0;
+            if (d.thr_nz)
+                b = (uint32_t)(w.x <= d.thr_m1) | ((uint32_t)(w.y <= d.thr_m1) << 1) |
+                    ((uint32_t)(w.z <= d.thr_m1) << 8) | ((uint32_t)(w.w <= d.thr_m1) << 9);
+            reinterpret_cast<uint16_t*>(D)[p] = (uint16_t)b;
+        }
+    };
+    draws(t0);
     __syncthreads();
 
+    // equal pairs (per wave) and state counts of the strip's rows, added to tot
+    // and hist; the loop below calls count_row for its own loads
+    uint32_t n_eq = 0, ones = 0;
+    uint64_t packed[2] = {0ull, 0ull};
+    const bool q2 = q == 2, q8 = q <= 8, q16 = q <= 16;
+    auto count_row = [&](uint64_t vm, uint32_t s0, uint64_t EX, uint64_t EY) {
+        n_eq += popc64(EX) + popc64(EY);
+        if (q2) {
+            ones += popc64(ballot(s0 != 0) & vm);
+            return;
+        }
+        const bool v = lane_in(vm);
+        if (q8) count_state_byte(packed, v, s0);
+        else if (q16) count_state_bytes(packed, v, s0 & 15u);
+        else if (v && s0) atomicAdd(&hist[s0], 1u);
+    };
+    auto count_flush = [&]() {
+        if (lane == 0) {
+            atomicAdd(&tot[0], n_eq);
+            if (q2) atomicAdd(&hist[1], ones);
+        }
+        if (q16 && !q2) flush_state_bytes(packed, hist, q, lane);
+        n_eq = ones = 0;
+        packed[0] = packed[1] = 0ull;
+    };
+    // the record of sweep t: its counts are in tot[0] and hist, written whole
+    // into copy 0 with the whole-record flag
+    const uint32_t words = NCOPY * ring_stride(q);
+    uint32_t slot = meas ? t0 % d.cap : 0u;   // the next record to write
+    auto write_record = [&](uint32_t active) {
+        const gptr<int64_t> rec = glb(d.ring) + (size_t)slot * words;
+        slot = slot + 1 == d.cap ? 0u : slot + 1;
+        if (tid == 0) {
+            rec[0] = 2ll * N - tot[0];
+            rec[1] = active;
+            rec[ring_words(q)] = 1;
+        }
+        if (tid >= 1 && tid < q) rec[1 + tid] = hist[tid];
+    };
+
+    uint32_t active_prev = 0;   // n_active of the previous sweep (every thread)
     for (uint32_t k = 0; k < n; ++k) {
         const uint32_t t = t0 + k;
-        if (tid < 256) hist[tid] = 0;
-        if (tid < 2) tot[tid] = 0;
-        // (1) bonds, row by row (64 columns per pass, one column per lane), each
-        // site's two draws from its pair's Philox call; each site points at the
-        // first site of its run
-        uint32_t active = 0;
-        {
-        auto bond_row = [&](uint32_t y, uint32_t x0, uint32_t wx, uint32_t wy) {
-            const uint32_t x = x0 + lane, i = y * L + x;
-            const bool v = x < L;
-            bool bx = false, by = false;
-            if (v) {
-                const uint32_t si = s[i];
-                bx = d.thr_nz && si == s[right(i, x)] && wx <= d.thr_m1;
-                by = d.thr_nz && si == s[down(i, x, y)] && wy <= d.thr_m1;
-                bnd[i] = (uint8_t)((bx ? 1u : 0u) | (by ? 2u : 0u));
-            }
-            active += (uint32_t)bx + (uint32_t)by;
-            const uint64_t validm = ballot(v);
-            const uint64_t C = (ballot(bx) << 1) & validm;   // bit x: bond (x-1) -> x inside the pass
-            const uint64_t S = ~C & validm;                  // first sites of runs
-            const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-            if (v) P[i] = (uint16_t)(y * L + x0 + 63u - (uint32_t)__builtin_clzll(S & upto));
-        };
-        if ((L & 1u) == 0) {
-            // wave w takes the row pairs (2w, 2w + 1), (2w + 2 NW, ...), ...; a
-            // pass's valid lanes come in whole pairs (L and 64 are even)
-            const bool odd = lane & 1u;
-            for (uint32_t y = 2 * wave; y < L; y += 2 * NW) {
-                for (uint32_t x0 = 0; x0 < L; x0 += TX) {
-                    const uint32_t pair = ((odd ? (y + 1) * L : y * L) + x0 + (lane & ~1u)) >> 1;
-                    const u32x4 q4 = philox4x32_10(pair, 0u, t, 0u, d.key0, d.key1);
-                    const uint32_t recv0 = swap_pair(odd ? q4.x : q4.z);
-                    const uint32_t recv1 = swap_pair(odd ? q4.y : q4.w);
-                    bond_row(y, x0, odd ? recv0 : q4.x, odd ? recv1 : q4.y);
-                    bond_row(y + 1, x0, odd ? q4.z : recv0, odd ? q4.w : recv1);
-                }
-            }
-        } else {
-            // wave w takes rows w, w + NW, ...; each lane its own site's call
-            for (uint32_t y = wave; y < L; y += NW) {
-                for (uint32_t x0 = 0; x0 < L; x0 += TX) {
-                    const uint32_t i = y * L + x0 + lane;
-                    const u32x4 w = philox4x32_10(i >> 1, 0u, t, 0u, d.key0, d.key1);
-                    bond_row(y, x0, (i & 1u) ? w.z : w.x, (i & 1u) ? w.w : w.y);
-                }
-            }
-        }
-        }
-        __syncthreads();
-        // (2) unions, queued per wave and run 64 at a time with every lane busy
-        // (the cost of a union is a few dependent LDS round trips, so batches
-        // matter more than counts): the +x bonds leaving a 64-column pass
-        // (into the next pass or across the periodic edge) and the +y bonds
-        // between runs (one per pair of runs: a bond whose left neighbour joins
-        // the same two runs adds nothing); each wave takes a strip of rows, and
-        // the +y bonds out of a strip's last row are joined after a barrier
+        const bool meas_prev = meas && k > 0;
+        const bool out = (flags & 1u) && k + 1 == n;   // the last sweep's bonds and labels are wanted
         uint32_t qn = 0;   // wave-uniform
         auto drain = [&]() {
             for (uint32_t j0 = 0; j0 < qn; j0 += 64) {
                 const uint32_t j = j0 + lane;
                 if (j < qn) {
-                    const uint32_t e = UQ[wave][j];
+                    const uint32_t e = lds_ld(&UQ[wave][j]);
                     lds_union(P, e & 0xFFFFu, e >> 16, bad);
                 }
             }
             qn = 0;
         };
         auto push = [&](uint64_t m, uint32_t a, uint32_t b) {
-            const uint32_t at = qn + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-            if ((m >> lane) & 1ull) UQ[wave][at] = a | (b << 16);
-            qn += (uint32_t)__popcll(m);
-            if (qn > QCAP - 64) drain();
+            if (lane_in(m)) lds_st(&UQ[wave][qn + lanes_below(m)], a | (b << 16));
+            qn += popc64(m);
         };
-        auto vertical = [&](uint32_t y, uint32_t x0) {
-            const uint32_t yd = (y + 1 == L) ? 0u : y + 1;
-            const uint32_t x = x0 + lane, i = y * L + x;
-            const bool v = x < L;
-            const uint32_t b = v ? bnd[i] : 0u, bd = v ? bnd[yd * L + x] : 0u;
-            const uint64_t validm = ballot(v);
-            const uint64_t V = ballot(b & 2u);
-            const uint64_t Cu = (ballot(b & 1u) << 1) & validm, Cd = (ballot(bd & 1u) << 1) & validm;
-            const uint64_t R = V & (V << 1) & Cu & Cd;
-            push(V & ~R, i, yd * L + x);
-        };
-        const uint32_t rps = (L + NW - 1) / NW;   // rows of a wave's strip
-        const uint32_t y_lo = min(L, wave * rps), y_hi = min(L, y_lo + rps);
-        for (uint32_t y = y_lo; y < y_hi; ++y) {
-            for (uint32_t x0 = 0; x0 < L; x0 += TX) {
-                const uint32_t x = x0 + lane, i = y * L + x;
-                const bool out = x < L && (bnd[i] & 1u) && (lane == 63 || x + 1 == L);
-                push(ballot(out), i, x < L ? right(i, x) : 0u);
-            }
-            if (y + 1 < y_hi)
-                for (uint32_t x0 = 0; x0 < L; x0 += TX) vertical(y, x0);
-        }
-        drain();
-        __syncthreads();
-        if (y_lo < y_hi)
-            for (uint32_t x0 = 0; x0 < L; x0 += TX) vertical(y_hi - 1, x0);
-        drain();
-        __syncthreads();
-        // every entry straight to its root: the forest is final, so a site walks
-        // to its root reading only and stores it; a walk passing a stored entry
-        // meets the same root (entries only ever point at ancestors)
-        for (uint32_t i = tid; i < N; i += NT) {
-            uint32_t r = i, p = lds_ld(&P[r]);
-            for (uint32_t it = 0; p < r && it < LDS_CAP; ++it) {
-                r = p;
-                p = lds_ld(&P[r]);
-            }
-            bad |= p != r;
-            lds_st(&P[i], r);
-        }
-        __syncthreads();
-        // (3) roots draw their clusters' states, gathered into the wave's queue
-        // (free after the unions) and drawn 64 at a time, then every site takes
-        // its root's
-        {
-            uint32_t nr = 0;   // wave-uniform
-            auto draw = [&]() {
-                for (uint32_t j0 = 0; j0 < nr; j0 += 64) {
-                    const uint32_t j = j0 + lane;
-                    if (j < nr) {
-                        const uint32_t r = UQ[wave][j];
-                        s[r] = (uint8_t)state_of_draw(philox4x32_10(r, 0u, t, 1u, d.key0, d.key1).x, q);
+        // ---- 1. bonds, runs, measurement of the incoming configuration
+        uint32_t lab[RP][CH];                   // labels of the lane's sites
+        uint64_t C0[CH] = {};                   // run links of the strip's first row
+        uint64_t Vp[CH] = {}, Cp[CH] = {};      // +y bonds and run links of the row above
+        uint32_t n_act = 0, wrap = 0, join = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < RP; ++j) {
+            if (j >= rows) break;
+            const uint32_t y = y0 + j;
+            if (qn > QCAP - 64 * CH) drain();
+#pragma unroll
+            for (uint32_t c = 0; c < CH; ++c) {
+                const uint32_t x = 64 * c + lane, li = y * L + x;
+                const uint64_t vm = columns(c);
+                const uint32_t s0 = s[y * SPS + x], sr = s[y * SPS + xr[c]], sd = s[below(y) * SPS + x], dd = D[li];
+                const uint64_t EX = ballot(s0 == sr) & vm, EY = ballot(s0 == sd) & vm;
+                const uint64_t BX = EX & ballot(dd & 1u), BY = EY & ballot(dd & 2u);
+                if (meas_prev) count_row(vm, s0, EX, EY);
+                n_act += popc64(BX) + popc64(BY);
+                const uint64_t C = (BX << 1) & vm;   // bit x: linked to x - 1
+                const uint64_t S = ~C & vm;          // first sites of runs
+                const uint32_t h = y * L + 64 * c + 63u - (uint32_t)__builtin_clzll((S & upto) | 1ull);
+                if (j == 0) {
+                    C0[c] = C;
+                    if (lane_in(S)) lds_st(&P[li], li);
+                    lab[j][c] = h;
+                } else {
+                    const uint64_t V = Vp[c];
+                    // sites above whose run here has a +y bond further left: a
+                    // carry from a bond runs to the end of its run
+                    const uint64_t X = (V << 1) & C;
+                    const uint64_t later = (C & ~(C + X)) | X;
+                    // a run's label: its first site, or the label above its first
+                    // +y bond; its first site's entry carries the choice to all
+                    // its sites (LDS accesses of a wave are done in order)
+                    const uint32_t lp = lab[j > 0 ? j - 1 : 0][c];
+                    if (lane_in(S)) lds_st(&P[li], li);
+                    if (lane_in(V & ~later)) lds_st(&P[h], lp);
+                    const uint32_t l = lds_ld(&P[h]);
+                    lab[j][c] = l;
+                    // bonds x-1 and x from one run above into one run here add nothing
+                    push(V & later & ~((V << 1) & C & Cp[c]) & ballot(l != lp), lp, l);
+                }
+                // across the passes and the periodic edge: one bit a row, joined below
+                if (c == last_c) wrap |= (uint32_t)((BX >> last_lane) & 1u) << j;
+                else if (c < last_c) join |= (uint32_t)(BX >> 63) << j;
+                if (lane == (c == last_c ? last_lane : 63u)) LN[wave][c][j] = (uint16_t)h;
+                Vp[c] = BY;
+                Cp[c] = C;
+                if (j + 1 == rows) {
+                    HB[wave][x] = (uint16_t)lab[j][c];
+                    if (lane == 0) {
+                        MB[wave][c][0] = BY;
+                        MB[wave][c][1] = C;
                     }
                 }
-                nr = 0;
+                if (out && lane == 0) {
+                    BW[y][c][0] = BX;
+                    BW[y][c][1] = BY;
+                }
+            }
+        }
+        {
+            // (a run's first site is its node: column 0 and column 64 start runs,
+            // the node of a row's last site was kept by its lane)
+            const uint32_t row = (y0 + lane) * L;
+            push(wrap, LN[wave][last_c][lane & (RP - 1)], row);
+            if (CH > 1) push(join, LN[wave][0][lane & (RP - 1)], row + 64);
+        }
+        drain();
+        if (meas) {
+            if (meas_prev) count_flush();
+            if (lane == 0 && n_act) atomicAdd(&tot[1], n_act);
+        }
+        __syncthreads();
+        // ---- 2. seams
+        uint32_t active = 0;
+        if (meas) {
+            active = tot[1];
+            if (meas_prev) write_record(active_prev);
+        }
+        if (rows) {
+            const uint32_t pw = wave ? wave - 1 : ns - 1;
+#pragma unroll
+            for (uint32_t c = 0; c < CH; ++c) {
+                const uint64_t mv = MB[pw][c][0], mc = MB[pw][c][1];
+                const uint32_t up = HB[pw][64 * c + lane];
+                const uint64_t V = uniform64(mv), Cu = uniform64(mc);
+                push(V & ~((V << 1) & C0[c] & Cu) & ballot(up != lab[0][c]), up, lab[0][c]);
+            }
+            drain();
+        }
+        __syncthreads();
+        // ---- 3. roots draw their clusters' states; every other label's entry is
+        // pointed at its root (labels are first sites of runs that took no label
+        // from above, so their own lanes know them)
+        {
+            auto draw = [&]() {
+                for (uint32_t j0 = 0; j0 < qn; j0 += 64) {
+                    const uint32_t j = j0 + lane;
+                    if (j < qn) {
+                        const uint32_t r = lds_ld(&UQ[wave][j]);
+                        lds_st(&P[r], TAG | state_of_draw(philox4x32_10(r, 0u, t, 1u, d.key0, d.key1).x, q));
+                    }
+                }
+                qn = 0;
             };
-            for (uint32_t i0 = 0; i0 < N; i0 += NT) {
-                const uint32_t i = i0 + tid;
-                const bool root = i < N && P[i] == i;
-                const uint64_t m = ballot(root);
-                if (root) UQ[wave][nr + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = i;
-                nr += (uint32_t)__popcll(m);
-                if (nr > QCAP - 64) draw();
+            uint32_t p[RP][CH];
+#pragma unroll
+            for (uint32_t j = 0; j < RP; ++j)
+#pragma unroll
+                for (uint32_t c = 0; c < CH; ++c) {
+                    const uint32_t li = (y0 + j) * L + 64 * c + lane;
+                    p[j][c] = (j < rows && lane_in(columns(c)) && lab[j][c] == li) ? lds_ld(&P[li]) : 0xFFFFFFFFu;
+                }
+#pragma unroll
+            for (uint32_t j = 0; j < RP; ++j) {
+                if (j >= rows) break;
+                if (qn > QCAP - 64 * CH) draw();
+#pragma unroll
+                for (uint32_t c = 0; c < CH; ++c) {
+                    const uint32_t li = (y0 + j) * L + 64 * c + lane;
+                    const uint64_t m = ballot(p[j][c] == li);
+                    if (lane_in(m)) lds_st(&UQ[wave][qn + lanes_below(m)], li);
+                    qn += popc64(m);
+                }
             }
             draw();
-        }
-        __syncthreads();
-        for (uint32_t i = tid; i < N; i += NT) {
-            const uint32_t r = P[i];
-            if (r != i) s[i] = s[r];
-        }
-        __syncthreads();
-        if (meas) {
-            // the new configuration: unequal nearest-neighbour pairs, states
-            uint32_t unsat = 0;
-            for (uint32_t i0 = 0; i0 < N; i0 += NT) {   // every lane of a wave takes part in the counting
-                const uint32_t i = i0 + tid;
-                const bool v = i < N;
-                uint32_t si = 0;
-                if (v) {
-                    const uint32_t y = div_L(d, i), x = i - y * L;
-                    si = s[i];
-                    unsat += (uint32_t)(si != s[right(i, x)]) + (uint32_t)(si != s[down(i, x, y)]);
+#pragma unroll
+            for (uint32_t j = 0; j < RP; ++j) {
+                if (j >= rows) break;
+#pragma unroll
+                for (uint32_t c = 0; c < CH; ++c) {
+                    const uint32_t li = (y0 + j) * L + 64 * c + lane;
+                    uint32_t r = p[j][c];
+                    if (r < li) {   // (not a root; entries only point at smaller sites)
+                        uint32_t up = lds_ld(&P[r]);
+                        while (up < r) {
+                            r = up;
+                            up = lds_ld(&P[r]);
+                        }
+                        bad |= up != r && !(up & TAG);
+                        lds_st(&P[li], r);
+                    }
                 }
-                count_wave_states(hist, v, si);
             }
-            const uint32_t us = wave_sum_u32(unsat), ac = wave_sum_u32(active);
-            if ((tid & 63u) == 0) {
-                atomicAdd(&tot[0], us);
-                atomicAdd(&tot[1], ac);
-            }
-            __syncthreads();
-            // the whole record into copy 0, flagged as whole
-            const gptr<int64_t> rec = glb(d.ring) + (size_t)(t % d.cap) * NCOPY * ring_stride(q);
-            if (tid == 0) {
-                rec[0] = tot[0];
-                rec[1] = tot[1];
-                rec[ring_words(q)] = 1;
-            }
-            if (tid >= 1 && tid < q) rec[1 + tid] = hist[tid];
-            __syncthreads();
         }
+        __syncthreads();
+        // ---- 4. every site takes its cluster's state: its label's entry is the
+        // root's state or the root, whose entry is the state
+        {
+            uint32_t e[RP][CH], st[RP][CH];
+#pragma unroll
+            for (uint32_t j = 0; j < RP; ++j)
+#pragma unroll
+                for (uint32_t c = 0; c < CH; ++c) {
+                    const bool in = j < rows && lane_in(columns(c));
+                    e[j][c] = in ? lab[j][c] : 0u;
+                    st[j][c] = lds_ld(&P[e[j][c]]);
+                }
+#pragma unroll
+            for (uint32_t j = 0; j < RP; ++j)
+#pragma unroll
+                for (uint32_t c = 0; c < CH; ++c)
+                    if (!(st[j][c] & TAG)) {
+                        e[j][c] = st[j][c];
+                        st[j][c] = lds_ld(&P[e[j][c]]);
+                    }
+#pragma unroll
+            for (uint32_t j = 0; j < RP; ++j) {
+                if (j >= rows) break;
+#pragma unroll
+                for (uint32_t c = 0; c < CH; ++c) {
+                    const uint32_t y = y0 + j, x = 64 * c + lane;
+                    if (x < L) {
+                        const uint8_t v = (uint8_t)st[j][c];
+                        bad |= !(st[j][c] & TAG);
+                        s[y * SPS + x] = v;
+                        if (out) glb(d.lab)[y * L + x] = e[j][c];
+                    }
+                }
+            }
+            if (k + 1 < n) draws(t + 1);
+            if (meas) {
+                if (tid < 256) hist[tid] = 0;
+                if (tid < 2) tot[tid] = 0;
+            }
+            active_prev = active;
+        }
+        __syncthreads();
     }
 
-    // back to global memory: spins, and on request the last sweep's labels and bonds
-    for (uint32_t i = tid; i < N; i += NT) glb(d.s)[i] = s[i];
-    if (flags & 1u) {
-        for (uint32_t i = tid; i < N; i += NT) glb(d.lab)[i] = P[i];
-        // bond words, tile-major (tile, plane, row), one ballot per row, plane
-        // and 64-column tile; wave w takes rows w, w + NT/64, ...
-        for (uint32_t y = wave; y < L; y += NT / 64) {
-            for (uint32_t x0 = 0; x0 < L; x0 += TX) {
-                const uint32_t x = x0 + lane;
-                const uint32_t b = x < L ? bnd[y * L + x] : 0u;
-                const uint64_t bx = ballot(b & 1u), by = ballot(b & 2u);
-                const size_t tile = (size_t)(y / ty) * d.ntx + x0 / TX;
-                const uint32_t r = y % ty;
-                if (lane == 0) {
-                    glb(d.bonds)[(tile * 2 + 0) * ty + r] = bx;
-                    glb(d.bonds)[(tile * 2 + 1) * ty + r] = by;
-                }
-            }
-        }
-    }
-    // the record after the last one starts from zero (the tile kernels add into it)
     if (meas) {
-        const uint32_t words = NCOPY * ring_stride(q);
-        const gptr<int64_t> rec = glb(d.ring) + (size_t)((t0 + n) % d.cap) * words;
+        // the last sweep's result
+        for (uint32_t j = 0; j < rows; ++j)
+            for (uint32_t c = 0; c <= last_c; ++c) {
+                const uint32_t y = y0 + j, x = 64 * c + lane;
+                const uint64_t vm = columns(c);
+                const uint32_t s0 = s[y * SPS + x], sr = s[y * SPS + (x + 1 == L ? 0u : x + 1)], sd = s[below(y) * SPS + x];
+                count_row(vm, s0, ballot(s0 == sr) & vm, ballot(s0 == sd) & vm);
+            }
+        count_flush();
+        __syncthreads();
+        write_record(active_prev);
+        // the record after it starts from zero (the tile kernels add into it)
+        const gptr<int64_t> rec = glb(d.ring) + (size_t)slot * words;
         for (uint32_t i = tid; i < words; i += NT) rec[i] = 0;
     }
+    for (uint32_t i = tid; i < N; i += NT) {
+        const uint32_t y = div_L(d, i), x = i - y * L;
+        glb(d.s)[i] = s[y * SPS + x];
+    }
+    if (flags & 1u) {
+        for (uint32_t i = tid; i < L * CH * 2; i += NT) {
+            const uint32_t y = i / (CH * 2), c = (i / 2) % CH, pl = i & 1u;
+            if (c <= last_c) glb(d.bonds)[((size_t)((y / ty) * d.ntx + c) * 2 + pl) * ty + y % ty] = BW[y][c][pl];
+        }
+    }
     if (bad) flag_error(d.err);
-    __syncthreads();
     if (tid == 0 && !(flags & 2u)) *glb(d.counter) = t0 + n;
 }
 
@@ -316,10 +423,10 @@ hipError_t launch_whole(const LatDesc* descs, const uint32_t* list, uint32_t cou
 {
     if (count == 0) return hipSuccess;
     if (lmax <= 64)
-        hipLaunchKernelGGL(k_whole<64>, dim3(count), dim3(whole_threads<64>()), 0, s, descs, list, k0, n_uniform,
+        hipLaunchKernelGGL(k_whole<64>, dim3(count), dim3(WHOLE_NT), 0, s, descs, list, k0, n_uniform,
                            n_each, flags, ty);
     else if (lmax <= WHOLE_LMAX)
-        hipLaunchKernelGGL(k_whole<128>, dim3(count), dim3(whole_threads<128>()), 0, s, descs, list, k0, n_uniform,
+        hipLaunchKernelGGL(k_whole<128>, dim3(count), dim3(WHOLE_NT), 0, s, descs, list, k0, n_uniform,
                            n_each, flags, ty);
     else
         return hipErrorInvalidValue;

@@ -79,3 +79,21 @@ def test_sweep_counters_of_a_mixed_batch(tile_rows):
         assert np.array_equal(b.measure(r, 0, n), rows), f"rows of replica {r}"
         assert np.array_equal(b.spins(r), ref.s), f"spins of replica {r}"
     b.close()
+
+
+@pytest.mark.parametrize("L,q", [(2, 2), (16, 3), (17, 2), (48, 2), (49, 8), (63, 9), (64, 17), (65, 2), (113, 4),
+                                 (127, 16), (128, 255)])
+def test_whole_lattice_strips(L, q):
+    """One to eight rows a strip, one and two passes of columns, full and partial
+    strips and passes, every way the states are counted; the rows of the first
+    sweep of a call, of later ones and of the last."""
+    check(L, q, calls=(1, 2, 9), tile_rows=binding.SW_TILE_WHOLE)
+
+
+@pytest.mark.parametrize("K", [0.0, float("inf")])
+@pytest.mark.parametrize("L", [5, 64, 128])
+def test_whole_lattice_extreme_couplings(L, K):
+    """No bond at all, and one cluster holding every equal bond (the longest
+    chains and the fullest queues, from a cold start too)."""
+    check(L, 2, K=K, calls=(2, 3), tile_rows=binding.SW_TILE_WHOLE)
+    check(L, 2, K=K, calls=(2,), tile_rows=binding.SW_TILE_WHOLE, random_start=False)
