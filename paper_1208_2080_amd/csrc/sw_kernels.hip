@@ -1067,10 +1067,16 @@ __device__ __forceinline__ void cs_add(unsigned long long* sums, uint64_t c)
     add_u128(&sums[1], &sums[2], (unsigned __int128)c2 * c2, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-template <int TY>
-__global__ __launch_bounds__(threads_of<TY>()) void k_csize(const LatDesc* descs, const WorkItem* map, uint32_t k)
+// k_csize is bound by latency (a chain of LDS reads per site): one wave takes
+// whole rows, a run of equal roots along a row adds its length at once, and the
+// sums of |C|^2 and |C|^4 over the clusters inside the tile stay in registers
+// until one reduction per wave (in 64 bits: a tile's sizes add up to at most
+// 2^13, so the fourth powers to at most 2^52).  The 198 tiles of 36 replicas of
+// L = 32 ... 256, q = 2 near K_c: 12.0 us a sweep, 32.2 with an LDS atomic per
+// site and three per cluster on the sums.
+template <int TY, uint32_t NW>
+__global__ __launch_bounds__(64 * NW) void k_csize(const LatDesc* descs, const WorkItem* map, uint32_t k)
 {
-    constexpr uint32_t NT = threads_of<TY>();
     __shared__ uint16_t E[TY * TX];
     __shared__ uint32_t C[TY * TX];
     __shared__ unsigned long long sums[3];
@@ -1080,43 +1086,60 @@ __global__ __launch_bounds__(threads_of<TY>()) void k_csize(const LatDesc* descs
     if (!d.csize) return;
     const TileGeom g = tile_geom(d, tile, TY);
     const uint32_t t = *glb(d.counter) + k;
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, wave = wave_id(), lane = tid & 63u;
     const uint32_t NS = nslot(TY), n_nodes = d.ntiles * NS, node0 = tile * NS;
     const gptr<const uint16_t> lab = glb(d.tlab);
     bool bad = false;
     if (tid < 3) sums[tid] = 0;
-    for (uint32_t li = tid; li < TY * TX; li += NT) {
-        const uint32_t r = li / TX, c = li % TX;
-        E[li] = (r < g.h && c < g.w) ? lab[(size_t)(g.y0 + r) * d.L + g.x0 + c] : (ROOT16 | NOSLOT);
-        C[li] = 0;
+    for (uint32_t r = wave; r < g.h; r += NW) {
+        if (lane < g.w) E[r * TX + lane] = lab[(size_t)(g.y0 + r) * d.L + g.x0 + lane];
+        C[r * TX + lane] = 0;
     }
     __syncthreads();
-    for (uint32_t li = tid; li < TY * TX; li += NT) {
-        if (li / TX >= g.h || li % TX >= g.w) continue;
-        uint32_t cur = li, x = E[cur];
-        while (!(x & ROOT16) && x < cur) {
-            cur = x;
-            x = E[cur];
+    const bool vx = lane < g.w;
+    for (uint32_t r = wave; r < g.h; r += NW) {
+        uint32_t cur = INVALID;
+        if (vx) {
+            cur = r * TX + lane;
+            uint32_t x = E[cur];
+            while (!(x & ROOT16) && x < cur) {
+                cur = x;
+                x = E[cur];
+            }
+            bad |= !(x & ROOT16);
         }
-        if (!(x & ROOT16)) {
-            bad = true;
-            continue;
-        }
-        atomicAdd(&C[cur], 1u);
+        const uint32_t left = (uint32_t)__shfl_up((int)cur, 1);
+        const uint64_t heads = ballot(lane == 0 || cur != left);
+        const uint64_t right = lane == 63 ? 0ull : heads >> (lane + 1);
+        const uint32_t len = right ? (uint32_t)__builtin_ctzll(right) + 1u : 64u - lane;
+        if (vx && lane_in(heads)) atomicAdd(&C[cur], min(len, g.w - lane));
     }
     __syncthreads();
-    for (uint32_t li = tid; li < TY * TX; li += NT) {
-        const uint32_t x = E[li], c = C[li];
+    uint64_t s2 = 0, s4 = 0;
+    for (uint32_t r = wave; r < g.h; r += NW) {
+        const uint32_t li = r * TX + lane;
+        const uint32_t x = vx ? E[li] : 0u, c = C[li];
         if (!(x & ROOT16) || !c) continue;
         const uint32_t slot = x & 0x7FFFu;
         if (slot == NOSLOT) {
-            cs_add(sums, c);
+            const uint64_t c2 = (uint64_t)c * c;
+            s2 += c2;
+            s4 += c2 * c2;
         } else {
             const uint64_t rw = n_root(glb(d.nodes), n_nodes, node0 + slot, bad);
             if (!bad)
                 __hip_atomic_fetch_add((gptr<unsigned long long>)(glb(d.csize) + node_of(rw)), (unsigned long long)c,
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        s2 += (uint64_t)__shfl_xor((unsigned long long)s2, o);
+        s4 += (uint64_t)__shfl_xor((unsigned long long)s4, o);
+    }
+    if (lane == 0 && s2) {
+        __hip_atomic_fetch_add(&sums[0], (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(&sums[1], (unsigned long long)s4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
     cs_flush(d, t, sums, tid);
@@ -1463,10 +1486,30 @@ hipError_t launch_merge(const Work& w, uint32_t bump)
     return hipGetLastError();
 }
 
+template <int TY>
+hipError_t start_csize(const Work& w, uint32_t k)
+{
+    auto go = [&](auto nw) {
+        constexpr uint32_t NW = decltype(nw)::value;
+        hipLaunchKernelGGL((k_csize<TY, NW>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k);
+    };
+    // sixteen waves a tile where there is at most one tile per CU
+    if (w.nitems <= CUS) go(std::integral_constant<uint32_t, 16>{});
+    else go(std::integral_constant<uint32_t, waves_of<TY>()>{});
+    return hipGetLastError();
+}
+
 hipError_t launch_cluster_sums(const Work& w, uint32_t k)
 {
     if (w.nitems == 0) return hipSuccess;
-    SWMI_TY_DISPATCH(w.ty, k_csize, w.nitems, w.descs, w.map, k);
+    hipError_t e = hipErrorInvalidValue;
+    switch (w.ty) {
+    case 32: e = start_csize<32>(w, k); break;
+    case 64: e = start_csize<64>(w, k); break;
+    case 128: e = start_csize<128>(w, k); break;
+    default: break;
+    }
+    if (e != hipSuccess) return e;
     SWMI_TY_DISPATCH(w.ty, k_croot, w.nitems, w.descs, w.map, k);
     return hipGetLastError();
 }

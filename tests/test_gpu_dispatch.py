@@ -97,3 +97,24 @@ def test_whole_lattice_extreme_couplings(L, K):
     chains and the fullest queues, from a cold start too)."""
     check(L, 2, K=K, calls=(2, 3), tile_rows=binding.SW_TILE_WHOLE)
     check(L, 2, K=K, calls=(2,), tile_rows=binding.SW_TILE_WHOLE, random_start=False)
+
+
+@pytest.mark.parametrize("L,reps,tile_rows", [(2, 1, 64), (63, 2, 64), (65, 1, 32), (200, 1, 128), (512, 4, 64),
+                                              (513, 4, 64)])
+def test_cluster_sums_of_few_and_many_tiles(L, reps, tile_rows):
+    """Sums of |C|^2 and |C|^4 with sixteen waves a tile (up to 256 tiles) and
+    with four (324), ragged tiles, runs that end at a tile's edge, K = inf (one
+    cluster over all tiles: the largest sizes) next to K_c."""
+    Ks = [float("inf"), wl.critical_coupling(2), 0.0, 0.8]
+    rep = [dict(L=L, q=2, K=Ks[i], seed=3 + i, random_start=i != 0, cluster_sums=True) for i in range(reps)]
+    print(f"case cluster sums L={L} reps={reps} ty={tile_rows}", flush=True)
+    b = binding.Batch(rep, obs_capacity=8, tile_rows=tile_rows)
+    b.sweep_all(3)
+    for i, r in enumerate(rep):
+        ref = oracle.OracleLattice(L, 2, r["K"], r["seed"], random_start=r["random_start"])
+        want = []
+        for _ in range(3):
+            sizes = np.unique(ref.sweep()["labels"], return_counts=True)[1]
+            want.append([sum(int(c) ** 2 for c in sizes), sum(int(c) ** 4 for c in sizes)])
+        assert b.cluster_sums(i, 0, 3).tolist() == want, f"replica {i}"
+    b.close()
