@@ -180,45 +180,149 @@ __device__ void n_hook2(gptr<uint64_t> nodes, uint32_t n, uint64_t (&a)[2], uint
 // Spins of a tile and its halo in LDS: rows 0..h (row h is the row below the
 // tile, periodic), columns 0..w-1 plus column w = the column right of the tile
 // (periodic).  Row stride SPW bytes.
+//
+// A thread loads four columns of a few rows at once (a dword at any address:
+// rows of a lattice whose size is no multiple of four start anywhere); the last
+// word of a width that is no multiple of four is loaded from the row's last
+// four columns and shifted.  Every load is issued before the first store: the
+// wave waits for memory once, where a load and its store row by row waited once
+// a row (23 % of a wave's life at 64-row tiles, L = 16384).
 template <int TY, uint32_t NT>
 __device__ __forceinline__ void stage_spins(uint8_t* sp, const LatDesc& d, const TileGeom& g, uint32_t tid)
 {
+    typedef uint32_t __attribute__((aligned(1))) any_u32;
     const uint32_t L = d.L, w = g.w, h = g.h;
     const uint32_t yb = (g.y0 + h == L) ? 0u : g.y0 + h;          // row below the tile
     const uint32_t xh = (g.x0 + w == L) ? 0u : g.x0 + w;          // column right of the tile
-    if ((L & 3u) == 0) {
-        // rows start 4-byte aligned (w is then a multiple of 4): NT / 16 rows per pass
-        const uint32_t c = tid & 15u, dw = w >> 2;
+    const gptr<const uint8_t> s = glb(d.s);
+    const gptr<const uint8_t> tile0 = s + (size_t)g.y0 * L + g.x0;
+    constexpr uint32_t HB = (TY + NT) / NT;                       // halo bytes per thread
+    uint8_t hb[HB];
 #pragma unroll
-        for (uint32_t rr = 0; rr <= (uint32_t)TY; rr += NT / 16) {
-            const uint32_t r = rr + (tid >> 4);
-            if (r <= h && c < dw) {
-                const uint32_t y = (r < h) ? g.y0 + r : yb;
-                const uint32_t v = *reinterpret_cast<gptr<const uint32_t>>(glb(d.s) + (size_t)y * L + g.x0 + 4 * c);
-                *reinterpret_cast<uint32_t*>(sp + r * SPW + 4 * c) = v;
+    for (uint32_t k = 0; k < HB; ++k) {
+        const uint32_t r = min(tid + k * NT, h);
+        hb[k] = s[(size_t)(r < h ? g.y0 + r : yb) * L + xh];
+    }
+    if (w >= 4) {
+        constexpr uint32_t PER = TY * 16 / NT;                    // words per thread
+        const uint32_t c = tid & 15u, r0 = tid >> 4;
+        const uint32_t col = min(4 * c, w - 4), sh = 8u * (4 * c - col);   // (sh >= 32: no such word)
+        uint32_t v[PER], vb;
+#pragma unroll
+        for (uint32_t k = 0; k < PER; ++k)
+            v[k] = *reinterpret_cast<gptr<const any_u32>>(tile0 + (size_t)min(r0 + k * (NT / 16), h - 1) * L + col);
+        vb = *reinterpret_cast<gptr<const any_u32>>(s + (size_t)yb * L + g.x0 + col);
+        __builtin_amdgcn_sched_barrier(0);
+        if (sh < 32) {
+#pragma unroll
+            for (uint32_t k = 0; k < PER; ++k) {
+                const uint32_t r = r0 + k * (NT / 16);
+                if (r < h) *reinterpret_cast<uint32_t*>(sp + r * SPW + 4 * c) = v[k] >> sh;
             }
+            if (r0 == 0) *reinterpret_cast<uint32_t*>(sp + h * SPW + 4 * c) = vb >> sh;
         }
+        // the halo column's byte may share a word with the last columns: it is
+        // stored after them
+        if (w & 3u) __syncthreads();
     } else {
         const uint32_t c = tid & 63u;
-#pragma unroll 4
-        for (uint32_t rr = 0; rr <= (uint32_t)TY; rr += NT / 64) {
-            const uint32_t r = rr + (tid >> 6);
-            if (r <= h && c < w) {
-                const uint32_t y = (r < h) ? g.y0 + r : yb;
-                sp[r * SPW + c] = glb(d.s)[(size_t)y * L + g.x0 + c];
-            }
-        }
+        for (uint32_t r = tid >> 6; r <= h; r += NT / 64)
+            if (c < w) sp[r * SPW + c] = s[(size_t)(r < h ? g.y0 + r : yb) * L + g.x0 + c];
     }
-    for (uint32_t r = tid; r <= h; r += NT) {
-        const uint32_t y = (r < h) ? g.y0 + r : yb;
-        sp[r * SPW + w] = glb(d.s)[(size_t)y * L + xh];
+#pragma unroll
+    for (uint32_t k = 0; k < HB; ++k) {
+        const uint32_t r = tid + k * NT;
+        if (r <= h) sp[r * SPW + w] = hb[k];
     }
 }
 
-// Sites of one row in each state c >= 1 for q > 16, straight into hist.
-__device__ __forceinline__ void count_states(uint32_t* hist, bool valid, uint32_t s)
+// State counts of the tile's sites from the staged spins, four at a time: for
+// q <= 16 the counts of sites whose state has all the bits of m set, m = 1..15
+// (population counts of the ands of the words' bit planes), into hist[m]; the
+// states' own counts follow from those by inclusion and exclusion
+// (states_of_subsets).  For q = 2 that is one and and one count per word, where
+// counting each site in its lane took four instructions a site.  q > 16: one
+// LDS atomic per site.  At most 16 sites per lane, so two counts fit a word.
+template <int TY, uint32_t NT>
+__device__ __forceinline__ void count_tile_states(const uint8_t* sp, const TileGeom& g, uint32_t q, uint32_t* hist,
+                                                  uint32_t tid)
 {
-    if (valid && s) atomicAdd(&hist[s], 1u);
+    static_assert(TY * TX / NT <= 16, "two counts per word");
+    const uint32_t c = tid & 15u, lane = tid & 63u;
+    const uint32_t nb = g.w > 4 * c ? min(4u, g.w - 4 * c) : 0u;   // columns of word c inside the tile
+    const uint32_t one = nb ? 0x01010101u >> (8u * (4u - nb)) : 0u;
+    auto words = [&](auto f) {
+#pragma unroll
+        for (uint32_t rr = 0; rr < (uint32_t)TY; rr += NT / 16) {
+            const uint32_t r = rr + (tid >> 4);
+            if (r < g.h) f(*reinterpret_cast<const uint32_t*>(sp + r * SPW + 4 * c));
+        }
+    };
+    auto add = [&](uint32_t v, uint32_t m) {   // two counts (m, m + 1) of the wave
+        const uint32_t n = wave_sum(v);
+        if (lane == 0 && n) {
+            atomicAdd(&hist[m], n & 0xFFFFu);
+            if (n >> 16) atomicAdd(&hist[m + 1], n >> 16);
+        }
+    };
+    if (q == 2) {
+        uint32_t n1 = 0;
+        words([&](uint32_t v) { n1 += (uint32_t)__popc(v & one); });
+        add(n1, 1);
+    } else if (q <= 4) {
+        uint32_t n1 = 0, n2 = 0, n3 = 0;
+        words([&](uint32_t v) {
+            const uint32_t b0 = v & one, b1 = (v >> 1) & one;
+            n1 += (uint32_t)__popc(b0);
+            n2 += (uint32_t)__popc(b1);
+            n3 += (uint32_t)__popc(b0 & b1);
+        });
+        add(n1 | (n2 << 16), 1);
+        add(n3, 3);
+    } else if (q <= 16) {
+        uint32_t n[16] = {};
+        words([&](uint32_t v) {
+            uint32_t b[16];
+            b[1] = v & one;
+            b[2] = (v >> 1) & one;
+            b[4] = (v >> 2) & one;
+            b[8] = (v >> 3) & one;
+#pragma unroll
+            for (uint32_t m = 1; m < 16; ++m) {
+                const uint32_t top = m & (0u - m);   // a single bit of m
+                if (m != top) b[m] = b[top] & b[m ^ top];
+                if (m < 8 || q > 8) n[m] += (uint32_t)__popc(b[m]);
+            }
+        });
+        add(n[1] | (n[2] << 16), 1);
+        add(n[3] | (n[4] << 16), 3);
+        add(n[5] | (n[6] << 16), 5);
+        add(n[7] | (n[8] << 16), 7);
+        if (q > 8) {
+            add(n[9] | (n[10] << 16), 9);
+            add(n[11] | (n[12] << 16), 11);
+            add(n[13] | (n[14] << 16), 13);
+            add(n[15], 15);
+        }
+    } else {
+        words([&](uint32_t v) {
+            for (uint32_t j = 0; j < nb; ++j) {
+                const uint32_t st = (v >> (8 * j)) & 0xFFu;
+                if (st) atomicAdd(&hist[st], 1u);
+            }
+        });
+    }
+}
+
+// Sites in state c >= 1 from the counts of count_tile_states.
+__device__ __forceinline__ uint32_t states_of_subsets(const uint32_t* hist, uint32_t q, uint32_t c)
+{
+    if (q == 2 || q > 16) return hist[c];
+    const uint32_t top = q <= 4 ? 4u : q <= 8 ? 8u : 16u;
+    uint32_t n = 0;
+    for (uint32_t m = c; m < top; ++m)
+        if ((m & c) == c) n += (__popc(m ^ c) & 1) ? 0u - hist[m] : hist[m];
+    return n;
 }
 
 // Add a workgroup's measurement into a ring record (NCOPY partial copies).
@@ -237,7 +341,6 @@ constexpr uint32_t qcap_of() { return TY == 128 ? 224u : 256u; }
 
 struct UnionQueue {
     uint32_t* q;       // the wave's slots in LDS
-    uint32_t* trash;   // an LDS word for lanes with nothing to store
     uint32_t n;        // wave-uniform fill
 };
 
@@ -252,12 +355,11 @@ __device__ __forceinline__ void drain(UnionQueue& uq, uint16_t* P, uint32_t lane
 }
 
 // Queue the unions (a, b) of the lanes in `mask` where a != b (at most 64; the
-// caller keeps at least 64 slots free).  The other lanes store to a scratch
-// word instead of branching around the store (no branch on the scalar unit).
+// caller keeps at least 64 slots free).
 __device__ __forceinline__ void enqueue(UnionQueue& uq, uint64_t mask, uint32_t a, uint32_t b)
 {
     const uint64_t m = ballot(a != b) & mask;
-    lds_st(lane_in(m) ? &uq.q[uq.n + lanes_below(m)] : uq.trash, a | (b << 16));
+    if (lane_in(m)) lds_st(&uq.q[uq.n + lanes_below(m)], a | (b << 16));
     uq.n = __builtin_amdgcn_readfirstlane(uq.n + popc64(m));
 }
 
@@ -265,27 +367,27 @@ __device__ __forceinline__ void enqueue(UnionQueue& uq, uint64_t mask, uint32_t 
 // inside the tile; V: +y bonds from the row above (0 on a strip's first row);
 // lp: this lane's label of the row above.  Every run of +x bonds takes one
 // label: the label above one of its +y bonds, or, with none, its first site
-// (a new root).  The runs are numbered by their first sites, and one LDS slot
+// (a new root).  The runs are numbered from the left, and one LDS slot
 // per run carries the choice to all its sites.  Any further +y bond into the
 // run from a differently labelled site queues a union.  Every site's own
 // union-find entry points at its label (itself for a new root), so the forest
 // spans all sites and no separate array of provisional labels is kept.
-__device__ __forceinline__ uint32_t row_labels(uint16_t* P, uint32_t* rl, UnionQueue& uq, uint32_t r, uint32_t x,
+// Vector instructions bound the kernel (scalar ones issue beside them), so what
+// can be a mask is one: stores are masked by the lanes that have something to
+// store rather than sent to a scratch slot.
+__device__ __forceinline__ uint32_t row_labels(uint16_t* P, uint32_t* rl, UnionQueue& uq, uint32_t fresh,
                                                uint64_t validm, uint64_t hx, uint64_t V, uint64_t hprev, uint32_t lp)
 {
     const uint64_t C = hx << 1;                 // bit x: bond (x-1) -> x
     const uint64_t S = ~C & validm;             // first sites of runs (site 0 always is one)
-    // run index of x = run starts in 0..x, less one: counted from an initial
-    // value of (x starts a run) - 1, with no scalar shift of S
-    const uint32_t ri = __builtin_amdgcn_mbcnt_hi((uint32_t)(S >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)S, (uint32_t)lane_in(S) - 1u));
-    const uint32_t fresh = r * TX + x;
+    // run index of x: the sites left of x whose +x bond is missing
+    uint32_t* const slot = &rl[lanes_below(~hx)];
     // lanes talk through the slots, so these accesses must not be folded away;
     // a run's first site offers itself and every +y bond offers the label
     // above, in one store: any offer may win (unions below cover the rest)
-    const bool vb = lane_in(V);
-    lds_st(lane_in(S | V) ? &rl[ri] : &rl[64], vb ? lp : fresh);
-    const uint32_t lab = lds_ld(&rl[ri]);
+    const uint32_t offer = lane_in(V) ? lp : fresh;
+    if (lane_in(S | V)) lds_st(slot, offer);
+    const uint32_t lab = lds_ld(slot);
     lds_st(&P[fresh], lab);   // columns outside the tile write entries no one reads
     // bonds x-1 and x from the same run above into the same run here add nothing
     const uint64_t R = (V & C) & ((V & hprev) << 1);
@@ -341,6 +443,12 @@ extern "C" int sw_phase_clocks(unsigned long long* host, int clear)
 // (2m, 2m+1) of one row; lane 2m draws for row r and lane 2m+1 for row r+1,
 // and the two lanes swap the halves the other one needs.
 //
+// What bounds it: vector issue (1580 instructions a wave of 16 rows at eight
+// waves a SIMD; 8 x 88 of them the row loop, of which Philox 37) and, where a
+// wave waits, latency (a quarter more time at six waves a SIMD than at eight).
+// L = 16384, q = 2 at K_c: 0.66 ms (0.74 with 1870 vector instructions, loads
+// staged row by row and paths split at every step of a find).
+//
 // flags bit 0: also measure the configuration the bonds are drawn on (the
 // result of the previous sweep, t - 1).
 // PRESET: the bonds are already in the bond plane (drawn by the XY model's own
@@ -352,16 +460,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     constexpr uint32_t NT = 64 * NW;
     constexpr uint32_t RPW = TY / NW;  // rows per wave (even)
     static_assert(RPW % 2 == 0, "rows are labelled two at a time");
-    static_assert(RPW < 32, "per-lane measurement counters hold at most 31 rows");
     constexpr uint32_t QCAP = qcap_of<TY>();
     __shared__ __align__(16) uint16_t P[TY * TX];   // union-find over the tile's sites
     __shared__ __align__(16) uint8_t sp[(TY + 1) * SPW];
     __shared__ uint64_t rb[TY][2];     // per row: +x bond word, +y bond word
     // per wave: the label of every run of a row; once a wave has left its
     // strip, its row holds the labels of the strip's last row (the seam)
-    __shared__ uint32_t RL[NW][65];    // [64]: scratch word of lanes with nothing to store
-    __shared__ uint32_t UQT[NW];       // scratch words of the union queues
-    uint32_t(*const seam)[65] = RL;
+    __shared__ uint32_t RL[NW][64];
+    uint32_t(*const seam)[64] = RL;
     __shared__ uint32_t UQ[NW][QCAP];  // per wave: pending unions
     __shared__ uint32_t hist[256];
     __shared__ uint32_t tot[3];        // unequal pairs, active bonds, edge-forest nodes
@@ -390,6 +496,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     }
     __syncthreads();
     SW_PHASE(pc, 0);   // staging
+    if (meas_prev) count_tile_states<TY, NT>(sp, g, d.q, hist, tid);
 
     const uint32_t x = lane;
     const bool vx = x < w;
@@ -398,50 +505,107 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     const uint32_t r0 = wave * RPW, r1 = min(h, r0 + RPW);
     const uint64_t bondm = d.thr_nz ? validm : 0ull;   // K = 0: no bond at all
     const bool even_L = (L & 1u) == 0;
-    const bool q2 = d.q == 2;
     uint32_t* rl = RL[wave];
-    UnionQueue uq{UQ[wave], &UQT[wave], 0u};
-    // measurement: equal-spin pairs and q = 2 spins counted per lane (column;
-    // vector adds keep the work off the scalar unit), active bonds counted from
-    // the bond words
-    uint32_t n_eq = 0, ones = 0;
-    // q <= 16: each lane counts its sites in states 1..q-1 in the bytes of two
-    // 64-bit words (at most 16 rows per lane, so no byte overflows)
-    const bool q8 = !q2 && d.q <= 8, q16 = !q2 && d.q <= 16;
-    uint64_t packed[2] = {0ull, 0ull};
-    const uint32_t vbyte = vx ? 0xFFu : 0u;
+    UnionQueue uq{UQ[wave], 0u};
+    uint32_t n_eq = 0;   // equal-spin pairs of the strip (wave-uniform)
     uint32_t lp = 0;
     const PhiloxKeys ks = philox_keys_v(d.key0, d.key1);
     bool bad = false;   // this lane met a corrupted forest
     uint64_t hprev = 0, vprev = 0;
 
-    // The row loop, compiled three times: the q = 9..16 counters (two words per
-    // lane) stay out of the common instantiations, whose code they would
-    // otherwise perturb; FAST is a full strip of a full-width tile of a lattice
-    // of even L, q <= 8 and K > 0: no lane or row masks, always two rows, one
-    // Philox path, the measurement counted without branches (used only when
-    // measuring) and the bond words gathered into lanes, one row per lane, and
-    // stored once per strip.  That keeps the scalar unit's share of the loop
-    // small (it is the busier of the two issue units here).
-    auto strip_rows = [&](auto wide, auto fast) {
-        constexpr bool WIDE = decltype(wide)::value;
-        constexpr bool FAST = decltype(fast)::value;
-        const uint64_t vm = FAST ? ~0ull : validm, bm = FAST ? ~0ull : bondm;
-        uint32_t bxl = 0, bxh = 0, byl = 0, byh = 0;   // FAST: lane k holds row r0 + k's bond words
+    // Full strips of full-width tiles (K > 0), the common case: no lane or row
+    // masks, always two rows, one Philox call per lane and pass, the bond words
+    // gathered into lanes (one row per lane) and stored once per strip.
+    // ODD: L is odd.  Row r then starts at an even site index (y0 + r and x0 are
+    // even) and row r+1 at an odd one, so the pairs of row r are the columns
+    // (2m, 2m+1) and those of row r+1 the columns (2m+1, 2m+2): an even lane
+    // draws for row r, an odd lane for row r+1, and either way the pair's second
+    // half belongs to the lane on the right.  Column 0 of row r+1 is the second
+    // half of a pair that starts left of the tile; lane k draws it for pass k
+    // before the loop.  (Two calls per lane and pass, as for ragged tiles below,
+    // cost an odd lattice a third: 32 uneven lattices, half of them odd, 237 us
+    // a labelling against 171 at the even lattices' rate.)
+    auto full_rows = [&](auto odd_tag) {
+        constexpr bool ODD = decltype(odd_tag)::value;
+        uint32_t words[4] = {0u, 0u, 0u, 0u};   // lane k holds row r0 + k's bond words
+        const bool odd = x & 1u;
+        // site indices in 32 bits: exact for every row of the lattice (N <= 2^32)
+        const uint32_t base = (y0 + r0) * L + x0;
+        const uint32_t pair = ODD ? ((odd ? base + L : base) >> 1) + ((x + 1u) >> 1)
+                                  : ((odd ? base + L : base) + (x & ~1u)) >> 1;
+        uint64_t m0 = PHILOX_M0 * pair;
+        const uint64_t m0_step = PHILOX_M0 * L;   // two rows on, pairs are L further
+        uint32_t ez = 0, ew = 0;
+        if constexpr (ODD) {
+            const u32x4 e = philox4x32_10((base + (2u * min(lane, RPW / 2 - 1u) + 1u) * L) >> 1, 0u, t, 0u, ks);
+            ez = e.z;
+            ew = e.w;
+        }
+#pragma unroll 1
+        for (uint32_t k = 0; k < RPW; k += 2) {
+            const uint32_t r = r0 + k;
+            if (uq.n > QCAP - 128) drain(uq, P, lane, bad);
+            const uint8_t* row = sp + r * SPW;
+            const uint32_t s0 = row[x], s0r = row[x + 1];
+            const uint32_t s1 = row[SPW + x], s1r = row[SPW + x + 1];
+            const uint32_t s2 = row[2 * SPW + x];
+            const u32x4 q4 = philox4x32_10_from(m0, t, ks);
+            m0 += m0_step;
+            uint32_t wx0, wy0, wx1, wy1;
+            if constexpr (ODD) {
+                // the left lane's second half; lane 0 the one drawn ahead
+                const uint32_t lz = (uint32_t)__builtin_amdgcn_update_dpp(__builtin_amdgcn_readlane((int)ez, (int)(k / 2)),
+                                                                          (int)q4.z, 0x138, 0xF, 0xF, false);   // wave_shr:1
+                const uint32_t lw = (uint32_t)__builtin_amdgcn_update_dpp(__builtin_amdgcn_readlane((int)ew, (int)(k / 2)),
+                                                                          (int)q4.w, 0x138, 0xF, 0xF, false);
+                wx0 = odd ? lz : q4.x;
+                wy0 = odd ? lw : q4.y;
+                wx1 = odd ? q4.x : lz;
+                wy1 = odd ? q4.y : lw;
+            } else {
+                const uint32_t recv0 = swap_pair(odd ? q4.x : q4.z);
+                const uint32_t recv1 = swap_pair(odd ? q4.y : q4.w);
+                wx0 = odd ? recv0 : q4.x;
+                wy0 = odd ? recv1 : q4.y;
+                wx1 = odd ? q4.z : recv0;
+                wy1 = odd ? q4.w : recv1;
+            }
+            // equal-spin masks and draw masks as wave ballots; a bond needs both
+            const uint64_t EX0 = ballot(s0 == s0r), EY0 = ballot(s0 == s1);
+            const uint64_t EX1 = ballot(s1 == s1r), EY1 = ballot(s1 == s2);
+            const uint64_t BX0 = EX0 & ballot(wx0 <= d.thr_m1), BY0 = EY0 & ballot(wy0 <= d.thr_m1);
+            const uint64_t BX1 = EX1 & ballot(wx1 <= d.thr_m1), BY1 = EY1 & ballot(wy1 <= d.thr_m1);
+            n_eq += popc64(EX0) + popc64(EY0) + popc64(EX1) + popc64(EY1);
+            write_rows(words, k, BX0, BY0, BX1, BY1);
+
+            const uint64_t hx0 = BX0 & ~cross, hx1 = BX1 & ~cross;
+            const uint32_t fresh = r * TX + x;
+            lp = row_labels(P, rl, uq, fresh, ~0ull, hx0, vprev, hprev, lp);
+            lp = row_labels(P, rl, uq, fresh + TX, ~0ull, hx1, BY0, hx0, lp);
+            hprev = hx1;
+            vprev = BY1;
+        }
+        if (lane < RPW) {
+            rb[r0 + lane][0] = ((uint64_t)words[1] << 32) | words[0];
+            rb[r0 + lane][1] = ((uint64_t)words[3] << 32) | words[2];
+        }
+    };
+    // Ragged tiles and K = 0: masks for the columns and rows outside, one Philox
+    // call per row and lane where L is odd.
+    auto ragged_rows = [&]() {
 #pragma unroll 1
         for (uint32_t r = r0; r < r1; r += 2) {
-            const bool two = FAST || r + 1 < r1;
+            const bool two = r + 1 < r1;
             if (uq.n > QCAP - 128) drain(uq, P, lane, bad);
             const uint8_t* row = sp + r * SPW;
             const uint32_t s0 = row[x], s0r = row[x + 1];
             const uint32_t s1 = row[SPW + x], s1r = row[SPW + x + 1];
             const uint32_t s2 = two ? row[2 * SPW + x] : 0u;
 
-            // Site indices in 32 bits: exact for every row of the lattice (N <= 2^32);
-            // a draw for row r+1 past the last row wraps but is never used.
+            // a draw for row r+1 past the last row wraps but is never used
             const uint32_t base0 = (y0 + r) * L + x0;
             uint32_t wx0, wy0, wx1, wy1;
-            if (FAST || even_L) {
+            if (even_L) {
                 const bool odd = x & 1u;
                 const uint32_t pair = ((odd ? base0 + L : base0) + (x & ~1u)) >> 1;
                 const u32x4 q4 = philox4x32_10(pair, 0u, t, 0u, ks);
@@ -460,26 +624,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
                 wx1 = (gb & 1u) ? qb.z : qb.x;
                 wy1 = (gb & 1u) ? qb.w : qb.y;
             }
-            // equal-spin masks and draw masks as wave ballots; a bond needs both
-            const uint64_t EX0 = ballot(s0 == s0r) & vm, EY0 = ballot(s0 == s1) & vm;
-            const uint64_t BX0 = EX0 & ballot(wx0 <= d.thr_m1) & bm;
-            const uint64_t BY0 = EY0 & ballot(wy0 <= d.thr_m1) & bm;
+            const uint64_t EX0 = ballot(s0 == s0r) & validm, EY0 = ballot(s0 == s1) & validm;
+            const uint64_t BX0 = EX0 & ballot(wx0 <= d.thr_m1) & bondm;
+            const uint64_t BY0 = EY0 & ballot(wy0 <= d.thr_m1) & bondm;
             uint64_t EX1 = 0, EY1 = 0, BX1 = 0, BY1 = 0;
             if (two) {
-                EX1 = ballot(s1 == s1r) & vm;
-                EY1 = ballot(s1 == s2) & vm;
-                BX1 = EX1 & ballot(wx1 <= d.thr_m1) & bm;
-                BY1 = EY1 & ballot(wy1 <= d.thr_m1) & bm;
+                EX1 = ballot(s1 == s1r) & validm;
+                EY1 = ballot(s1 == s2) & validm;
+                BX1 = EX1 & ballot(wx1 <= d.thr_m1) & bondm;
+                BY1 = EY1 & ballot(wy1 <= d.thr_m1) & bondm;
             }
-            if constexpr (FAST) {
-                // vector selects only (no scalar work): lane k takes row r0 + k
-                const uint32_t k = r - r0;
-                const bool at0 = lane == k, at1 = lane == k + 1;
-                bxl = at0 ? (uint32_t)BX0 : at1 ? (uint32_t)BX1 : bxl;
-                bxh = at0 ? (uint32_t)(BX0 >> 32) : at1 ? (uint32_t)(BX1 >> 32) : bxh;
-                byl = at0 ? (uint32_t)BY0 : at1 ? (uint32_t)BY1 : byl;
-                byh = at0 ? (uint32_t)(BY0 >> 32) : at1 ? (uint32_t)(BY1 >> 32) : byh;
-            } else if (lane == 0) {
+            n_eq += popc64(EX0) + popc64(EY0) + popc64(EX1) + popc64(EY1);
+            if (lane == 0) {
                 rb[r][0] = BX0;
                 rb[r][1] = BY0;
                 if (two) {
@@ -489,45 +645,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             }
 
             const uint64_t hx0 = BX0 & ~cross;
-            const uint32_t lab0 = row_labels(P, rl, uq, r, x, validm, hx0, vprev, hprev, lp);
-            lp = lab0;
+            const uint32_t fresh = r * TX + x;
+            lp = row_labels(P, rl, uq, fresh, validm, hx0, vprev, hprev, lp);
             hprev = hx0;
             vprev = BY0;
             if (two) {
                 const uint64_t hx1 = BX1 & ~cross;
-                const uint32_t lab1 = row_labels(P, rl, uq, r + 1, x, validm, hx1, vprev, hprev, lp);
-                lp = lab1;
+                lp = row_labels(P, rl, uq, fresh + TX, validm, hx1, vprev, hprev, lp);
                 hprev = hx1;
                 vprev = BY1;
-            }
-
-            if (FAST) {
-                n_eq += (uint32_t)lane_in(EX0) + (uint32_t)lane_in(EY0) + (uint32_t)lane_in(EX1) +
-                        (uint32_t)lane_in(EY1);
-                count_state_byte(packed, true, s0);
-                count_state_byte(packed, true, s1);
-            } else if (meas_prev) {
-                // this lane's equal pairs (EX1, EY1 are 0 without row r+1)
-                n_eq += (uint32_t)lane_in(EX0) + (uint32_t)lane_in(EY0) + (uint32_t)lane_in(EX1) +
-                        (uint32_t)lane_in(EY1);
-                if (q2) ones += (s0 & vbyte) + (s1 & (two ? vbyte : 0u));
-                else if (q8) {
-                    // (lanes outside the tile add nothing; their bytes may be stale)
-                    count_state_byte(packed, vx, s0);
-                    count_state_byte(packed, vx && two, s1);
-                } else if (WIDE) {
-                    count_state_bytes(packed, vx, s0 & 15u);
-                    count_state_bytes(packed, vx && two, s1 & 15u);
-                } else {
-                    count_states(hist, vx, s0);
-                    if (two) count_states(hist, vx, s1);
-                }
-            }
-        }
-        if constexpr (FAST) {
-            if (lane < RPW) {
-                rb[r0 + lane][0] = ((uint64_t)bxh << 32) | bxl;
-                rb[r0 + lane][1] = ((uint64_t)byh << 32) | byl;
             }
         }
     };
@@ -536,28 +662,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         for (uint32_t r = r0; r < r1; ++r) {
             if (uq.n > QCAP - 64) drain(uq, P, lane, bad);
             const uint64_t hx = rb[r][0] & ~cross;
-            lp = row_labels(P, rl, uq, r, x, validm, hx, vprev, hprev, lp);
+            lp = row_labels(P, rl, uq, r * TX + x, validm, hx, vprev, hprev, lp);
             hprev = hx;
             vprev = rb[r][1];
         }
     };
-    const bool fast = w == TX && r1 - r0 == RPW && even_L && d.thr_nz && d.q <= 8;
+    const bool full = w == TX && r1 - r0 == RPW && d.thr_nz;
     if constexpr (PRESET) preset_rows();
-    else if (q16 && !q8) strip_rows(std::true_type{}, std::false_type{});
-    else if (fast) strip_rows(std::false_type{}, std::true_type{});
-    else strip_rows(std::false_type{}, std::false_type{});
-    SW_PHASE(pc, 1);   // rows: draws, ballots, row labels, queue drains, counting
+    else if (full && even_L) full_rows(std::false_type{});
+    else if (full) full_rows(std::true_type{});
+    else ragged_rows();
+    SW_PHASE(pc, 1);   // rows: draws, ballots, row labels, queue drains, equal pairs
     seam[wave][lane] = lp;
-    if (meas_prev) {
-        // every site of the strip owns two bonds
-        const uint32_t eq = wave_sum(n_eq);
-        if (lane == 0 && r0 < r1) atomicAdd(&tot[0], 2u * w * (r1 - r0) - eq);
-        if (q2 && !fast) {
-            const uint32_t n1 = wave_sum(ones);
-            if (lane == 0 && n1) atomicAdd(&hist[1], n1);
-        }
-        if (q16 || fast) flush_state_bytes(packed, hist, d.q, lane);   // (fast: q <= 8, one word)
-    }
+    // every site of the strip owns two bonds
+    if (meas_prev && lane == 0 && r0 < r1) atomicAdd(&tot[0], 2u * w * (r1 - r0) - n_eq);
     SW_PHASE(pc, 2);   // measurement sums of the strip
     __syncthreads();
     SW_PHASE(pc, 3);   // barrier
@@ -617,8 +735,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     // The first lane to reach a root claims it as a node of the tile's edge
     // forest: it takes the next slot (in no particular order: a node's word
     // carries its key), writes the node's word (a root of its own, keyed by its
-    // site index) and tags the root's LDS entry ROOT16 | slot, which the labels
-    // and the edge record copy.  Walks stop at tagged entries (all walks end
+    // site index) and makes the root's LDS entry NODE16 + slot, which the labels
+    // and the edge record carry on.  Walks stop at tagged entries (all walks end
     // before the first claim).
     // a site index fits 32 bits (N <= 2^32) and y, L fit 24 bits
     auto global_index = [&](uint32_t la) { return __umul24(y0 + la / TX, L) + x0 + la % TX; };
@@ -637,7 +755,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     // first and wins; an entry tagged already keeps its value (a slot stored
     // by another winner is never overwritten).  The four claims of a lane go
     // out together, then the wave's winners take consecutive slots with one
-    // LDS atomic and tag their roots ROOT16 | slot.
+    // LDS atomic and make their roots' entries NODE16 + slot.
     auto claim = [&](bool want, uint32_t r) {
         if (!want) return false;
         const uint32_t sh = (r & 1u) * 16u;
@@ -662,7 +780,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         auto assign = [&](bool won, uint32_t r, uint32_t slot) {
             if (!won) return;
             glb(d.nodes)[node0 + slot] = ((uint64_t)global_index(r) << 32) | (node0 + slot);
-            lds_st(&P[r], ROOT16 | slot);
+            lds_st(&P[r], NODE16 + slot);
         };
         assign(wR, rootR, base + lanes_below(mR));
         assign(wL, rootL, base + nR + lanes_below(mL));
@@ -676,25 +794,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     // Tile labels out (16 bits), per site: the tile-local index of its
     // union-find grandparent (a smaller site of its tile-local cluster; the
     // flip follows these pointers inside the tile), or, for a tile-local root,
-    // ROOT16 | its slot (NOSLOT if its cluster touches no tile edge).  A grandparent that is a
-    // node is not copied (its entry carries a slot, not an index): the parent
-    // is.  (The grandparent read is masked into the tile: a tagged entry's
-    // slot, or an unused column's entry, reads some entry that is not used.)
+    // ROOT16 or NODE16 + its slot.  A grandparent that is a node is not
+    // copied (its entry carries a slot, not an index): the parent is.  Tagged
+    // entries are larger than every index, so two minima do it: the entry of
+    // min(entry, own index) (its own entry again for a root), then the smaller
+    // of the two entries; a root inside the tile ends at its own index.
     // Entries of columns outside the tile are never stored (full-width tiles,
     // the common case, need no mask at all).
-    auto label_of = [&](uint32_t li, uint32_t p, uint32_t gp) {
-        return (p & ROOT16) ? p : (p == li) ? (ROOT16 | NOSLOT) : (gp & ROOT16) ? p : gp;
-    };
-    auto labels_out = [&](auto full) {
-        constexpr bool FULL = decltype(full)::value;
-        const bool vs = FULL || vx;
-        for (uint32_t r = r0; r < r1; ++r) {
-            const uint32_t li = r * TX + x, p = P[li];
-            const uint32_t out = label_of(li, p, P[p & (TY * TX - 1u)]);
-            const gptr<uint16_t> lrow = glb(d.tlab) + (size_t)(y0 + r) * L + x0;
-            if (vs) lrow[x] = (uint16_t)out;
-        }
-    };
     if (w == TX && r1 - r0 == RPW) {
         // a full strip: all parent reads first, then all grandparent reads, so
         // the LDS round trips overlap; each row is stored from its own
@@ -703,24 +809,29 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
 #pragma unroll
         for (uint32_t k = 0; k < RPW; ++k) p[k] = P[(r0 + k) * TX + x];   // (16-bit entries)
 #pragma unroll
-        for (uint32_t k = 0; k < RPW; ++k) gp[k] = P[p[k] & (TY * TX - 1u)];
+        for (uint32_t k = 0; k < RPW; ++k) gp[k] = P[min(p[k], (r0 + k) * TX + x)];
         gptr<uint16_t> out = glb(d.tlab) + (size_t)(y0 + r0) * L + x0 + x;   // this lane's site, row by row
 #pragma unroll
-        for (uint32_t k = 0; k < RPW; ++k, out += L) *out = (uint16_t)label_of((r0 + k) * TX + x, p[k], gp[k]);
-    } else if (w == TX) {
-        labels_out(std::true_type{});
-    } else {
-        labels_out(std::false_type{});
+        for (uint32_t k = 0; k < RPW; ++k, out += L) {
+            const uint32_t li = (r0 + k) * TX + x;
+            *out = (uint16_t)(p[k] == li ? ROOT16 : min(p[k], gp[k]));
+        }
+    } else if (vx) {
+        for (uint32_t r = r0; r < r1; ++r) {
+            const uint32_t li = r * TX + x, p = P[li];
+            glb(d.tlab)[(size_t)(y0 + r) * L + x0 + x] =
+                (uint16_t)(p == li ? ROOT16 : min(p, (uint32_t)P[min(p, li)]));
+        }
     }
     SW_PHASE(pc, 7);   // tile labels out
     // The edge record's slots, for the merge.
     const gptr<uint16_t> slots = (gptr<uint16_t>)(rec + 8);
     if (side) {
-        slots[rs] = P[rootR] & ~ROOT16;
-        slots[TY + rs] = P[rootL] & ~ROOT16;
+        slots[rs] = P[rootR] - NODE16;
+        slots[TY + rs] = P[rootL] - NODE16;
     }
-    if (top) slots[2 * TY + TX + x] = P[rootT] & ~ROOT16;
-    if (bottom) slots[2 * TY + x] = P[rootB] & ~ROOT16;
+    if (top) slots[2 * TY + TX + x] = P[rootT] - NODE16;
+    if (bottom) slots[2 * TY + x] = P[rootB] - NODE16;
     if (bad) flag_error(d.err);
 
     // the workgroup's sums into the ring, by wave 0 alone (the slot's modulo is
@@ -733,8 +844,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         if (meas_prev) {
             int64_t* const rp = d.ring + ((size_t)prev * NCOPY + copy) * ring_stride(d.q);
             if (lane == 0) atomic_add_i64(&rp[0], tot[0]);
-            for (uint32_t c = lane; c < d.q; c += 64)
-                if (c >= 1 && hist[c]) atomic_add_i64(&rp[1 + c], hist[c]);
+            for (uint32_t c = lane; c < d.q; c += 64) {
+                const uint32_t n = c ? states_of_subsets(hist, d.q, c) : 0u;
+                if (n) atomic_add_i64(&rp[1 + c], n);
+            }
         }
     }
     SW_PHASE(pc, 8);   // slots, ring sums
@@ -836,7 +949,7 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
 // roots of clusters inside the tile it found (keyed by their own sites).
 // Wave w owns rows w, w+4, w+8, ... (lane = column); its labels are all
 // loaded first.  LDS entries are 16 bits (so more workgroups fit a CU): a
-// tile-local index, ROOT16 | slot for a node, ROOT16 | RES16 | state for a
+// tile-local index, NODE16 + slot for a node, ROOT16 | RES16 | state for a
 // resolved root inside the tile.
 // XY: the draw per cluster is a reflection bit instead of a state, and each
 // site of a reflected cluster has its angle reflected across the line
@@ -850,10 +963,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     constexpr uint32_t RES16 = 0x4000u;     // a resolved root inside the tile
     constexpr uint32_t NKN = 512;           // node table (>= nslot(TY), a power of two)
     constexpr uint32_t NODE_ENTRY = 0x8000u;   // a list entry that names a node
-    static_assert(nslot(TY) <= NKN && nslot(TY) <= NT && nslot(TY) < RES16, "one thread per node");
+    static_assert(nslot(TY) < NKN && nslot(TY) <= NT && nslot(TY) < RES16, "one thread per node");
     __shared__ uint16_t E[TY * TX];
     __shared__ uint16_t list[NW][PER * TX + 64 + 64];   // roots inside the tile, nodes, a scratch slot per lane
-    __shared__ uint32_t NK[NKN];            // per node: its root's key, then its state
+    __shared__ uint32_t NK[NKN];            // per node (slot + 1): its root's key, then its state
 
     LatDesc d;
     uint32_t tile, lat;
@@ -877,7 +990,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     const uint32_t wave_step = NW * L;             // sites between a wave's consecutive rows
     const gptr<const char> lab_tile = (gptr<const char>)(glb(d.tlab) + (size_t)y0 * L + x0);
     const gptr<char> s_tile = (gptr<char>)(glb(d.s) + (size_t)y0 * L + x0);
-    const uint32_t n_used = min(glb(d.edges)[(size_t)tile * edge_words(TY) + 6], NS);
+    // the tile's node count, by a vector load ahead of the labels': a scalar one
+    // would be waited for before them
+    uint32_t lane0 = 0;
+    asm("" : "+v"(lane0));
+    const uint32_t n_loaded = glb(d.edges)[(size_t)tile * edge_words(TY) + 6 + lane0];
     // XY: the sweep's direction (wave-uniform)
     const uint32_t phi = XY ? __builtin_amdgcn_readfirstlane(xy_direction(d, t)) : 0u;
 
@@ -893,6 +1010,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             v[j] = (vcol && (FULL || r < h)) ? (uint32_t)*lab_p : 0u;
             lab_p += wave_step;
         }
+        const uint32_t n_used = min(n_loaded, NS);
         const uint32_t nj = lane * NW + wave;   // this lane's node
         const bool is_node = nj < n_used;
         const uint64_t nw = is_node ? nodes[node0 + nj] : 0ull;
@@ -907,28 +1025,29 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             if (vcol) E[li0 + j * NW * TX] = (uint16_t)v[j];
         }
         SW_PHASE(pc, 0);   // labels in
-        // The roots (tagged ROOT16), one ballot per row: a cluster inside the
-        // tile joins this wave's list, a node's slot must name a node of the
-        // tile (labels outside the tile are 0).  Lanes with nothing to list store
-        // to their scratch slot instead of branching around the store.
+        // The roots (tagged), one ballot per row: that of a cluster inside the tile
+        // joins this wave's list, a node's slot must name a node of the tile
+        // (labels outside the tile are 0).  Lanes with nothing
+        // to list store to their scratch slot instead of branching around the
+        // store.
         uint32_t nterm = 0;   // wave-uniform
-        uint32_t badv = 0;
+        uint32_t most = 0;
 #pragma unroll
         for (uint32_t j = 0; j < PER; ++j) {
             const uint32_t r = wave + NW * j;
             if (!FULL && r >= h) continue;
-            const uint64_t m = ballot(v[j] == (ROOT16 | NOSLOT));
-            badv |= (v[j] - (ROOT16 + n_used)) < (NOSLOT - n_used) ? 1u : 0u;
+            const uint64_t m = ballot(v[j] == ROOT16);
+            most = max(most, v[j]);
             my_list[lane_in(m) ? nterm + lanes_below(m) : PER * TX + 64 + lane] = (uint16_t)(li0 + j * NW * TX);
             nterm += popc64(m);
         }
-        bad |= badv != 0;
+        bad |= most >= NODE16 + n_used;
         SW_PHASE(pc, 1);   // roots inside the tile listed
         // this wave's nodes find their roots' keys and join the list
-        if (is_node) NK[nj] = key_of(n_find_from(nodes, n_nodes, node0 + nj, nw, bad));
+        if (is_node) NK[nj + 1] = key_of(n_find_from(nodes, n_nodes, node0 + nj, nw, bad));
         {
             const uint64_t m = ballot(is_node);
-            if (is_node) my_list[nterm + lanes_below(m)] = (uint16_t)(NODE_ENTRY | nj);
+            if (is_node) my_list[nterm + lanes_below(m)] = (uint16_t)(NODE_ENTRY | (nj + 1));
             nterm += popc64(m);
         }
         SW_PHASE(pc, 2);   // node roots found
@@ -1102,7 +1221,7 @@ __global__ __launch_bounds__(64 * NW) void k_csize(const LatDesc* descs, const W
         if (vx) {
             cur = r * TX + lane;
             uint32_t x = E[cur];
-            while (!(x & ROOT16) && x < cur) {
+            while (x < cur) {   // (a tagged entry is larger than every index)
                 cur = x;
                 x = E[cur];
             }
@@ -1120,8 +1239,8 @@ __global__ __launch_bounds__(64 * NW) void k_csize(const LatDesc* descs, const W
         const uint32_t li = r * TX + lane;
         const uint32_t x = vx ? E[li] : 0u, c = C[li];
         if (!(x & ROOT16) || !c) continue;
-        const uint32_t slot = x & 0x7FFFu;
-        if (slot == NOSLOT) {
+        const uint32_t slot = x - NODE16;
+        if (x == ROOT16) {
             const uint64_t c2 = (uint64_t)c * c;
             s2 += c2;
             s4 += c2 * c2;
@@ -1201,30 +1320,23 @@ __global__ __launch_bounds__(threads_of<TY>()) void k_measure(const LatDesc* des
     stage_spins<TY, threads_of<TY>()>(sp, d, g, tid);
     __syncthreads();
     const uint32_t x = lane;
-    const bool vx = x < w;
     const uint64_t validm = (w == 64) ? ~0ull : ((1ull << w) - 1ull);
     const uint32_t r0 = wave * RPW, r1 = min(h, r0 + RPW);
-    static_assert(RPW < 32, "per-lane counters hold at most 31 rows");
-    // unequal pairs counted per wave in a scalar; for q <= 16 the states
-    // 1..q-1 in per-lane bytes (as in k_bond_label), other q through the
-    // shared histogram
-    const bool q8 = d.q <= 8, q16 = d.q <= 16;
-    uint32_t n_unsat = 0;
-    uint64_t packed[2] = {0ull, 0ull};
+    count_tile_states<TY, threads_of<TY>()>(sp, g, d.q, hist, tid);
+    uint32_t n_unsat = 0;   // wave-uniform
     for (uint32_t r = r0; r < r1; ++r) {
         const uint8_t* row = sp + r * SPW;
         const uint32_t s = row[x], sr = row[x + 1], sd = row[SPW + x];
         n_unsat += popc64(ballot(s != sr) & validm) + popc64(ballot(s != sd) & validm);
-        if (q8) count_state_byte(packed, vx, s);
-        else if (q16) count_state_bytes(packed, vx, s & 15u);
-        else count_states(hist, vx, s);
     }
     if (lane == 0) atomicAdd(&tot, n_unsat);
-    if (q16) flush_state_bytes(packed, hist, d.q, lane);
     __syncthreads();
     int64_t* rp = ring_record(d, t, blockIdx.x % NCOPY);
     if (tid == 0) atomic_add_i64(&rp[0], tot);
-    if (tid >= 1 && tid < d.q && hist[tid]) atomic_add_i64(&rp[1 + tid], hist[tid]);
+    if (tid >= 1 && tid < d.q) {
+        const uint32_t n = states_of_subsets(hist, d.q, tid);
+        if (n) atomic_add_i64(&rp[1 + tid], n);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1262,24 +1374,24 @@ __global__ __launch_bounds__(threads_of<TY>()) void k_resolve(const LatDesc* des
     bool bad = false;
     for (uint32_t li = threadIdx.x; li < TY * TX; li += NT) {
         const uint32_t r = li / TX, c = li % TX;
-        E[li] = (r < g.h && c < g.w) ? lab[(size_t)(g.y0 + r) * d.L + g.x0 + c] : (ROOT16 | NOSLOT);
+        E[li] = (r < g.h && c < g.w) ? lab[(size_t)(g.y0 + r) * d.L + g.x0 + c] : ROOT16;
     }
     __syncthreads();
     for (uint32_t li = threadIdx.x; li < TY * TX; li += NT) {
         const uint32_t r = li / TX, c = li % TX, y = g.y0 + r;
         if (r >= g.h || c >= g.w || y < ya || y >= yb) continue;
         uint32_t cur = li, v = E[cur];
-        while (!(v & ROOT16) && v < cur) {
+        while (v < cur) {   // (a tagged entry is larger than every index)
             cur = v;
             v = E[cur];
         }
         uint32_t root = INVALID;
         if (!(v & ROOT16)) {
             bad = true;
-        } else if ((v & ~ROOT16) == NOSLOT) {
+        } else if (v == ROOT16) {
             root = (g.y0 + cur / TX) * d.L + g.x0 + cur % TX;
         } else {
-            root = key_of(n_root(glb(d.nodes), n_nodes, node0 + (v & ~ROOT16), bad));
+            root = key_of(n_root(glb(d.nodes), n_nodes, node0 + (v - NODE16), bad));
         }
         out[(size_t)(y - ya) * d.L + g.x0 + c] = root;
     }

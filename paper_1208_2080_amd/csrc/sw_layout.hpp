@@ -11,9 +11,9 @@
 //                             of a smaller site of its tile-local cluster (its
 //                             union-find grandparent in the tile), or, for the
 //                             cluster's smallest site (its tile-local root),
-//                             ROOT16 | slot, slot the root's node in the tile's
-//                             edge forest, NOSLOT if the cluster touches no
-//                             tile edge
+//                             ROOT16 if the cluster touches no tile edge, else
+//                             NODE16 + slot, slot the root's node in the tile's
+//                             edge forest
 //     resolved     uint32 from byte 0: smallest site indices of the clusters,
 //                             for label reads (at most N/2 sites at a time, so
 //                             the tile labels stay intact); a lattice swept
@@ -44,8 +44,8 @@ namespace swmi {
 
 constexpr uint32_t TX = 64;           // tile width: one wave, one column per lane
 constexpr uint32_t NCOPY = 64;        // partial copies of each ring record
-constexpr uint32_t NOSLOT = 0x7FFFu;       // root of a cluster inside its tile
-constexpr uint32_t ROOT16 = 0x8000u;       // tile-local root's tag in 16-bit entries and tile labels
+constexpr uint32_t ROOT16 = 0x8000u;       // tag of tile-local roots in 16-bit entries and tile labels
+constexpr uint32_t NODE16 = ROOT16 + 1u;   // plus a slot: a root with a node
 constexpr uint32_t INVALID = 0xFFFFFFFFu;
 constexpr uint32_t WHOLE_LMAX = 128;       // largest L swept whole in one workgroup's LDS
 

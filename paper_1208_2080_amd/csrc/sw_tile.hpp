@@ -70,6 +70,30 @@ __device__ __forceinline__ void flush_state_bytes(const uint64_t (&w)[2], uint32
     }
 }
 
+// Lanes k and k + 1 (k wave-uniform) of the words v[0..3] set to the halves of
+// the wave-uniform values x0, y0 (lane k) and x1, y1.  The lane goes through m0
+// (an instruction takes one scalar register), which is given back as it was.
+__device__ __forceinline__ void write_rows(uint32_t (&v)[4], uint32_t k, uint64_t x0, uint64_t y0, uint64_t x1, uint64_t y1)
+{
+    uint32_t m0;
+    asm("s_mov_b32 %4, m0\n\t"
+        "s_mov_b32 m0, %5\n\t"
+        "v_writelane_b32 %0, %6, m0\n\t"
+        "v_writelane_b32 %1, %7, m0\n\t"
+        "v_writelane_b32 %2, %8, m0\n\t"
+        "v_writelane_b32 %3, %9, m0\n\t"
+        "s_add_u32 m0, m0, 1\n\t"
+        "v_writelane_b32 %0, %10, m0\n\t"
+        "v_writelane_b32 %1, %11, m0\n\t"
+        "v_writelane_b32 %2, %12, m0\n\t"
+        "v_writelane_b32 %3, %13, m0\n\t"
+        "s_mov_b32 m0, %4"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "=&s"(m0)
+        : "s"(k), "s"((uint32_t)x0), "s"((uint32_t)(x0 >> 32)), "s"((uint32_t)y0), "s"((uint32_t)(y0 >> 32)),
+          "s"((uint32_t)x1), "s"((uint32_t)(x1 >> 32)), "s"((uint32_t)y1), "s"((uint32_t)(y1 >> 32))
+        : "scc");
+}
+
 struct TileGeom {
     uint32_t tx, ty, x0, y0, w, h;
 };
@@ -172,7 +196,7 @@ constexpr uint32_t LDS_CAP = 1u << 15;     // cap of union retries in LDS (> sit
 // 128 x 128 sites), an index below 2^15 (16 bits: a tile has at most 2^13
 // sites, such a lattice 2^14) that is never larger than its own; roots point
 // at themselves.  Entries only ever decrease (unions hook the larger root under
-// the smaller one with a minimum; finds point nodes at their grandparents),
+// the smaller one with a minimum; finds point nodes at their roots),
 // so every walk that steps only to smaller indices ends.  A walk that stops at
 // a node pointing to a larger index has met a corrupted forest and sets `bad`,
 // which the kernel reports.  16-bit entries halve the forest's LDS, so more
@@ -212,29 +236,26 @@ __device__ __forceinline__ uint32_t lds_min(uint16_t* P, uint32_t i, uint32_t v,
     return v;
 }
 
-// Roots of a and b while unions may still run, both walked in the same loop
-// so that their LDS round trips overlap, with path splitting: every visited
-// node is pointed at its grandparent (a stored value is always an ancestor,
-// so races with other finds and hooks are benign).
+// Roots of a and b while unions may still run, both walked in the same loop so
+// that their LDS round trips overlap.  A walked node is pointed at the root it
+// found (an ancestor, so races with other finds and hooks are benign); a chain
+// that has ended stays where it is without a predicate.  Splitting the path
+// at every step instead takes two more reads and stores a step: the labelling at
+// L = 16384 0.670 ms against 0.659; no shortening at all 0.666, but the flip
+// then walks longer (0.347 against 0.324).
 template <class T>
 __device__ __forceinline__ void lds_find2(T* P, uint32_t& a, uint32_t& b, bool& bad)
 {
+    const uint32_t a0 = a, b0 = b;
     uint32_t pa = lds_ld(&P[a]), pb = lds_ld(&P[b]);
     while (pa < a || pb < b) {
-        const bool sa = pa < a, sb = pb < b;
-        const uint32_t ga = sa ? lds_ld(&P[pa]) : pa;
-        const uint32_t gb = sb ? lds_ld(&P[pb]) : pb;
-        if (sa) {
-            lds_st(&P[a], ga);
-            a = pa;
-            pa = ga;
-        }
-        if (sb) {
-            lds_st(&P[b], gb);
-            b = pb;
-            pb = gb;
-        }
+        a = min(a, pa);
+        b = min(b, pb);
+        pa = lds_ld(&P[a]);
+        pb = lds_ld(&P[b]);
     }
+    if (a < a0) lds_st(&P[a0], a);
+    if (b < b0) lds_st(&P[b0], b);
     bad |= pa != a || pb != b;
 }
 

@@ -118,3 +118,35 @@ def test_cluster_sums_of_few_and_many_tiles(L, reps, tile_rows):
             want.append([sum(int(c) ** 2 for c in sizes), sum(int(c) ** 4 for c in sizes)])
         assert b.cluster_sums(i, 0, 3).tolist() == want, f"replica {i}"
     b.close()
+
+
+@pytest.mark.parametrize("L,q,tile_rows", [(129, 2, 64), (193, 3, 64), (257, 9, 64), (191, 4, 32), (321, 5, 128),
+                                           (1023, 2, 64), (1027, 16, 64), (1153, 2, 64), (130, 2, 32), (192, 13, 128)])
+def test_full_and_ragged_strips(L, q, tile_rows):
+    """Full strips of odd lattices (pairs that cross rows' starts and tiles'
+    edges) and of even ones, ragged tiles beside them, at every tile height and
+    number of waves, every way the states are counted."""
+    check(L, q, calls=(1, 3), tile_rows=tile_rows)
+
+
+@pytest.mark.parametrize("K", [0.0, float("inf")])
+@pytest.mark.parametrize("L", [128, 193, 1025])
+def test_extreme_couplings_by_tiles(L, K):
+    check(L, 2, K=K, calls=(2,), tile_rows=64)
+    check(L, 3, K=K, calls=(2,), tile_rows=64, random_start=False)
+
+
+@pytest.mark.parametrize("q", [2, 3, 4, 5, 8, 9, 16, 17, 255])
+def test_state_counts_by_subsets(q):
+    """The counts of a lattice loaded with every state in known numbers, full and
+    partial words at the right edge."""
+    for L in (130, 197):
+        rng = np.random.default_rng(q)
+        spins = rng.choice(q, size=(L, L), p=np.arange(1, q + 1) / (q * (q + 1) / 2)).astype(np.uint8)
+        lat = binding.Lattice(L, q, 0.0, seed=1, obs_capacity=8, tile_rows=64)
+        ref = oracle.OracleLattice(L, q, 0.0, 1, spins=spins, sweep=5)
+        lat.load_spins(spins, 5)
+        lat.sweep(3)
+        print(f"case counts q={q} L={L}", flush=True)
+        assert np.array_equal(lat.measure(5, 3), ref.run(3))
+        lat.close()
