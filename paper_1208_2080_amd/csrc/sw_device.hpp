@@ -73,15 +73,15 @@ __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
     return {c0, c1, c2, c3};
 }
 
-// Counter (c0, 0, c2, 0) with the first round's product of c0 given: a loop
+// Counter (c0, 0, c2, c3) with the first round's product of c0 given: a loop
 // whose c0 moves by a constant keeps that product by one 64-bit addition.
 constexpr uint64_t PHILOX_M0 = 0xD2511F53u;
 
-__device__ __forceinline__ u32x4 philox4x32_10_from(uint64_t c0_times_m0, uint32_t c2, const PhiloxKeys& ks)
+__device__ __forceinline__ u32x4 philox4x32_10_from(uint64_t c0_times_m0, uint32_t c2, uint32_t c3_in, const PhiloxKeys& ks)
 {
     const uint64_t q1 = (uint64_t)0xCD9E8D57u * c2;
     uint32_t c0 = (uint32_t)(q1 >> 32) ^ ks.k0[0], c1 = (uint32_t)q1;
-    uint32_t d2 = (uint32_t)(c0_times_m0 >> 32) ^ ks.k1[0], c3 = (uint32_t)c0_times_m0;
+    uint32_t d2 = (uint32_t)(c0_times_m0 >> 32) ^ c3_in ^ ks.k1[0], c3 = (uint32_t)c0_times_m0;
 #pragma unroll
     for (int round = 1; round < 10; ++round) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;

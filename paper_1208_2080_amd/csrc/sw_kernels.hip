@@ -549,7 +549,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             const uint32_t s0 = row[x], s0r = row[x + 1];
             const uint32_t s1 = row[SPW + x], s1r = row[SPW + x + 1];
             const uint32_t s2 = row[2 * SPW + x];
-            const u32x4 q4 = philox4x32_10_from(m0, t, ks);
+            const u32x4 q4 = philox4x32_10_from(m0, t, 0u, ks);
             m0 += m0_step;
             uint32_t wx0, wy0, wx1, wy1;
             if constexpr (ODD) {

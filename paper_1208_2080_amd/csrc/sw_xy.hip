@@ -16,7 +16,7 @@
 // polynomials, then rotate by the quarter turns; a site's projection on the
 // direction and the cos and sin of its bonds' angle differences follow from
 // products of those values.  The bond test is the FP64 rule u < -expm1(-y),
-// with an FP32 estimate deciding whenever u is far from the threshold.
+// with an FP32 estimate deciding whenever u is far enough from the threshold.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -41,14 +41,21 @@ __device__ __forceinline__ double fma_k(double a, double b, double k)
     return r;
 }
 
+// v with its sign changed if bit 31 of k is set.
+__device__ __forceinline__ double flip_sign(double v, uint32_t k)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v) ^ ((uint64_t)(k & 0x80000000u) << 32);
+    return __longlong_as_double((long long)b);
+}
+
 // sin and cos of the angle a (a fraction a / 2^32 of a turn).  With k the
 // nearest quarter turn and d = a - k 2^30 in [-2^29, 2^29), x = d pi / 2^31
 // lies in [-pi/4, pi/4); the Taylor series of sin to x^17 and of cos to x^18
 // leave out less than 1e-19 there.
 __device__ __forceinline__ void sincos_turn(uint32_t a, double& s, double& c)
 {
-    const uint32_t k = ((a + 0x20000000u) >> 30) & 3u;
-    const int32_t d = (int32_t)(a - (k << 30));
+    const uint32_t k = a + 0x20000000u;   // the quarter turn in the top two bits
+    const int32_t d = (int32_t)(a - (k & 0xC0000000u));
     const double x = (double)d * PI_2_31;
     const double x2 = x * x;
     // sin x = x + x^3 (-1/3! + x^2 (1/5! - ...)), cos x = 1 + x^2 (-1/2! + x^2 (1/4! - ...))
@@ -71,18 +78,26 @@ __device__ __forceinline__ void sincos_turn(uint32_t a, double& s, double& c)
     pc = fma_k(pc, x2, -1.0 / 24.0);                 // 1/4!
     pc = fma_k(pc, x2, 0.5);                         // the 1/2! term, subtracted below
     const double cx = fma(-x2, pc, 1.0);
-    // rotate by k quarter turns
-    const bool odd = k & 1u;
+    // rotate by k quarter turns: sin and cos change places for odd k; sin changes
+    // sign for k = 2, 3 and cos for k = 1, 2 (sign bits taken from k itself)
+    const bool odd = k & 0x40000000u;
     const double ss = odd ? cx : sx, cc = odd ? sx : cx;
-    s = (k >= 2u) ? -ss : ss;
-    c = (k == 1u || k == 2u) ? -cc : cc;
+    s = flip_sign(ss, k);
+    c = flip_sign(cc, k + 0x40000000u);
 }
 
-// A term of an observable sum: v (|v| <= 1) rounded to a multiple of 2^-30
-// (to nearest, ties to even), in those units, as an integer-valued double: a
-// lane adds one term per row of its strip (at most TY, |sum| <= 2^37 < 2^53),
-// so its sums are exact in FP64 and become int64 unchanged.
-__device__ __forceinline__ double fx30(double v) { return rint(v * 1073741824.0); }
+// Observable sums: a term v (|v| <= 1) counts as v 2^30 rounded to an integer (to
+// nearest, ties to even).  1.5 2^52 + v 2^30, rounded once, is that integer in
+// the low bits of a double whose spacing there is one, so the bits of such
+// doubles can be added as 64-bit integers; FX_ZERO is the bits of a zero term.
+// Two instructions a term (multiply, round, add in FP64: three).
+constexpr double FX_BASE = 6755399441055744.0;   // 1.5 * 2^52
+constexpr uint64_t FX_ZERO = 0x4338000000000000ull;
+
+__device__ __forceinline__ void fx30_add(uint64_t& acc, double v, double two30)
+{
+    acc += (uint64_t)__double_as_longlong(fma_k(v, two30, FX_BASE));
+}
 
 // The projection cos(theta - phi) = cos theta cos phi + sin theta sin phi,
 // rounded product by product (no fused multiply-add): for a spin exactly a
@@ -93,30 +108,27 @@ __device__ __forceinline__ double projection(double s, double c, double sphi, do
     return __dadd_rn(__dmul_rn(c, cphi), __dmul_rn(s, sphi));
 }
 
-// u < 1 - exp(-y), y >= 0 (may be +inf), decided as in FP64: an FP32
-// estimate of 1 - e^{-y} is within a few 1e-7 of the FP64 value, so when u is
-// farther than BOND_MARGIN from it the estimate decides, else FP64 expm1 does.
-constexpr double BOND_MARGIN = 1.0 / 4096.0;
+// The bond rule u < 1 - exp(-y), y >= 0 (may be +inf), decided as in FP64: an
+// FP32 estimate of u - (1 - exp(-y)) from the top 32 bits of u is within 10^-6
+// of the FP64 value (the exponential's own error, its argument's and three
+// roundings are a few 10^-7, the bits left out of u 2^-32), so when it is larger
+// than BOND_MARGIN in magnitude its sign decides, else FP64 expm1 does (one
+// test in 10^5).
+constexpr float BOND_MARGIN = 1.0f / 262144.0f;
 
-__device__ __forceinline__ bool bond_test(double u, double y)
+__device__ __forceinline__ bool bond_exact(uint32_t wa, uint32_t wb, double y)
 {
-    const double pf = (double)(1.0f - __expf(-(float)y));
-    if (u < pf - BOND_MARGIN) return true;
-    if (u >= pf + BOND_MARGIN) return false;
+    const double u = (double)((((uint64_t)wa) << 21) | (wb >> 11)) * 0x1p-53;
     return u < -expm1(-y);
 }
 
-template <class T>
-__device__ __forceinline__ T shfl_down1(T v)
+// The value of the lane whose number times four is addr.
+__device__ __forceinline__ double lane_value(double v, uint32_t addr)
 {
-    static_assert(sizeof(T) == 8, "64-bit values");
-    uint64_t b;
-    __builtin_memcpy(&b, &v, 8);
-    const uint32_t lo = (uint32_t)__shfl_down((int)(uint32_t)b, 1), hi = (uint32_t)__shfl_down((int)(uint32_t)(b >> 32), 1);
-    b = ((uint64_t)hi << 32) | lo;
-    T out;
-    __builtin_memcpy(&out, &b, 8);
-    return out;
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute((int)addr, (int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)addr, (int)(uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
 __device__ __forceinline__ long long wave_sum_i64(long long v)
@@ -150,6 +162,12 @@ __device__ __forceinline__ int64_t* xy_record(const LatDesc& d, uint32_t sweep, 
 // call (counter (i, 0, t, 4)): words 0, 1 make the 53-bit uniform of the +x
 // bond, words 2, 3 that of the +y bond.  The bond words go to the tile-major
 // bond plane the labeller reads.
+//
+// Bound by vector issue: 137 instructions per row of 64 sites (36 Philox, 35
+// sin and cos, 20 the two bond tests, 20 the six sums), 1.10 ms at L = 16384
+// with measurement; 172 and 1.50 ms with the tests' estimates formed in FP64
+// from 53-bit uniforms, projections computed twice and three instructions per
+// term of the sums.
 template <int TY, uint32_t NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_xy_bonds(const LatDesc* descs, const WorkItem* map, uint32_t k,
                                                                uint32_t flags)
@@ -190,51 +208,66 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     const PhiloxKeys ks = philox_keys_v(d.key0, d.key1);
     const gptr<uint64_t> bw = glb(d.bonds) + (size_t)tile * 2 * TY;
     uint32_t n_active = 0;   // wave-uniform
-    double ex = 0, ey = 0, ix = 0, iy = 0, mx = 0, my = 0;
+    uint64_t ex = 0, ey = 0, ix = 0, iy = 0, mx = 0, my = 0;
+    const float kf = (float)(-k2 * 1.4426950408889634074);   // -2K log2 e
+    const uint32_t right = ((lane + 1u) & 63u) * 4u;
+    double two30 = 1073741824.0;
+    asm("" : "+v"(two30));   // in vector registers: fx30_add's other constant takes the scalar operand
 
     if (r0 < r1) {
         // tile row rr of this column (row h is the first row of the tile below,
-        // or row 0 of the lattice)
-        auto row_angle = [&](uint32_t rr) { return ang[((y0 + rr == L) ? 0u : y0 + rr) * L + x]; };
+        // or row 0 of the lattice), from a wave-uniform base
+        auto row_angle = [&](uint32_t rr) { return (ang + (size_t)((y0 + rr == L) ? 0u : y0 + rr) * L)[x]; };
         double si, ci;
         sincos_turn(row_angle(r0), si, ci);
+        double pi_ = projection(si, ci, sphi, cphi);
+        // site indices fit 32 bits (N <= 2^32)
+        uint64_t m0 = PHILOX_M0 * (uint32_t)((y0 + r0) * L + x);
+        const uint64_t m0_step = PHILOX_M0 * L;
         // the rows below are loaded two iterations ahead of their use
         uint32_t a1 = row_angle(r0 + 1), a2 = (r0 + 2 <= r1) ? row_angle(r0 + 2) : 0u;
         for (uint32_t r = r0; r < r1; ++r) {
-            const uint32_t y = y0 + r;
-            const uint32_t i = y * L + x;   // site indices fit 32 bits (N <= 2^32)
             const uint32_t ad = a1;
             a1 = a2;
             if (r + 3 <= r1) a2 = row_angle(r + 3);
+            const double s_right = lane_value(si, right), c_right = lane_value(ci, right);
             double sd, cd;
             sincos_turn(ad, sd, cd);
-            const double s_right = shfl_down1(si), c_right = shfl_down1(ci);
             const double sr = edge ? sedge[r] : s_right, cr = edge ? cedge[r] : c_right;
             if (!only_measure) {
-                const double pi_ = projection(si, ci, sphi, cphi);
                 const double pr = projection(sr, cr, sphi, cphi);
                 const double pd = projection(sd, cd, sphi, cphi);
-                const u32x4 q = philox4x32_10(i, 0u, t, 4u, ks);
-                const double ux = (double)((((uint64_t)q.x) << 21) | (q.y >> 11)) * 0x1p-53;
-                const double uy = (double)((((uint64_t)q.z) << 21) | (q.w >> 11)) * 0x1p-53;
-                const double kc = k2 * pi_;
-                const bool bx = vx && pi_ * pr > 0.0 && bond_test(ux, kc * pr);
-                const bool by = vx && pi_ * pd > 0.0 && bond_test(uy, kc * pd);
-                const uint64_t BX = ballot(bx) & validm, BY = ballot(by) & validm;
+                const u32x4 q = philox4x32_10_from(m0, t, 4u, ks);
+                m0 += m0_step;
+                // the estimates: c_i c_j keeps its sign and is no denormal in FP32
+                // (a nonzero projection is above 2^-56); 2K may overflow to
+                // infinity there, where exp(-y) is 0 in FP64 too
+                const float fi = (float)pi_, fr = (float)pr, fd = (float)pd, ki = kf * fi;
+                const float tx = fmaf((float)q.x, 0x1p-32f, __builtin_amdgcn_exp2f(ki * fr)) - 1.0f;
+                const float ty = fmaf((float)q.z, 0x1p-32f, __builtin_amdgcn_exp2f(ki * fd)) - 1.0f;
+                const uint64_t sx = ballot(fi * fr > 0.0f) & validm, sy = ballot(fi * fd > 0.0f) & validm;
+                uint64_t BX = sx & ballot(tx < 0.0f), BY = sy & ballot(ty < 0.0f);
+                const uint64_t nx = sx & ballot(!(fabsf(tx) >= BOND_MARGIN)), ny = sy & ballot(!(fabsf(ty) >= BOND_MARGIN));
+                if (nx | ny) {
+                    const double kc = k2 * pi_;
+                    BX = (BX & ~nx) | (nx & ballot(bond_exact(q.x, q.y, kc * pr)));
+                    BY = (BY & ~ny) | (ny & ballot(bond_exact(q.z, q.w, kc * pd)));
+                }
                 if (lane == 0) {
                     bw[r] = BX;
                     bw[TY + r] = BY;
                 }
                 n_active += popc64(BX) + popc64(BY);
+                pi_ = pd;
             }
-            if (meas && vx) {
+            if (meas) {
                 // cos and sin of theta_i - theta_j from the two sites' sin and cos
-                ex += fx30(fma(ci, cr, si * sr));
-                ix += fx30(fma(si, cr, -(ci * sr)));
-                ey += fx30(fma(ci, cd, si * sd));
-                iy += fx30(fma(si, cd, -(ci * sd)));
-                mx += fx30(ci);
-                my += fx30(si);
+                fx30_add(ex, fma(ci, cr, si * sr), two30);
+                fx30_add(ix, fma(si, cr, -(ci * sr)), two30);
+                fx30_add(ey, fma(ci, cd, si * sd), two30);
+                fx30_add(iy, fma(si, cd, -(ci * sd)), two30);
+                fx30_add(mx, ci, two30);
+                fx30_add(my, si, two30);
             }
             si = sd;
             ci = cd;
@@ -242,11 +275,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
     }
 
     if (meas) {
-        const long long v[6] = {(long long)ex, (long long)ey, (long long)ix, (long long)iy, (long long)mx,
-                                (long long)my};
+        const uint64_t zero = (uint64_t)(r0 < r1 ? r1 - r0 : 0u) * FX_ZERO;
+        const uint64_t v[6] = {ex, ey, ix, iy, mx, my};
 #pragma unroll
         for (int j = 0; j < 6; ++j) {
-            const long long sum = wave_sum_i64(v[j]);
+            const long long sum = wave_sum_i64(vx ? (long long)(v[j] - zero) : 0ll);
             if (lane == 0 && sum) atomicAdd(&acc[1 + j], (unsigned long long)sum);
         }
     }

@@ -150,3 +150,23 @@ def test_state_counts_by_subsets(q):
         print(f"case counts q={q} L={L}", flush=True)
         assert np.array_equal(lat.measure(5, 3), ref.run(3))
         lat.close()
+
+
+@pytest.mark.parametrize("K", [0.0, 1e-30, 0.3, 50.0, 1e300, float("inf")])
+@pytest.mark.parametrize("L", [65, 130])
+def test_xy_bond_estimates(L, K):
+    """Bonds of the XY sweep over the whole range of couplings (the estimates
+    under- and overflow at its ends): bonds, labels and angles as the oracle's."""
+    print(f"case XY L={L} K={K}", flush=True)
+    for start in (True, False):
+        lat = binding.XYLattice(L, K, seed=21, random_start=start, obs_capacity=4)
+        ref = oracle.XYOracleLattice(L, K, 21, random_start=start)
+        for _ in range(3):
+            lat.sweep(1)
+            out = ref.sweep()
+            bx, by = lat.bonds()
+            assert np.array_equal(bx, oracle.pack_bonds(out["bx"]))
+            assert np.array_equal(by, oracle.pack_bonds(out["by"]))
+            assert np.array_equal(lat.labels(), out["labels"])
+            assert np.array_equal(lat.angles(), ref.a)
+        lat.close()
