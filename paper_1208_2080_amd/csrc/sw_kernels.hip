@@ -485,11 +485,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
 
     if (tid < 256) hist[tid] = 0;
     if (tid < 3) tot[tid] = 0;
+    uint64_t preset[2] = {0ull, 0ull};   // PRESET: lane k holds row r0 + k's bond words
     if constexpr (PRESET) {
-        const gptr<uint64_t> bin = glb(d.bonds) + (size_t)tile * 2 * TY;
-        for (uint32_t j = tid; j < 2 * TY; j += NT) {
-            const uint32_t r = j % TY;
-            rb[r][j / TY] = r < h ? bin[j] : 0ull;
+        const gptr<const uint64_t> bin = glb(d.bonds) + (size_t)tile * 2 * TY;
+        const uint32_t r = wave * RPW + lane;
+        if (lane < RPW) {
+            if (r < h) {
+                preset[0] = bin[r];
+                preset[1] = bin[TY + r];
+            }
+            rb[r][0] = preset[0];
+            rb[r][1] = preset[1];
         }
     } else {
         stage_spins<TY, NT>(sp, d, g, tid);
@@ -657,14 +663,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             }
         }
     };
-    // the same row labelling over bond words that are already in LDS
+    // the same row labelling over bond words that are there already
     auto preset_rows = [&]() {
         for (uint32_t r = r0; r < r1; ++r) {
             if (uq.n > QCAP - 64) drain(uq, P, lane, bad);
-            const uint64_t hx = rb[r][0] & ~cross;
+            const uint64_t hx = lane_value64(preset[0], r - r0) & ~cross;
             lp = row_labels(P, rl, uq, r * TX + x, validm, hx, vprev, hprev, lp);
             hprev = hx;
-            vprev = rb[r][1];
+            vprev = lane_value64(preset[1], r - r0);
         }
     };
     const bool full = w == TX && r1 - r0 == RPW && d.thr_nz;
@@ -951,6 +957,9 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
 // loaded first.  LDS entries are 16 bits (so more workgroups fit a CU): a
 // tile-local index, NODE16 + slot for a node, ROOT16 | RES16 | state for a
 // resolved root inside the tile.
+// Bound by vector issue and latency in about equal parts (L = 16384, q = 2 at
+// K_c: 0.308 ms at eight workgroups a CU; 0.324 with the first step of every
+// walk read back from LDS); the XY form by HBM (0.60 ms, 2.7 GB).
 // XY: the draw per cluster is a reflection bit instead of a state, and each
 // site of a reflected cluster has its angle reflected across the line
 // perpendicular to the sweep's direction (the others are not touched).
@@ -1073,9 +1082,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         // the walk ends) to a root: resolved inside the tile, or a node whose
         // state is in the table; the new spins are stored at the end.
         // (A root's entry, ROOT16 and up, is larger than every tile index, so
-        // `x < cur` alone continues the walk.)
+        // `x < cur` alone continues the walk.)  The first step is taken from the
+        // label still in its register: a pointer leads to its target, a root's
+        // tag back to the site itself (one of two to three steps saved a row).
         auto walk = [&](uint32_t j) -> uint32_t {
-            uint32_t cur = li0 + j * NW * TX, x = E[cur];
+            uint32_t cur = min(v[j], li0 + j * NW * TX), x = E[cur];
             while (x < cur) {
                 cur = x;
                 x = E[cur];
@@ -1108,18 +1119,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
                         *(gptr<uint32_t>)(a_tile + (site0 + (j0 + j) * wave_step) * 4u) = xy_reflect(av[j], phi);
             }
         } else {
-            uint32_t e[PER];
 #pragma unroll
             for (uint32_t j = 0; j < PER; ++j) {
                 const uint32_t r = wave + NW * j;
-                e[j] = (vcol && (FULL || r < h)) ? walk(j) : 0u;
+                if (vcol && (FULL || r < h)) v[j] = walk(j);   // (the new state)
             }
             SW_PHASE(pc, 5);   // walks
             gptr<uint8_t> s_p = (gptr<uint8_t>)s_tile + site0;
 #pragma unroll
             for (uint32_t j = 0; j < PER; ++j) {
                 const uint32_t r = wave + NW * j;
-                if (vcol && (FULL || r < h)) *s_p = (uint8_t)e[j];
+                if (vcol && (FULL || r < h)) *s_p = (uint8_t)v[j];
                 s_p += wave_step;
             }
         }

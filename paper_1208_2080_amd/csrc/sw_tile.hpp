@@ -94,6 +94,14 @@ __device__ __forceinline__ void write_rows(uint32_t (&v)[4], uint32_t k, uint64_
         : "scc");
 }
 
+// The value of lane k (wave-uniform) as a scalar.
+__device__ __forceinline__ uint64_t lane_value64(uint64_t v, uint32_t k)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)k);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 struct TileGeom {
     uint32_t tx, ty, x0, y0, w, h;
 };
