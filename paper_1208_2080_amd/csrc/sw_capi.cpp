@@ -859,20 +859,24 @@ struct sw_batch {
     uint32_t* d_n;
     size_t total_tiles;
     std::vector<WorkItem> h_map;    // host copy of the last uploaded map
-    std::vector<uint32_t> h_n;
+    std::vector<uint32_t> h_n, h_nw;
     std::vector<uint32_t> map_order;  // replica order of the uploaded map
     StepGraphs steps;                            // captured sweeps of every replica (sweep_all)
     bool csum = false;                           // some replica measures cluster-size sums
-    // replicas swept whole (k_whole): device list, L <= 64 first, then the rest
+    // replicas that may be swept whole (k_whole): device list, L <= 64 first, then
+    // the rest, and a call's sweep counts of those it sweeps so
     uint32_t* d_list = nullptr;
+    uint32_t* d_nw = nullptr;
     uint32_t n_whole64 = 0, n_whole128 = 0;
-    size_t tile_tiles = 0;                       // tiles of the replicas swept by tiles
+    bool whole_all = false;                      // sweep_all sweeps them whole (else by tiles, like the others)
+    bool whole_alone = false;                    // and so does a call that sweeps no others
+    size_t tile_tiles = 0;                       // tiles of the replicas sweep_all sweeps by tiles
 };
 
 namespace {
 
 struct BatchLayout {
-    size_t descs, map, nvec, list, header;
+    size_t descs, map, nvec, list, nwhole, header;
     std::vector<size_t> off;
     std::vector<Geometry> g;
     std::vector<Carve> c;
@@ -906,6 +910,8 @@ int batch_layout(const sw_params* params, uint32_t n, BatchLayout* out)
     off = align_up(off + sizeof(uint32_t) * n);
     b.list = off;
     off = align_up(off + sizeof(uint32_t) * n);
+    b.nwhole = off;
+    off = align_up(off + sizeof(uint32_t) * n);
     b.header = off;
     for (uint32_t r = 0; r < n; ++r) {
         b.off[r] = off;
@@ -916,14 +922,38 @@ int batch_layout(const sw_params* params, uint32_t n, BatchLayout* out)
     return SW_OK;
 }
 
-// Upload the tile list of the replicas with n_each[r] > 0, largest count first,
-// so that the replicas still sweeping at step k are a prefix of the list.
+// Whether sweeping the replicas that fit LDS whole is faster than by tiles, for
+// the same number of sweeps of every replica.  Whole, one after another on 256
+// CUs: 9.7 us a sweep per lattice and CU up to L = 64 and 28 us up to L = 128.
+// By tiles: their sites at 240 a ns, plus the 25 us that three launches over few
+// tiles take, unless other replicas need those launches anyway.  Measured, us a
+// sweep whole / by tiles: 256 lattices of L = 64 9.8 / 25.3, 1024 37.5 / 41.5,
+// 2048 74.8 / 59.3; 256 of L = 128 27.7 / 42.4, 512 54.8 / 60.9, 1024 109 / 96;
+// 256 uneven replicas of which 81 fit LDS, 50 sweeps: 63.6 / 61.8 ms.
+bool whole_is_faster(const BatchLayout& lay, bool others)
+{
+    double whole_us = 0.0, tiles_us = others ? 0.0 : 25.0;
+    uint64_t n64 = 0, n128 = 0;
+    for (const Geometry& g : lay.g) {
+        if (!g.whole) continue;
+        ++(g.L <= 64 ? n64 : n128);
+        tiles_us += (double)g.N / 240e3;
+    }
+    if (n64) whole_us += 9.7 * std::max(1.0, (double)n64 / 256.0);
+    if (n128) whole_us += 28.0 * std::ceil((double)n128 / 256.0);
+    return whole_us < tiles_us;
+}
+
+// Upload the tile list of the replicas with n_each[r] > 0 among those swept by
+// tiles, largest count first, so that the replicas still sweeping at step k are
+// a prefix of the list.
 // Returns, through prefix[k], the number of work items active at step k.
-int upload_map(sw_batch* b, const uint32_t* n_each, uint32_t kmax, std::vector<uint32_t>* prefix)
+int upload_map(sw_batch* b, const uint32_t* n_each, const std::vector<char>& by_tiles, uint32_t kmax,
+               std::vector<uint32_t>* prefix)
 {
     std::vector<uint32_t> order;
     for (uint32_t r = 0; r < b->n; ++r)
-        if (n_each[r] && !b->g[r].whole) order.push_back(r);
+        if (n_each[r] && by_tiles[r]) order.push_back(r);
     std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t c) { return n_each[a] > n_each[c]; });
     if (order != b->map_order || b->h_map.empty()) {
         b->h_map.clear();
@@ -964,19 +994,37 @@ int batch_whole(sw_batch* b, uint32_t n_uniform, const uint32_t* d_n_each, bool 
 
 int batch_enqueue(sw_batch* b, const uint32_t* n_each)
 {
-    uint32_t kmax = 0, kall = 0;
+    // kt: steps that the replicas too large for LDS take anyway; the others join
+    // those steps unless they have more sweeps to do (or sweep_all has them whole)
+    uint32_t kt = 0, kall = 0;
     for (uint32_t r = 0; r < b->n; ++r) {
         kall = std::max(kall, n_each[r]);
-        if (!b->g[r].whole) kmax = std::max(kmax, n_each[r]);
+        if (!b->g[r].whole) kt = std::max(kt, n_each[r]);
     }
     if (kall == 0) return SW_OK;
+    std::vector<char> by_tiles(b->n);
+    uint32_t kmax = 0;
+    bool any_whole = false;
+    b->h_nw.assign(b->n, 0u);
+    for (uint32_t r = 0; r < b->n; ++r) {
+        by_tiles[r] = !b->g[r].whole || (kt == 0 ? !b->whole_alone : !b->whole_all && n_each[r] <= kt);
+        if (by_tiles[r]) kmax = std::max(kmax, n_each[r]);
+        else if (n_each[r]) {
+            b->h_nw[r] = n_each[r];
+            any_whole = true;
+        }
+    }
     b->h_n.assign(n_each, n_each + b->n);
     HIP_TRY(hipMemcpyAsync(b->d_n, b->h_n.data(), b->n * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream));
-    int rc = batch_whole(b, 0, b->d_n, false);
-    if (rc) return rc;
+    int rc = SW_OK;
+    if (any_whole) {
+        HIP_TRY(hipMemcpyAsync(b->d_nw, b->h_nw.data(), b->n * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream));
+        rc = batch_whole(b, 0, b->d_nw, false);
+        if (rc) return rc;
+    }
     std::vector<uint32_t> prefix;
     if (kmax) {
-        rc = upload_map(b, n_each, kmax, &prefix);
+        rc = upload_map(b, n_each, by_tiles, kmax, &prefix);
         if (rc) return rc;
     }
     for (uint32_t k = 0; k < kmax; ++k) {
@@ -1050,8 +1098,14 @@ int sw_batch_init(const sw_params* params, uint32_t n, void* dev_ws, size_t ws_b
     for (uint32_t r = 0; r < n; ++r)
         if (lay.g[r].whole && lay.g[r].L > 64) list.push_back(r);
     b->n_whole128 = (uint32_t)list.size() - b->n_whole64;
+    b->d_nw = reinterpret_cast<uint32_t*>(b->base + lay.nwhole);
+    // (a replica made with SW_TILE_WHOLE keeps them all whole)
+    bool asked = false;
+    for (uint32_t r = 0; r < n; ++r) asked = asked || params[r].tile_rows == SW_TILE_WHOLE;
+    b->whole_all = asked || whole_is_faster(lay, list.size() < n);
+    b->whole_alone = asked || whole_is_faster(lay, false);
     for (uint32_t r = 0; r < n; ++r)
-        if (!lay.g[r].whole) b->tile_tiles += lay.g[r].ntiles;
+        if (!lay.g[r].whole || !b->whole_all) b->tile_tiles += lay.g[r].ntiles;
     b->desc.resize(n);
     for (uint32_t r = 0; r < n; ++r) b->csum = b->csum || b->g[r].csum;
     for (uint32_t r = 0; r < n; ++r) {
@@ -1117,7 +1171,7 @@ int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps)
         for (uint32_t r = 0; r < b->n; ++r) b->done[r] += n_sweeps;
         return SW_OK;
     }
-    if (b->n_whole64 + b->n_whole128) {
+    if (b->whole_all && b->n_whole64 + b->n_whole128) {
         // the replicas swept whole first, in launches of at most WHOLE_CHUNK
         // sweeps, each advancing their counters
         for (uint32_t done = 0; done < n_sweeps;) {
@@ -1134,11 +1188,14 @@ int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps)
     // the captured steps bake in the work map of every replica swept by
     // tiles; make sure it is the one uploaded
     std::vector<uint32_t> order;
-    for (uint32_t r = 0; r < b->n; ++r)
-        if (!b->g[r].whole) order.push_back(r);
+    std::vector<char> by_tiles(b->n);
+    for (uint32_t r = 0; r < b->n; ++r) {
+        by_tiles[r] = !b->g[r].whole || !b->whole_all;
+        if (by_tiles[r]) order.push_back(r);
+    }
     if (b->map_order != order || b->h_map.empty()) {
         std::vector<uint32_t> prefix;
-        int rc = upload_map(b, all.data(), 1, &prefix);
+        int rc = upload_map(b, all.data(), by_tiles, 1, &prefix);
         if (rc) return rc;
     }
     const Work w{b->d_descs, b->d_map, (uint32_t)b->tile_tiles, b->ty, b->stream, b->csum};

@@ -170,3 +170,30 @@ def test_xy_bond_estimates(L, K):
             assert np.array_equal(lat.labels(), out["labels"])
             assert np.array_equal(lat.angles(), ref.a)
         lat.close()
+
+
+@pytest.mark.parametrize("Ls", [[64] * 3, [128, 17], [64, 200], [2, 3, 500, 128]])
+def test_batches_of_small_lattices(Ls):
+    """Lattices that fit LDS alone (swept whole) and beside one that does not
+    (swept by tiles with it, or whole in a call that sweeps only them or sweeps
+    them further), with calls of both kinds in turn."""
+    reps = [dict(L=L, q=2 + i, K=wl.critical_coupling(2 + i), seed=80 + i, random_start=True) for i, L in enumerate(Ls)]
+    print(f"case small batch {Ls}", flush=True)
+    b = binding.Batch(reps, obs_capacity=64)
+    counts = np.zeros(len(Ls), dtype=int)
+    small = [2 if L <= 128 else 0 for L in Ls]
+    more = [6 if L <= 128 else 3 for L in Ls]
+    fewer = [1 if L <= 128 else 4 for L in Ls]
+    for each in (None, small, more, fewer, None, small, None):
+        if each is None:
+            b.sweep_all(2)
+            each = [2] * len(Ls)
+        else:
+            b.sweep(each)
+        counts += each
+    for r, rep in enumerate(reps):
+        ref = oracle.OracleLattice(rep["L"], rep["q"], rep["K"], rep["seed"], random_start=True)
+        rows = ref.run(int(counts[r]))
+        assert np.array_equal(b.measure(r, 0, int(counts[r])), rows), f"rows of replica {r}"
+        assert np.array_equal(b.spins(r), ref.s), f"spins of replica {r}"
+    b.close()
