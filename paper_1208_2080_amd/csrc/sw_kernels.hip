@@ -1411,10 +1411,11 @@ __global__ __launch_bounds__(threads_of<TY>()) void k_resolve(const LatDesc* des
 // One thread per (record, word): the sum of the word over the record's NCOPY
 // partial copies.
 __global__ __launch_bounds__(256) void k_ring_sum(const int64_t* ring, int64_t* out, uint32_t slots, uint32_t slot0,
-                                                  uint32_t n, uint32_t W, uint32_t stride)
+                                                  uint32_t n, uint32_t W, uint32_t stride, const uint32_t* err)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n * W) return;
+    if (i == 0 && err) glb(out)[(size_t)n * W] = *glb(err);
     const uint32_t rec = i / W, w = i - rec * W;
     const uint32_t slot = (uint32_t)(((uint64_t)slot0 + rec) % slots);
     const size_t R = stride;
@@ -1428,6 +1429,20 @@ __global__ __launch_bounds__(256) void k_ring_sum(const int64_t* ring, int64_t* 
         for (uint32_t c = 0; c < NCOPY; ++c) sum += base[(size_t)c * R];
     }
     glb(out)[i] = sum;
+}
+
+// Bytes of src copied to out by words (src 4-byte aligned, out too), then the
+// error flag.
+__global__ __launch_bounds__(256) void k_read_out(const uint32_t* src, uint32_t bytes, uint32_t* out, const uint32_t* err)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x, words = bytes >> 2;
+    if (i < words) glb(out)[i] = glb(src)[i];
+    if (i == 0) {
+        const gptr<const uint8_t> tail = (gptr<const uint8_t>)(glb(src) + words);
+        const gptr<uint8_t> to = (gptr<uint8_t>)(glb(out) + words);
+        for (uint32_t j = 0; j < (bytes & 3u); ++j) to[j] = tail[j];
+        glb(out)[(bytes + 3u) >> 2] = *glb(err);
+    }
 }
 
 // Advance sweep counters: lattice i by n (or by n_each[i] when given).
@@ -1672,13 +1687,21 @@ hipError_t launch_resolve(const LatDesc* descs, uint32_t lat, uint32_t ntiles, u
 }
 
 hipError_t launch_ring_sum(const int64_t* ring, int64_t* out, uint32_t slots, uint32_t slot0, uint32_t n,
-                           uint32_t words, uint32_t stride, hipStream_t s)
+                           uint32_t words, uint32_t stride, const uint32_t* err, hipStream_t s)
 {
     const uint64_t total = (uint64_t)n * words;
     if (total == 0) return hipSuccess;
     if (total > 0xFFFFFFFFull || slot0 >= slots || n >= slots || words > stride) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_ring_sum, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, s, ring, out, slots, slot0, n,
-                       words, stride);
+                       words, stride, err);
+    return hipGetLastError();
+}
+
+hipError_t launch_read_out(const void* src, size_t bytes, void* out, const uint32_t* err, hipStream_t s)
+{
+    if (bytes == 0 || bytes > (1u << 30)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_read_out, dim3((uint32_t)((bytes / 4 + 256) / 256)), dim3(256), 0, s,
+                       static_cast<const uint32_t*>(src), (uint32_t)bytes, static_cast<uint32_t*>(out), err);
     return hipGetLastError();
 }
 

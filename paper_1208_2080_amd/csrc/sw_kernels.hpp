@@ -56,9 +56,12 @@ hipError_t launch_resolve(const LatDesc* descs, uint32_t lat, uint32_t ntiles, u
                           hipStream_t s);
 // Sum the NCOPY partial copies of n ring records of `words` words (copies
 // `stride` words apart), from slot slot0 on (wrapping at `slots`), into
-// out[n][words].
+// out[n][words]; with err, its value into the word after them.
 hipError_t launch_ring_sum(const int64_t* ring, int64_t* out, uint32_t slots, uint32_t slot0, uint32_t n,
-                           uint32_t words, uint32_t stride, hipStream_t s);
+                           uint32_t words, uint32_t stride, const uint32_t* err, hipStream_t s);
+// bytes of src (4-byte aligned) to out, then *err to the uint32 at out + bytes
+// rounded up to a multiple of 4.
+hipError_t launch_read_out(const void* src, size_t bytes, void* out, const uint32_t* err, hipStream_t s);
 hipError_t launch_bump(const LatDesc* descs, uint32_t count, const uint32_t* n_each, uint32_t n, hipStream_t s);
 
 // No-allocation entry point: copy the descriptor d to d_out, clear the error

@@ -197,3 +197,35 @@ def test_batches_of_small_lattices(Ls):
         assert np.array_equal(b.measure(r, 0, int(counts[r])), rows), f"rows of replica {r}"
         assert np.array_equal(b.spins(r), ref.s), f"spins of replica {r}"
     b.close()
+
+
+def test_reads_small_and_large_from_several_threads():
+    """Reads that fit a pinned buffer and reads that do not, more readers at once
+    than there are buffers, and after every handle (and buffer) was given back."""
+    import threading
+
+    def use(i, L, n, errors):
+        try:
+            lat = binding.Lattice(L, 2, 0.88, seed=i, obs_capacity=n + 1, stream=torch.cuda.Stream())
+            ref = oracle.OracleLattice(L, 2, 0.88, i)
+            rows = ref.run(n)
+            for _ in range(3):
+                if lat.sweeps_done == 0:
+                    lat.sweep(n)
+                assert np.array_equal(lat.measure(0, n), rows)
+                assert np.array_equal(lat.measure(n // 2, 1), rows[n // 2:n // 2 + 1])
+                assert lat.measure(0, 0).shape == (0, 4)
+                assert np.array_equal(lat.spins(), ref.s)
+            lat.close()
+        except BaseException as e:   # reported by the test's thread
+            errors.append((L, n, e))
+
+    for _ in range(2):
+        errors = []
+        jobs = [(1, 7, 3), (2, 33, 5), (3, 362, 2), (4, 363, 2), (5, 400, 2), (6, 16, 2800), (7, 9, 40)]
+        threads = [threading.Thread(target=use, args=(*j, errors)) for j in jobs]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not errors, errors
