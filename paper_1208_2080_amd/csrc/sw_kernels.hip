@@ -874,6 +874,7 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
 {
     const uint32_t wave = wave_id(), lane = threadIdx.x & 63u;
     const uint32_t idx = blockIdx.x * 4 + wave;
+    __shared__ uint8_t pairs[4][2][256];
     if (idx >= nitems) return;
     LatDesc d;
     uint32_t tile, lat;
@@ -893,8 +894,11 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
 
     // Lane l takes the crossing bond of row l of the right edge (row l of the
     // right neighbour's left column) and of column l of the bottom edge
-    // (column l of the top row of the tile below); consecutive crossing bonds
-    // between the same two clusters are joined once.  The nodes' words are all
+    // (column l of the top row of the tile below); crossing bonds between the
+    // same two clusters are joined once: every hook is an atomic at memory, and
+    // those at one address wait for each other (at q = 2, K_c, dropping equal
+    // pairs that are not neighbours too takes the kernel from 0.141 to 0.131 ms
+    // at L = 16384, from 0.074 to 0.063 at 8192).  The nodes' words are all
     // loaded before the first union, so their round trips overlap.
     bool bad = false;
     uint32_t pa = INVALID, pb = INVALID;
@@ -928,8 +932,25 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
         }
         pa = __shfl(a1, 63);
         pb = __shfl(b1, 63);
-        const bool u1 = right && !(ua == a1 && ub == b1) && a1 < n && b1 < n;
-        const bool u2 = below && !(va == a2 && vb == b2) && a2 < n && b2 < n;
+        bool u1 = right && !(ua == a1 && ub == b1) && a1 < n && b1 < n;
+        bool u2 = below && !(va == a2 && vb == b2) && a2 < n && b2 < n;
+        // lanes further apart: the last lane of a table slot's pairs stands for
+        // those equal to its own
+        {
+            const uint32_t k1 = sa1 | (sb1 << 16), k2 = sa2 | (sb2 << 16);
+            uint8_t* const t1 = &pairs[wave][0][(k1 * 0x9E3779B1u) >> 24];
+            uint8_t* const t2 = &pairs[wave][1][(k2 * 0x9E3779B1u) >> 24];
+            // (other lanes' stores are read: these accesses must not be folded away)
+            if (u1) __hip_atomic_store(t1, (uint8_t)lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (u2) __hip_atomic_store(t2, (uint8_t)lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const uint32_t w1 = u1 ? __hip_atomic_load(t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : lane;
+            const uint32_t w2 = u2 ? __hip_atomic_load(t2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : lane;
+            // (by all lanes: a permute reads nothing from a lane that is masked off)
+            const uint32_t q1 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(w1 * 4), (int)k1);
+            const uint32_t q2 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(w2 * 4), (int)k2);
+            u1 = u1 && (w1 == lane || q1 != k1);
+            u2 = u2 && (w2 == lane || q2 != k2);
+        }
         bad |= (right && !(a1 < n && b1 < n)) || (below && !(a2 < n && b2 < n));
         // both unions' four walks in step, then both hooks
         uint32_t xs[4] = {a1, b1, a2, b2};
