@@ -149,15 +149,39 @@ __device__ void n_find_m(gptr<uint64_t> nodes, uint32_t n, uint32_t (&x)[M], uin
 // on with that word and the smaller one: no reload and no new walk, one round
 // trip per attempt.  The larger word falls at every attempt, so the loop ends.
 // Two hooks of one lane run in step so that their atomics overlap.
+//
+// Where all tiles of a lattice merge at the same time, the pieces of a large
+// cluster first hang under their upper neighbours, in chains as long as the
+// lattice has rows of tiles, and a hook that comes late climbs two of them one
+// attempt at a time.  With BOTH it climbs both at once: beside the atomic on the
+// larger root it reads the word of the smaller one and goes on from its parent.
+// The read may be served by a cache, so that parent may be one it has left
+// since; whoever dropped that link joins the two (as above), so it is of the
+// same cluster in the end, and a smaller word in any case.  Only from the third
+// attempt on: most hooks need no more than two, and the read makes an attempt
+// about a tenth longer (a disordered lattice's whole sweep by 0.3 to 0.8 us).
+constexpr uint32_t CLIMB_FROM = 2;
+
+template <bool BOTH>
 __device__ void n_hook2(gptr<uint64_t> nodes, uint32_t n, uint64_t (&a)[2], uint64_t (&b)[2], bool& bad)
 {
     for (uint32_t it = 0; it < UNITE_CAP; ++it) {
         bool done = true;
-        uint64_t old[2], hi[2], lo[2];
+        uint64_t old[2], hi[2], lo[2], up[2];
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             hi[m] = max(a[m], b[m]);
             lo[m] = min(a[m], b[m]);
+            up[m] = lo[m];
+        }
+        if (BOTH && it >= CLIMB_FROM) {
+            // no branch of their own: the loads and the atomics fly together
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                up[m] = __hip_atomic_load(nodes + min(node_of(lo[m]), n - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
             const bool act = hi[m] != lo[m];
             if (act && node_of(hi[m]) >= n) {
                 bad = true;
@@ -168,7 +192,7 @@ __device__ void n_hook2(gptr<uint64_t> nodes, uint32_t n, uint64_t (&a)[2], uint
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             a[m] = old[m] == hi[m] ? lo[m] : old[m];
-            b[m] = lo[m];
+            b[m] = BOTH && old[m] != hi[m] ? min(lo[m], up[m]) : lo[m];
             done &= old[m] == hi[m];
         }
         if (done) return;
@@ -869,7 +893,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
 // wave of its tile 0.  This kernel alone does not read the counter, so a
 // captured step needs no launch of its own to move on to the next sweep; the
 // kernels after it in the step see the counter already moved.
-template <int TY>
+template <int TY, bool BOTH>
 __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkItem* map, uint32_t nitems, uint32_t bump)
 {
     const uint32_t wave = wave_id(), lane = threadIdx.x & 63u;
@@ -959,7 +983,7 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
         SW_PHASE(pc, 1);   // node words, walks to the roots
         if (bad) break;
         uint64_t ha[2] = {ws[0], ws[2]}, hb[2] = {ws[1], ws[3]};
-        n_hook2(nodes, n, ha, hb, bad);
+        n_hook2<BOTH>(nodes, n, ha, hb, bad);
         SW_PHASE(pc, 2);   // hooks
     }
     if (bad) flag_error(d.err);
@@ -1540,7 +1564,6 @@ uint32_t init_grid(size_t N)
     default: return hipErrorInvalidValue;                                                                  \
     }
 #define SWMI_TILE_BLOCK(T) threads_of<T>()
-#define SWMI_FOUR_WAVES(T) 256
 #define SWMI_TY_DISPATCH(TYV, KERNEL, GRID, ...) SWMI_TY_DISPATCH_B(TYV, KERNEL, GRID, SWMI_TILE_BLOCK, __VA_ARGS__)
 
 // Waves of a tile's workgroup.  A wave walks its strip of rows one after another,
@@ -1640,7 +1663,28 @@ hipError_t launch_flip_xy(const Work& w, uint32_t k)
 hipError_t launch_merge(const Work& w, uint32_t bump)
 {
     if (w.nitems == 0) return hipSuccess;
-    SWMI_TY_DISPATCH_B(w.ty, k_merge, (w.nitems + 3) / 4, SWMI_FOUR_WAVES, w.descs, w.map, w.nitems, bump);
+    // Hooks that climb both chains at once (n_hook2) for a lattice by itself of
+    // 24 x 24 to 160 x 160 tiles: fewer tiles make short chains, more do not all
+    // run at the same time and are bound by the rate of atomics instead, as are
+    // the many lattices of mapped work.  A whole sweep, us, one chain / both, q = 2
+    // at K_c: L = 1001 27.0 / 27.0, 1700 48.7 / 41.9, 2048 56.8 / 46.1, 4096 120 / 100,
+    // 6000 234 / 188; the merge alone, 8192 77 / 48, 10000 81 / 68, 11585 87 / 94,
+    // 16384 133 / 141; 256 uneven replicas 910 / 942.
+    const bool both = !w.map && w.nitems >= 576 && w.nitems <= 25600;
+    auto go = [&](auto ty) {
+        constexpr int TY = decltype(ty)::value;
+        const dim3 grid((w.nitems + 3) / 4), block(256);
+        if (both)
+            hipLaunchKernelGGL((k_merge<TY, true>), grid, block, 0, w.stream, w.descs, w.map, w.nitems, bump);
+        else
+            hipLaunchKernelGGL((k_merge<TY, false>), grid, block, 0, w.stream, w.descs, w.map, w.nitems, bump);
+    };
+    switch (w.ty) {
+    case 32: go(std::integral_constant<int, 32>{}); break;
+    case 64: go(std::integral_constant<int, 64>{}); break;
+    case 128: go(std::integral_constant<int, 128>{}); break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

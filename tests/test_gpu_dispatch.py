@@ -229,3 +229,27 @@ def test_reads_small_and_large_from_several_threads():
         for t in threads:
             t.join()
         assert not errors, errors
+
+
+@pytest.mark.parametrize("L,q,f,tile_rows,random_start", [
+    (1472, 2, 1.0, 0, True), (1473, 2, 1.0, 0, True), (1600, 2, 1.1, 0, False), (1537, 4, 1.05, 0, True),
+    (1056, 3, 1.0, 32, True), (1088, 3, 1.0, 32, True), (2944, 2, 1.05, 128, False), (3200, 2, 1.0, 0, True)])
+def test_merges_that_climb_both_chains(L, q, f, tile_rows, random_start):
+    """Tile counts on both sides of the lower line (529 and 576, 561 and 578),
+    from random and from ordered starts."""
+    check(L, q, K=f * wl.critical_coupling(q), tile_rows=tile_rows, calls=(1, 3), random_start=random_start)
+
+
+@pytest.mark.parametrize("L", [10240, 10241])
+def test_merges_agree_across_the_upper_line(L):
+    """The same sweeps with 64-row tiles (25600 of them at L = 10240, the line)
+    and with 32-row tiles, twice as many."""
+    print(f"case L={L}", flush=True)
+    got = []
+    for ty in (64, 32):
+        lat = binding.Lattice(L, 2, wl.critical_coupling(2), seed=3, obs_capacity=16, tile_rows=ty)
+        lat.sweep(8)
+        got.append((lat.measure(0, 8), lat.spins()))
+        lat.close()
+    assert np.array_equal(got[0][0], got[1][0])
+    assert np.array_equal(got[0][1], got[1][1])
