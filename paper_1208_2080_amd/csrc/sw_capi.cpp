@@ -465,7 +465,6 @@ int enqueue_sweeps(const Work& w, uint32_t n, bool measure, const LatDesc* descs
         if (ev) HIP_TRY(hipEventRecord(ev[4 * k + 3], w.stream));
         rc = phase_flip(w, k);
         if (rc) return rc;
-        if (w.cluster) HIP_TRY(launch_cluster_sums(w, k));
         if (ev) HIP_TRY(hipEventRecord(ev[4 * k + 4], w.stream));
     }
     if (measure) {
@@ -489,7 +488,6 @@ int enqueue_step(const Work& w, uint32_t flags)
     HIP_TRY(launch_merge(w, 1));
     rc = phase_flip(w, THIS);
     if (rc) return rc;
-    if (w.cluster) HIP_TRY(launch_cluster_sums(w, THIS));
     return SW_OK;
 }
 
@@ -575,7 +573,6 @@ static int create_lattice(const Geometry& g, uint64_t seed, uint32_t random_star
         HIP_TRY(hipMemsetAsync(h->base + c.state, 0, sizeof(DevState), h->stream));
         HIP_TRY(hipMemcpyAsync(h->d_desc, &h->desc, sizeof(LatDesc), hipMemcpyHostToDevice, h->stream));
         if (g.cap) HIP_TRY(hipMemsetAsync(h->base + c.ring, 0, (size_t)ring_slots(g) * NCOPY * rec_stride(g) * 8, h->stream));
-        if (g.csum) HIP_TRY(hipMemsetAsync(h->base + c.csize, 0, (size_t)g.ntiles * nslot(g.ty) * 8, h->stream));
         if (g.xy) HIP_TRY(launch_xy_init(h->d_desc, g.N, random_start, h->stream));
         else if (random_start) HIP_TRY(launch_init(h->d_desc, 0, g.N, 1u, h->stream));
         else HIP_TRY(hipMemsetAsync(h->desc.s, 0, g.N, h->stream));
@@ -1139,7 +1136,6 @@ int batch_enqueue(sw_batch* b, const uint32_t* n_each)
         HIP_TRY(launch_bond_label(w, k, k > 0 ? 1u : 0u));
         HIP_TRY(launch_merge(w));
         HIP_TRY(launch_flip(w, k));
-        if (w.cluster) HIP_TRY(launch_cluster_sums(w, k));
     }
     if (kmax) {
         const Work w0{b->d_descs, b->d_map, prefix[0], b->ty, b->stream};
@@ -1233,9 +1229,6 @@ int sw_batch_init(const sw_params* params, uint32_t n, void* dev_ws, size_t ws_b
             if (b->g[r].cap)
                 HIP_TRY(hipMemsetAsync(base + b->c[r].ring, 0,
                                        (size_t)ring_slots(b->g[r]) * NCOPY * ring_stride(b->g[r].q) * 8, b->stream));
-            if (b->g[r].csum)
-                HIP_TRY(hipMemsetAsync(base + b->c[r].csize, 0, (size_t)b->g[r].ntiles * nslot(b->g[r].ty) * 8,
-                                       b->stream));
             if (params[r].init) HIP_TRY(launch_init(b->d_descs, r, b->g[r].N, 1u, b->stream));
             else HIP_TRY(hipMemsetAsync(b->desc[r].s, 0, b->g[r].N, b->stream));
         }
@@ -1565,7 +1558,6 @@ int sw_group_sweep(sw_group* g, sw_lattice* const* lats, const uint32_t* n_sweep
         HIP_TRY(launch_bond_label(w, k, k > 0 ? 1u : 0u));
         HIP_TRY(launch_merge(w));
         HIP_TRY(launch_flip(w, k));
-        if (w.cluster) HIP_TRY(launch_cluster_sums(w, k));
     }
     const Work w0{g->d_descs, g->d_map, ends.back(), g->ty, g->stream};
     HIP_TRY(launch_measure_each(w0, g->d_n));

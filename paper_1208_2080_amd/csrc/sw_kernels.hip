@@ -810,6 +810,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         auto assign = [&](bool won, uint32_t r, uint32_t slot) {
             if (!won) return;
             glb(d.nodes)[node0 + slot] = ((uint64_t)global_index(r) << 32) | (node0 + slot);
+            if (!PRESET && d.csize) glb(d.csize)[node0 + slot] = 0;   // for the flip to gather in
             lds_st(&P[r], NODE16 + slot);
         };
         assign(wR, rootR, base + lanes_below(mR));
@@ -991,6 +992,34 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
 }
 
 // ---------------------------------------------------------------------------
+// Cluster-size sums of a sweep's clusters, for the improved estimators of the
+// moments of the magnetisation (given the clusters, the mean of |M|^2 over the
+// clusters' independent uniform states is sum |C|^2, and that of |M|^4 a
+// combination of (sum |C|^2)^2 and sum |C|^4).  The flip takes them along: it
+// walks every site to its tile-local root anyway.  |C| <= 2^30, so |C|^2 fits
+// 64 bits and the sums of |C|^4 take 128 (two words, carried by hand).
+
+// v added to the 128-bit number (lo, hi), atomically.
+template <int SCOPE, class P>
+__device__ __forceinline__ void add_u128(P lo, P hi, unsigned __int128 v)
+{
+    const unsigned long long vl = (unsigned long long)v, vh = (unsigned long long)(v >> 64);
+    if (!vl && !vh) return;
+    const unsigned long long old = __hip_atomic_fetch_add(lo, vl, __ATOMIC_RELAXED, SCOPE);
+    const unsigned long long up = vh + ((old + vl) < old ? 1u : 0u);
+    if (up) __hip_atomic_fetch_add(hi, up, __ATOMIC_RELAXED, SCOPE);
+}
+
+// The workgroup's sums (in LDS) into ring record t, partial copy 0.
+__device__ __forceinline__ void cs_flush(const LatDesc& d, uint32_t t, const unsigned long long* sums)
+{
+    const gptr<unsigned long long> rec =
+        (gptr<unsigned long long>)(glb(d.ring) + (size_t)(t % d.cap) * NCOPY * ring_stride(d.q) + cs_word(d.q));
+    if (sums[0]) __hip_atomic_fetch_add(rec, sums[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    add_u128<__HIP_MEMORY_SCOPE_AGENT>(rec + 1, rec + 2, ((unsigned __int128)sums[2] << 64) | sums[1]);
+}
+
+// ---------------------------------------------------------------------------
 // Flip: every site takes the state drawn for the smallest site index of its
 // cluster.  Inside the tile the labels form a forest of tile-local indices
 // whose terminals are the tile-local roots.  The tile's edge-forest nodes are
@@ -1008,7 +1037,16 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
 // XY: the draw per cluster is a reflection bit instead of a state, and each
 // site of a reflected cluster has its angle reflected across the line
 // perpendicular to the sweep's direction (the others are not touched).
-template <int TY, uint32_t NW, bool XY = false>
+// CS: lattices with cluster sums also have the sites of each tile-local cluster
+// counted as they are walked (a run of equal roots along a row adds its length
+// with one LDS atomic).  A cluster inside the tile adds |C|^2 and |C|^4; a node
+// adds its count c to its root's size with one returning atomic, and of the
+// powers what it raises them by, (old + c)^2 - old^2 and (old + c)^4 - old^4:
+// over a root's nodes these add up to the powers of its final size, whatever the
+// order, so no launch after the flip has to visit the roots.  The 198 tiles of
+// 36 replicas of L = 32 ... 256, q = 2 near K_c: 10.0 us a sweep for flip and
+// sums, 24.1 with two kernels of their own after the flip (counts, then roots).
+template <int TY, uint32_t NW, bool XY = false, bool CS = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) void k_flip(
     const LatDesc* descs, const WorkItem* map, uint32_t k)
 {
@@ -1021,6 +1059,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     __shared__ uint16_t E[TY * TX];
     __shared__ uint16_t list[NW][PER * TX + 64 + 64];   // roots inside the tile, nodes, a scratch slot per lane
     __shared__ uint32_t NK[NKN];            // per node (slot + 1): its root's key, then its state
+    // CS: sites per root inside the tile (by index), then per node (slot + 1), 16
+    // bits each, two a word (a tile has at most 2^13 sites)
+    static_assert(TY * TX < 65536, "a tile's sites are counted in 16 bits");
+    __shared__ uint32_t C[CS ? (TY * TX + NKN) / 2 : 1];
+    __shared__ uint32_t NR[CS ? NKN : 1];   // CS: per node (slot), its root
+    __shared__ unsigned long long sums[3];
 
     LatDesc d;
     uint32_t tile, lat;
@@ -1049,6 +1093,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     uint32_t lane0 = 0;
     asm("" : "+v"(lane0));
     const uint32_t n_loaded = glb(d.edges)[(size_t)tile * edge_words(TY) + 6 + lane0];
+    const bool count = CS && d.csize;
+    if (count) {
+        for (uint32_t i = tid; i < (TY * TX + NKN) / 2; i += NT) C[i] = 0;
+        if (tid < 3) sums[tid] = 0;
+    }
     // XY: the sweep's direction (wave-uniform)
     const uint32_t phi = XY ? __builtin_amdgcn_readfirstlane(xy_direction(d, t)) : 0u;
 
@@ -1098,7 +1147,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         bad |= most >= NODE16 + n_used;
         SW_PHASE(pc, 1);   // roots inside the tile listed
         // this wave's nodes find their roots' keys and join the list
-        if (is_node) NK[nj + 1] = key_of(n_find_from(nodes, n_nodes, node0 + nj, nw, bad));
+        if (is_node) {
+            const uint64_t root = n_find_from(nodes, n_nodes, node0 + nj, nw, bad);
+            NK[nj + 1] = key_of(root);
+            if (CS) NR[nj] = bad ? node0 + nj : node_of(root);
+        }
+        const uint32_t n_inside = nterm;
         {
             const uint64_t m = ballot(is_node);
             if (is_node) my_list[nterm + lanes_below(m)] = (uint16_t)(NODE_ENTRY | (nj + 1));
@@ -1130,22 +1184,24 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         // `x < cur` alone continues the walk.)  The first step is taken from the
         // label still in its register: a pointer leads to its target, a root's
         // tag back to the site itself (one of two to three steps saved a row).
-        auto walk = [&](uint32_t j) -> uint32_t {
+        auto walk = [&](uint32_t j, uint32_t& at) -> uint32_t {
             uint32_t cur = min(v[j], li0 + j * NW * TX), x = E[cur];
             while (x < cur) {
                 cur = x;
                 x = E[cur];
             }
             bad |= !(x & ROOT16);
+            if (CS) at = (x & RES16) ? cur : TY * TX + (x & (NKN - 1u));   // where C counts it
             return (x & RES16) ? x : NK[x & (NKN - 1u)];
         };
+        uint32_t at;
         if constexpr (XY) {
             // one bit per row (reflect or not) keeps the loop's registers few
             uint32_t bits = 0;
 #pragma unroll
             for (uint32_t j = 0; j < PER; ++j) {
                 const uint32_t r = wave + NW * j;
-                if (vcol && (FULL || r < h)) bits |= (walk(j) & 1u) << j;
+                if (vcol && (FULL || r < h)) bits |= (walk(j, at) & 1u) << j;
             }
             SW_PHASE(pc, 5);   // walks
             // the reflected sites' angles in batches of eight: all loads of a
@@ -1167,7 +1223,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
 #pragma unroll
             for (uint32_t j = 0; j < PER; ++j) {
                 const uint32_t r = wave + NW * j;
-                if (vcol && (FULL || r < h)) v[j] = walk(j);   // (the new state)
+                at = INVALID;
+                if (vcol && (FULL || r < h)) v[j] = walk(j, at);   // (the new state)
+                if (CS && count) {
+                    const uint32_t left = (uint32_t)__shfl_up((int)at, 1);
+                    const uint64_t heads = ballot(lane == 0 || at != left);
+                    const uint64_t right = lane == 63 ? 0ull : heads >> (lane + 1);
+                    const uint32_t len = right ? (uint32_t)__builtin_ctzll(right) + 1u : 64u - lane;
+                    if (at != INVALID && lane_in(heads)) atomicAdd(&C[at >> 1], len << (16u * (at & 1u)));
+                }
             }
             SW_PHASE(pc, 5);   // walks
             gptr<uint8_t> s_p = (gptr<uint8_t>)s_tile + site0;
@@ -1177,6 +1241,51 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
                 if (vcol && (FULL || r < h)) *s_p = (uint8_t)v[j];
                 s_p += wave_step;
             }
+        }
+        if constexpr (CS) {
+            if (!count) return;
+            __syncthreads();
+            auto sites = [&](uint32_t i) { return (C[i >> 1] >> (16u * (i & 1u))) & 0xFFFFu; };
+            uint64_t s2 = 0;
+            unsigned __int128 s4 = 0;
+            for (uint32_t j = lane; j < n_inside; j += 64) {
+                const uint32_t c = sites(my_list[j] & (TY * TX - 1u));
+                const uint64_t c2 = (uint64_t)c * c;
+                s2 += c2;
+                s4 += c2 * c2;   // (at most 2^52)
+            }
+            if (wave * 64 < n_used) {
+                // the nodes again, one a thread; those of the wave's first root (by
+                // number: most often the largest cluster) go in one addition
+                const uint32_t root = tid < n_used ? NR[tid] : INVALID;
+                uint32_t c = tid < n_used ? sites(TY * TX + tid + 1) : 0u, lead = root;
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1) lead = min(lead, (uint32_t)__shfl_xor((int)lead, o));
+                const uint64_t same = ballot(root == lead);
+                const uint32_t all = wave_sum(root == lead ? c : 0u);
+                if (lane_in(same)) c = lanes_below(same) ? 0u : all;
+                if (c) {
+                    const uint64_t old = __hip_atomic_fetch_add((gptr<unsigned long long>)(glb(d.csize) + root),
+                                                                (unsigned long long)c, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT);
+                    const uint64_t now = old + c, d2 = now * now - old * old;
+                    s2 += d2;
+                    s4 += (unsigned __int128)d2 * (now * now + old * old);
+                }
+            }
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) {
+                s2 += (uint64_t)__shfl_xor((unsigned long long)s2, o);
+                const uint64_t lo = (uint64_t)__shfl_xor((unsigned long long)s4, o);
+                s4 += ((unsigned __int128)__shfl_xor((unsigned long long)(s4 >> 64), o) << 64) | lo;
+            }
+            if (lane == 0 && s2) {
+                __hip_atomic_fetch_add(&sums[0], (unsigned long long)s2, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                add_u128<__HIP_MEMORY_SCOPE_WORKGROUP>(&sums[1], &sums[2], s4);
+            }
+            __syncthreads();
+            if (tid == 0) cs_flush(d, t, sums);
         }
     };
     if (w == TX && h == TY) body(std::true_type{});
@@ -1191,159 +1300,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         gptr<int64_t> rec = glb(d.ring) + (size_t)((t + 1) % d.cap) * words;
         for (uint32_t i = tid; i < words; i += NT) rec[i] = 0;
     }
-}
-
-// ---------------------------------------------------------------------------
-// Cluster-size sums of a sweep's clusters, for the improved estimators of the
-// moments of the magnetisation (given the clusters, the mean of |M|^2 over the
-// clusters' independent uniform states is sum |C|^2, and that of |M|^4 a
-// combination of (sum |C|^2)^2 and sum |C|^4).  After the flip the labels and
-// the edge forest still describe the sweep's clusters.  k_csize: one workgroup
-// per tile counts the sites of each tile-local cluster in LDS; a cluster
-// inside the tile adds |C|^2 and |C|^4 at once, the others add their count to
-// their edge-forest root.  k_croot: every edge-forest root adds the square and
-// fourth power of its gathered size and clears it.  |C| <= 2^30, so |C|^2 fits
-// 64 bits and the sums of |C|^4 take 128 (two words, carried by hand).
-
-// v added to the 128-bit number (lo, hi), atomically.
-template <class P>
-__device__ __forceinline__ void add_u128(P lo, P hi, unsigned __int128 v, int scope)
-{
-    const uint64_t vl = (uint64_t)v, vh = (uint64_t)(v >> 64);
-    if (!vl && !vh) return;
-    uint64_t old = 0;
-    if (scope == __HIP_MEMORY_SCOPE_AGENT)
-        old = __hip_atomic_fetch_add(lo, (unsigned long long)vl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-        old = __hip_atomic_fetch_add(lo, (unsigned long long)vl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    const uint64_t up = vh + ((old + vl) < old ? 1u : 0u);
-    if (!up) return;
-    if (scope == __HIP_MEMORY_SCOPE_AGENT)
-        __hip_atomic_fetch_add(hi, (unsigned long long)up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-        __hip_atomic_fetch_add(hi, (unsigned long long)up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// The workgroup's sums (in LDS) into ring record t, partial copy 0.
-__device__ __forceinline__ void cs_flush(const LatDesc& d, uint32_t t, unsigned long long* sums, uint32_t tid)
-{
-    if (tid != 0 || !d.cap) return;
-    const gptr<unsigned long long> rec =
-        (gptr<unsigned long long>)(glb(d.ring) + (size_t)(t % d.cap) * NCOPY * ring_stride(d.q) + cs_word(d.q));
-    if (sums[0]) __hip_atomic_fetch_add(rec, sums[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    add_u128(rec + 1, rec + 2, ((unsigned __int128)sums[2] << 64) | sums[1], __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void cs_add(unsigned long long* sums, uint64_t c)
-{
-    const uint64_t c2 = c * c;
-    __hip_atomic_fetch_add(&sums[0], (unsigned long long)c2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    add_u128(&sums[1], &sums[2], (unsigned __int128)c2 * c2, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// k_csize is bound by latency (a chain of LDS reads per site): one wave takes
-// whole rows, a run of equal roots along a row adds its length at once, and the
-// sums of |C|^2 and |C|^4 over the clusters inside the tile stay in registers
-// until one reduction per wave (in 64 bits: a tile's sizes add up to at most
-// 2^13, so the fourth powers to at most 2^52).  The 198 tiles of 36 replicas of
-// L = 32 ... 256, q = 2 near K_c: 12.0 us a sweep, 32.2 with an LDS atomic per
-// site and three per cluster on the sums.
-template <int TY, uint32_t NW>
-__global__ __launch_bounds__(64 * NW) void k_csize(const LatDesc* descs, const WorkItem* map, uint32_t k)
-{
-    __shared__ uint16_t E[TY * TX];
-    __shared__ uint32_t C[TY * TX];
-    __shared__ unsigned long long sums[3];
-    LatDesc d;
-    uint32_t tile, lat;
-    if (!pick(descs, map, blockIdx.x, true, d, tile, lat)) return;
-    if (!d.csize) return;
-    const TileGeom g = tile_geom(d, tile, TY);
-    const uint32_t t = *glb(d.counter) + k;
-    const uint32_t tid = threadIdx.x, wave = wave_id(), lane = tid & 63u;
-    const uint32_t NS = nslot(TY), n_nodes = d.ntiles * NS, node0 = tile * NS;
-    const gptr<const uint16_t> lab = glb(d.tlab);
-    bool bad = false;
-    if (tid < 3) sums[tid] = 0;
-    for (uint32_t r = wave; r < g.h; r += NW) {
-        if (lane < g.w) E[r * TX + lane] = lab[(size_t)(g.y0 + r) * d.L + g.x0 + lane];
-        C[r * TX + lane] = 0;
-    }
-    __syncthreads();
-    const bool vx = lane < g.w;
-    for (uint32_t r = wave; r < g.h; r += NW) {
-        uint32_t cur = INVALID;
-        if (vx) {
-            cur = r * TX + lane;
-            uint32_t x = E[cur];
-            while (x < cur) {   // (a tagged entry is larger than every index)
-                cur = x;
-                x = E[cur];
-            }
-            bad |= !(x & ROOT16);
-        }
-        const uint32_t left = (uint32_t)__shfl_up((int)cur, 1);
-        const uint64_t heads = ballot(lane == 0 || cur != left);
-        const uint64_t right = lane == 63 ? 0ull : heads >> (lane + 1);
-        const uint32_t len = right ? (uint32_t)__builtin_ctzll(right) + 1u : 64u - lane;
-        if (vx && lane_in(heads)) atomicAdd(&C[cur], min(len, g.w - lane));
-    }
-    __syncthreads();
-    uint64_t s2 = 0, s4 = 0;
-    for (uint32_t r = wave; r < g.h; r += NW) {
-        const uint32_t li = r * TX + lane;
-        const uint32_t x = vx ? E[li] : 0u, c = C[li];
-        if (!(x & ROOT16) || !c) continue;
-        const uint32_t slot = x - NODE16;
-        if (x == ROOT16) {
-            const uint64_t c2 = (uint64_t)c * c;
-            s2 += c2;
-            s4 += c2 * c2;
-        } else {
-            const uint64_t rw = n_root(glb(d.nodes), n_nodes, node0 + slot, bad);
-            if (!bad)
-                __hip_atomic_fetch_add((gptr<unsigned long long>)(glb(d.csize) + node_of(rw)), (unsigned long long)c,
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        s2 += (uint64_t)__shfl_xor((unsigned long long)s2, o);
-        s4 += (uint64_t)__shfl_xor((unsigned long long)s4, o);
-    }
-    if (lane == 0 && s2) {
-        __hip_atomic_fetch_add(&sums[0], (unsigned long long)s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&sums[1], (unsigned long long)s4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __syncthreads();
-    cs_flush(d, t, sums, tid);
-    if (bad) flag_error(d.err);
-}
-
-template <int TY>
-__global__ __launch_bounds__(threads_of<TY>()) void k_croot(const LatDesc* descs, const WorkItem* map, uint32_t k)
-{
-    constexpr uint32_t NT = threads_of<TY>();
-    __shared__ unsigned long long sums[3];
-    LatDesc d;
-    uint32_t tile, lat;
-    if (!pick(descs, map, blockIdx.x, true, d, tile, lat)) return;
-    if (!d.csize) return;
-    const uint32_t t = *glb(d.counter) + k;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t NS = nslot(TY), node0 = tile * NS;
-    const uint32_t n_used = min(glb(d.edges)[(size_t)tile * edge_words(TY) + 6], NS);
-    if (tid < 3) sums[tid] = 0;
-    __syncthreads();
-    for (uint32_t s = tid; s < n_used; s += NT) {
-        const uint32_t node = node0 + s;
-        if (node_of(glb(d.nodes)[node]) != node) continue;   // not a root
-        const uint64_t c = glb(d.csize)[node];
-        glb(d.csize)[node] = 0;
-        if (c) cs_add(sums, c);
-    }
-    __syncthreads();
-    cs_flush(d, t, sums, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -1604,7 +1560,11 @@ hipError_t start_flip(const Work& w, uint32_t k)
 {
     auto go = [&](auto nw) {
         constexpr uint32_t NW = decltype(nw)::value;
-        hipLaunchKernelGGL((k_flip<TY, NW, XY>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k);
+        const dim3 grid(w.nitems), block(64 * NW);
+        if (!XY && w.cluster)
+            hipLaunchKernelGGL((k_flip<TY, NW, XY, !XY>), grid, block, 0, w.stream, w.descs, w.map, k);
+        else
+            hipLaunchKernelGGL((k_flip<TY, NW, XY>), grid, block, 0, w.stream, w.descs, w.map, k);
     };
     if constexpr (TY == 64) {
         if (w.nitems <= CUS) go(std::integral_constant<uint32_t, 16>{});
@@ -1685,34 +1645,6 @@ hipError_t launch_merge(const Work& w, uint32_t bump)
     case 128: go(std::integral_constant<int, 128>{}); break;
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-template <int TY>
-hipError_t start_csize(const Work& w, uint32_t k)
-{
-    auto go = [&](auto nw) {
-        constexpr uint32_t NW = decltype(nw)::value;
-        hipLaunchKernelGGL((k_csize<TY, NW>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k);
-    };
-    // sixteen waves a tile where there is at most one tile per CU
-    if (w.nitems <= CUS) go(std::integral_constant<uint32_t, 16>{});
-    else go(std::integral_constant<uint32_t, waves_of<TY>()>{});
-    return hipGetLastError();
-}
-
-hipError_t launch_cluster_sums(const Work& w, uint32_t k)
-{
-    if (w.nitems == 0) return hipSuccess;
-    hipError_t e = hipErrorInvalidValue;
-    switch (w.ty) {
-    case 32: e = start_csize<32>(w, k); break;
-    case 64: e = start_csize<64>(w, k); break;
-    case 128: e = start_csize<128>(w, k); break;
-    default: break;
-    }
-    if (e != hipSuccess) return e;
-    SWMI_TY_DISPATCH(w.ty, k_croot, w.nitems, w.descs, w.map, k);
     return hipGetLastError();
 }
 

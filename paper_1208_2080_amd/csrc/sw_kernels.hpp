@@ -25,11 +25,9 @@ hipError_t launch_bond_label(const Work& w, uint32_t k, uint32_t flags);
 // bump: sweeps the merge advances the counter of every lattice in w by (it does
 // not read it; launches after it see the counter moved)
 hipError_t launch_merge(const Work& w, uint32_t bump = 0);
+// (with the cluster-size sums of the lattices that measure them)
 hipError_t launch_flip(const Work& w, uint32_t k);
 hipError_t launch_measure(const Work& w, uint32_t k);
-// cluster-size sums of the sweep counter + k (after its flip), for the
-// lattices that measure them
-hipError_t launch_cluster_sums(const Work& w, uint32_t k);
 // measurement after n_each[lattice] sweeps of each lattice (batched form)
 hipError_t launch_measure_each(const Work& w, const uint32_t* n_each);
 hipError_t launch_init(const LatDesc* descs, uint32_t lat, size_t N, uint32_t random_start, hipStream_t s);

@@ -253,3 +253,24 @@ def test_merges_agree_across_the_upper_line(L):
         lat.close()
     assert np.array_equal(got[0][0], got[1][0])
     assert np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("L,K,tile_rows,calls", [(2112, 0.0, 64, (1, 1)), (2112, float("inf"), 64, (2,)),
+                                                 (2100, None, 0, (1, 2)), (1090, None, 32, (3,))])
+def test_cluster_sums_by_four_waves(L, K, tile_rows, calls):
+    """The flip's own cluster sums above 1024 tiles (four waves a tile): sites
+    alone, one cluster over all tiles, K_c with ragged tiles; the sums of every
+    sweep whether it is the last of a call or not."""
+    print(f"case cluster sums L={L} K={K} ty={tile_rows} calls={calls}", flush=True)
+    K = wl.critical_coupling(2) if K is None else K
+    ref = oracle.OracleLattice(L, 2, K, 11, random_start=False)
+    b = binding.Batch([dict(L=L, q=2, K=K, seed=11, random_start=False, cluster_sums=True)], obs_capacity=8,
+                      tile_rows=tile_rows)
+    want = []
+    for n in calls:
+        b.sweep_all(n)
+        for _ in range(n):
+            sizes = np.unique(ref.sweep()["labels"], return_counts=True)[1]
+            want.append([sum(int(c) ** 2 for c in sizes), sum(int(c) ** 4 for c in sizes)])
+    assert b.cluster_sums(0, 0, sum(calls)).tolist() == want
+    b.close()
