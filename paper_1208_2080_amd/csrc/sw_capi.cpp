@@ -57,7 +57,15 @@ struct Geometry {
     bool whole = false;      // swept whole in one workgroup's LDS (k_whole); ty is the bond-word layout
     uint32_t dir_bits = 0;   // XY: bits of the direction draw kept
     double K = 0.0;          // XY: the coupling
+    bool spans = false;      // the coupling is where clusters span the lattice
 };
+
+// Clusters span the lattice from the transition on: e^K - 1 >= sqrt(q) for
+// Potts (less a rounding's worth, so that K_c itself is in); for XY, whose
+// clusters are those of one direction, from a little below the
+// Kosterlitz-Thouless coupling 1.12.  The merge takes another form there.
+bool spans_potts(double K, uint32_t q) { return std::expm1(K) >= 0.999 * std::sqrt((double)q); }
+bool spans_xy(double K) { return K >= 1.04; }
 
 // Words of a ring record and of one partial copy's stride, for either model.
 inline uint32_t rec_words(const Geometry& g) { return g.xy ? XY_WORDS : ring_words(g.q); }
@@ -106,6 +114,7 @@ int check_xy_params(const sw_xy_params* p, Geometry* g)
     g->xy = true;
     g->dir_bits = p->dir_bits;
     g->K = p->K;
+    g->spans = spans_xy(p->K);
     return SW_OK;
 }
 
@@ -123,6 +132,7 @@ int check_params(const sw_params* p, Geometry* g)
         return fail(SW_EINVAL, "cluster sums need L <= 32768 and obs_capacity > 0");
     g->q = p->q;
     g->thr = threshold_of(p->K);
+    g->spans = spans_potts(p->K, p->q);
     g->csum = (p->flags & SW_CLUSTER_SUMS) != 0;
     const bool fits = p->L <= WHOLE_LMAX && !g->csum;
     if (p->tile_rows == SW_TILE_WHOLE && !fits)
@@ -622,7 +632,7 @@ int sw_sweep(sw_lattice* h, uint32_t n_sweeps)
     if (n_sweeps == 0) return SW_OK;
     if ((uint64_t)h->done + n_sweeps > 0xFFFFFFFFull) return fail(SW_ESTATE, "sweep counter would overflow");
     if (h->g.whole) return whole_sweeps(h, n_sweeps);
-    const Work w{h->d_desc, nullptr, h->g.ntiles, h->g.ty, h->stream, h->g.csum, h->g.xy};
+    const Work w{h->d_desc, nullptr, h->g.ntiles, h->g.ty, h->stream, h->g.csum, h->g.xy, h->g.spans};
     // the legacy NULL stream cannot be captured: launch directly
     const int rc = h->stream ? run_steps(h->graphs, w, n_sweeps, h->g.cap != 0)
                              : enqueue_sweeps(w, n_sweeps, h->g.cap != 0, h->d_desc, 1, nullptr);
@@ -665,7 +675,7 @@ int sw_sweep_profiled(sw_lattice* h, uint32_t n_sweeps, double* phase_ms)
             rc = fail(SW_EHIP, "hipEventCreate failed");
             break;
         }
-    const Work w{h->d_desc, nullptr, h->g.ntiles, h->g.ty, h->stream, h->g.csum, h->g.xy};
+    const Work w{h->d_desc, nullptr, h->g.ntiles, h->g.ty, h->stream, h->g.csum, h->g.xy, h->g.spans};
     if (rc == SW_OK) rc = enqueue_sweeps(w, n_sweeps, h->g.cap != 0, h->d_desc, 1, nullptr, ev.data());
     if (rc == SW_OK) {
         h->done += n_sweeps;
@@ -1689,7 +1699,7 @@ extern "C" int sw_sweep_static(const sw_params* p, uint8_t* dev_spins, uint32_t 
     const uint32_t W = 2 + g.q;
 
     HIP_TRY(launch_static_setup(d, d_desc, st, first_sweep, ring, ring_words, stream));
-    const Work w{d_desc, nullptr, g.ntiles, g.ty, stream};
+    const Work w{d_desc, nullptr, g.ntiles, g.ty, stream, false, false, g.spans};
     for (uint32_t k = 0; k < n_sweeps; ++k) {
         HIP_TRY(launch_bond_label(w, k, (measure && k > 0) ? 1u : 0u));
         // the record of sweep k - 1 is complete once the bonds of sweep k are drawn

@@ -159,7 +159,7 @@ __device__ void n_find_m(gptr<uint64_t> nodes, uint32_t n, uint32_t (&x)[M], uin
 // since; whoever dropped that link joins the two (as above), so it is of the
 // same cluster in the end, and a smaller word in any case.  Only from the third
 // attempt on: most hooks need no more than two, and the read makes an attempt
-// about a tenth longer (a disordered lattice's whole sweep by 0.3 to 0.8 us).
+// longer (a sweep of small clusters by 0.3 to 1 us: launch_merge picks).
 constexpr uint32_t CLIMB_FROM = 2;
 
 template <bool BOTH>
@@ -1624,13 +1624,18 @@ hipError_t launch_merge(const Work& w, uint32_t bump)
 {
     if (w.nitems == 0) return hipSuccess;
     // Hooks that climb both chains at once (n_hook2) for a lattice by itself of
-    // 24 x 24 to 160 x 160 tiles: fewer tiles make short chains, more do not all
-    // run at the same time and are bound by the rate of atomics instead, as are
-    // the many lattices of mapped work.  A whole sweep, us, one chain / both, q = 2
-    // at K_c: L = 1001 27.0 / 27.0, 1700 48.7 / 41.9, 2048 56.8 / 46.1, 4096 120 / 100,
-    // 6000 234 / 188; the merge alone, 8192 77 / 48, 10000 81 / 68, 11585 87 / 94,
-    // 16384 133 / 141; 256 uneven replicas 910 / 942.
-    const bool both = !w.map && w.nitems >= 576 && w.nitems <= 25600;
+    // 12 x 12 to 160 x 160 tiles, at a coupling where clusters span it: smaller
+    // clusters make short chains, fewer tiles too, and more tiles do not all run
+    // at the same time and are bound by the rate of atomics instead, as are the
+    // many lattices of mapped work.  A whole sweep, us, one chain / both:
+    //   q = 2, K_c     L = 512 27.5 / 27.3, 777 33.0 / 31.4, 1001 35.4 / 32.7,
+    //                  2048 56.4 / 46.5, 4096 121 / 101, 6000 234 / 188
+    //   q = 2, 2048    0.95 K_c 37.1 / 37.7, 0.99 40.2 / 41.4, 1.01 51.8 / 46.9
+    //   q = 8, 2048    0.99 K_c 36.3 / 36.6, 1.00 37.4 / 37.8, 1.01 52.4 / 45.2
+    //   XY, 2048       K = 1.01 60.8 / 61.9, 1.05 67.8 / 65.6, 1.12 72.2 / 65.9
+    // the merge alone, q = 2, K_c, 8192 77 / 48, 10000 81 / 68, 11585 87 / 94, 16384
+    // 133 / 141; 32 uneven jobs 292 / 300.
+    const bool both = w.spans && !w.map && w.nitems >= 144 && w.nitems <= 25600;
     auto go = [&](auto ty) {
         constexpr int TY = decltype(ty)::value;
         const dim3 grid((w.nitems + 3) / 4), block(256);

@@ -19,6 +19,7 @@ struct Work {
     hipStream_t stream;
     bool cluster = false;  // some lattice measures cluster-size sums
     bool xy = false;       // XY lattices (Wolff's embedded clusters)
+    bool spans = false;    // one lattice, at a coupling where clusters span it
 };
 
 hipError_t launch_bond_label(const Work& w, uint32_t k, uint32_t flags);

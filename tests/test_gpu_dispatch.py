@@ -274,3 +274,24 @@ def test_cluster_sums_by_four_waves(L, K, tile_rows, calls):
             want.append([sum(int(c) ** 2 for c in sizes), sum(int(c) ** 4 for c in sizes)])
     assert b.cluster_sums(0, 0, sum(calls)).tolist() == want
     b.close()
+
+
+@pytest.mark.parametrize("L,f", [(704, 1.0), (705, 1.0), (705, 0.99), (640, 1.1), (1001, 1.1)])
+def test_merges_of_spanning_clusters(L, f):
+    """Both sides of the lower line (121 and 144 tiles) and of the coupling."""
+    check(L, 3, K=f * wl.critical_coupling(3), calls=(2, 2), random_start=f <= 1.0)
+
+
+@pytest.mark.parametrize("L,K", [(705, 1.03), (705, 1.05), (1001, 2.0), (1500, float("inf"))])
+def test_merges_of_spanning_clusters_xy(L, K):
+    print(f"case XY L={L} K={K}", flush=True)
+    cold = K > 1.5
+    lat = binding.XYLattice(L, K, seed=5, random_start=not cold, obs_capacity=4)
+    ref = oracle.XYOracleLattice(L, K, 5, random_start=not cold)
+    for c in (1, 2):
+        lat.sweep(c)
+        for _ in range(c):
+            out = ref.sweep()
+        assert np.array_equal(lat.angles(), ref.a)
+        assert np.array_equal(lat.labels(), out["labels"])
+    lat.close()
