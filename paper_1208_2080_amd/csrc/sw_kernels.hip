@@ -760,8 +760,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     __syncthreads();
     SW_PHASE(pc, 5);   // bond words out, edge record, barrier
 
-    // Edge sites find their tile-local roots (lane i takes the left and right
-    // sites of strip row i; the first and last strips the top and bottom rows).
+    // Edge sites find their tile-local roots, one a thread, in the order of the
+    // edge record's slots (a tile has no more of them than threads; with the left
+    // and right sites of a strip taken by its own wave, and the top and bottom
+    // rows by the first and last, the waves walked up to four times each with
+    // mostly idle lanes: 0.658 ms a labelling against 0.626, L = 16384).
     // The first lane to reach a root claims it as a node of the tile's edge
     // forest: it takes the next slot (in no particular order: a node's word
     // carries its key), writes the node's word (a root of its own, keyed by its
@@ -783,40 +786,40 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     // A claim of root r sets the ROOT16 bit of its entry with one LDS atomic
     // OR on the entry's 32-bit word: the lane that finds the bit clear is the
     // first and wins; an entry tagged already keeps its value (a slot stored
-    // by another winner is never overwritten).  The four claims of a lane go
-    // out together, then the wave's winners take consecutive slots with one
-    // LDS atomic and make their roots' entries NODE16 + slot.
+    // by another winner is never overwritten).  Then the wave's winners take
+    // consecutive slots with one LDS atomic and make their roots' entries
+    // NODE16 + slot.
     auto claim = [&](bool want, uint32_t r) {
         if (!want) return false;
         const uint32_t sh = (r & 1u) * 16u;
         const uint32_t old = atomicOr(reinterpret_cast<uint32_t*>(P) + (r >> 1), ROOT16 << sh);
         return ((old >> sh) & 0xFFFFu) == r;
     };
-    const bool side = r0 < r1 && lane < r1 - r0;
-    const bool top = r0 == 0 && r0 < r1 && vx;
-    const bool bottom = r1 == h && r0 < r1 && vx;
-    const uint32_t rs = r0 + lane;
-    const uint32_t rootR = side ? edge_root(rs * TX + w - 1) : 0u;
-    const uint32_t rootL = side ? edge_root(rs * TX) : 0u;
-    const uint32_t rootT = top ? edge_root(x) : 0u;
-    const uint32_t rootB = bottom ? edge_root((h - 1) * TX + x) : 0u;
-    const bool wR = claim(side, rootR), wL = claim(side, rootL), wT = claim(top, rootT), wB = claim(bottom, rootB);
-    {
-        const uint64_t mR = ballot(wR), mL = ballot(wL), mT = ballot(wT), mB = ballot(wB);
-        const uint32_t nR = popc64(mR), nL = popc64(mL), nT = popc64(mT), n_won = nR + nL + nT + popc64(mB);
+    static_assert(nslot(TY) <= NT, "one thread per edge site");
+    uint32_t site = 0, root = 0;
+    bool edge = false;
+    if (wave * 64 < nslot(TY)) {
+        if (tid < 2 * TY) {
+            const uint32_t r = tid < TY ? tid : tid - TY;
+            edge = r < h;
+            site = r * TX + (tid < TY ? w - 1 : 0u);
+        } else {
+            const uint32_t c = (tid - 2 * TY) % TX;
+            edge = c < w && tid < nslot(TY);
+            site = (tid < 2 * TY + TX ? (h - 1) * TX : 0u) + c;
+        }
+        if (edge) root = edge_root(site);
+        const bool won = claim(edge, root);
+        const uint64_t m = ballot(won);
         uint32_t base = 0;
-        if (lane == 0 && n_won) base = atomicAdd(&tot[2], n_won);
+        if (lane == 0 && m) base = atomicAdd(&tot[2], popc64(m));
         base = __builtin_amdgcn_readfirstlane(base);
-        auto assign = [&](bool won, uint32_t r, uint32_t slot) {
-            if (!won) return;
-            glb(d.nodes)[node0 + slot] = ((uint64_t)global_index(r) << 32) | (node0 + slot);
+        if (won) {
+            const uint32_t slot = base + lanes_below(m);
+            glb(d.nodes)[node0 + slot] = ((uint64_t)global_index(root) << 32) | (node0 + slot);
             if (!PRESET && d.csize) glb(d.csize)[node0 + slot] = 0;   // for the flip to gather in
-            lds_st(&P[r], NODE16 + slot);
-        };
-        assign(wR, rootR, base + lanes_below(mR));
-        assign(wL, rootL, base + nR + lanes_below(mL));
-        assign(wT, rootT, base + nR + nL + lanes_below(mT));
-        assign(wB, rootB, base + nR + nL + nT + lanes_below(mB));
+            lds_st(&P[root], NODE16 + slot);
+        }
     }
     __syncthreads();
     SW_PHASE(pc, 6);   // edge roots, node claims, barrier
@@ -856,13 +859,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     }
     SW_PHASE(pc, 7);   // tile labels out
     // The edge record's slots, for the merge.
-    const gptr<uint16_t> slots = (gptr<uint16_t>)(rec + 8);
-    if (side) {
-        slots[rs] = P[rootR] - NODE16;
-        slots[TY + rs] = P[rootL] - NODE16;
-    }
-    if (top) slots[2 * TY + TX + x] = P[rootT] - NODE16;
-    if (bottom) slots[2 * TY + x] = P[rootB] - NODE16;
+    if (edge) ((gptr<uint16_t>)(rec + 8))[tid] = P[root] - NODE16;
     if (bad) flag_error(d.err);
 
     // the workgroup's sums into the ring, by wave 0 alone (the slot's modulo is
@@ -1047,7 +1044,7 @@ __device__ __forceinline__ void cs_flush(const LatDesc& d, uint32_t t, const uns
 // 36 replicas of L = 32 ... 256, q = 2 near K_c: 10.0 us a sweep for flip and
 // sums, 24.1 with two kernels of their own after the flip (counts, then roots).
 template <int TY, uint32_t NW, bool XY = false, bool CS = false>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) void k_flip(
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 : 8))) void k_flip(
     const LatDesc* descs, const WorkItem* map, uint32_t k)
 {
     constexpr uint32_t NT = 64 * NW;
