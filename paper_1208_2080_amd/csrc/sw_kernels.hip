@@ -1024,16 +1024,19 @@ __device__ __forceinline__ void cs_flush(const LatDesc& d, uint32_t t, const uns
 // search their roots (halving the paths they walk); then each wave draws, in
 // compacted lanes, the states of its nodes (keyed by their roots) and of the
 // roots of clusters inside the tile it found (keyed by their own sites).
-// Wave w owns rows w, w+4, w+8, ... (lane = column); its labels are all
+// Wave w owns rows w, w+NW, w+2NW, ... (lane = column); its labels are all
 // loaded first.  LDS entries are 16 bits (so more workgroups fit a CU): a
 // tile-local index, NODE16 + slot for a node, ROOT16 | RES16 | state for a
 // resolved root inside the tile.
-// Bound by vector issue and latency in about equal parts (L = 16384, q = 2 at
-// K_c: 0.308 ms at eight workgroups a CU; 0.324 with the first step of every
-// walk read back from LDS); the XY form by HBM (0.60 ms, 2.7 GB).
+// Bound by vector issue (662 instructions a wave; L = 16384, q = 2 at K_c: 0.306
+// ms at eight workgroups a CU; 0.324 with the first step of every walk read back
+// from LDS); the XY form by HBM (2.7 GB in 0.585 ms).
 // XY: the draw per cluster is a reflection bit instead of a state, and each
 // site of a reflected cluster has its angle reflected across the line
-// perpendicular to the sweep's direction (the others are not touched).
+// perpendicular to the sweep's direction.  A lane takes four neighbouring columns
+// of every fourth row, so that labels and angles move 8 and 16 bytes a lane
+// (0.605 ms with a column a lane; four of them without a reflected site are not
+// touched).  Potts gains nothing from that (0.308 ms against 0.306).
 // CS: lattices with cluster sums also have the sites of each tile-local cluster
 // counted as they are walked (a run of equal roots along a row adds its length
 // with one LDS atomic).  A cluster inside the tile adds |C|^2 and |C|^4; a node
@@ -1048,12 +1051,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
     const LatDesc* descs, const WorkItem* map, uint32_t k)
 {
     constexpr uint32_t NT = 64 * NW;
-    constexpr uint32_t PER = TY / NW;       // rows per wave
+    constexpr uint32_t PER = TY / NW;       // sites per lane
+    constexpr uint32_t W = XY ? 4 : 1;      // neighbouring columns per lane: W rows a step
+    constexpr uint32_t STEPS = PER / W;
+    static_assert(PER % W == 0, "whole steps");
     constexpr uint32_t RES16 = 0x4000u;     // a resolved root inside the tile
     constexpr uint32_t NKN = 512;           // node table (>= nslot(TY), a power of two)
     constexpr uint32_t NODE_ENTRY = 0x8000u;   // a list entry that names a node
     static_assert(nslot(TY) < NKN && nslot(TY) <= NT && nslot(TY) < RES16, "one thread per node");
-    __shared__ uint16_t E[TY * TX];
+    typedef uint64_t __attribute__((aligned(2))) any_u64;   // rows start at any multiple of an entry
+    typedef uint32_t __attribute__((ext_vector_type(4), aligned(4))) any_u32x4;
+    __shared__ __align__(8) uint16_t E[TY * TX];
     __shared__ uint16_t list[NW][PER * TX + 64 + 64];   // roots inside the tile, nodes, a scratch slot per lane
     __shared__ uint32_t NK[NKN];            // per node (slot + 1): its root's key, then its state
     // CS: sites per root inside the tile (by index), then per node (slot + 1), 16
@@ -1071,7 +1079,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
     const uint32_t t = *glb(d.counter) + k;
     const uint32_t tid = threadIdx.x, wave = wave_id(), lane = tid & 63u;
     const uint32_t L = d.L, w = g.w, h = g.h, x0 = g.x0, y0 = g.y0;
-    const uint32_t col = lane;
+    const uint32_t lr = lane / (TX / W), col = lane % (TX / W) * W;   // row of a step, first column
     uint16_t* my_list = list[wave];
     const uint32_t NS = nslot(TY), n_nodes = d.ntiles * NS, node0 = tile * NS;
     const gptr<uint64_t> nodes = glb(d.nodes);
@@ -1080,9 +1088,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
     // The tile's entries are addressed from one wave-uniform base with 32-bit
     // per-lane offsets (a tile spans fewer than 2^32 / 4 sites of the arrays):
     // one vector add per row, where a scalar base per row would cost the busier
-    // scalar unit two 64-bit adds.  Row j of this wave is row wave + NW j.
-    const uint32_t site0 = wave * L + col;         // this lane's first site, from the tile origin
-    const uint32_t wave_step = NW * L;             // sites between a wave's consecutive rows
+    // scalar unit two 64-bit adds.  Step i of this wave covers rows
+    // W (wave + NW i) + 0 ... W - 1.
+    const uint32_t site0 = (W * wave + lr) * L + col;   // this lane's first site, from the tile origin
+    const uint32_t wave_step = W * NW * L;              // sites between a lane's consecutive steps
     const gptr<const char> lab_tile = (gptr<const char>)(glb(d.tlab) + (size_t)y0 * L + x0);
     const gptr<char> s_tile = (gptr<char>)(glb(d.s) + (size_t)y0 * L + x0);
     // the tile's node count, by a vector load ahead of the labels': a scalar one
@@ -1101,28 +1110,44 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
     // Full tiles (the common case) need no masks for columns or rows outside.
     auto body = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
-        const bool vcol = FULL || col < w;
+        // this lane's site c of step i is inside the tile
+        auto in = [&](uint32_t i, uint32_t c) { return FULL || (W * (wave + NW * i) + lr < h && col + c < w); };
         uint32_t v[PER];
-        gptr<const uint16_t> lab_p = (gptr<const uint16_t>)lab_tile + site0;
+        if constexpr (FULL && W == 4) {
+            uint64_t q4[STEPS];
 #pragma unroll
-        for (uint32_t j = 0; j < PER; ++j) {
-            const uint32_t r = wave + NW * j;
-            v[j] = (vcol && (FULL || r < h)) ? (uint32_t)*lab_p : 0u;
-            lab_p += wave_step;
+            for (uint32_t i = 0; i < STEPS; ++i)
+                q4[i] = *reinterpret_cast<gptr<const any_u64>>(lab_tile + (site0 + i * wave_step) * 2u);
+#pragma unroll
+            for (uint32_t i = 0; i < STEPS; ++i)
+#pragma unroll
+                for (uint32_t c = 0; c < W; ++c) v[i * W + c] = (uint32_t)(q4[i] >> (16 * c)) & 0xFFFFu;
+        } else {
+            gptr<const uint16_t> lab_p = (gptr<const uint16_t>)lab_tile + site0;
+#pragma unroll
+            for (uint32_t i = 0; i < STEPS; ++i, lab_p += wave_step)
+#pragma unroll
+                for (uint32_t c = 0; c < W; ++c) v[i * W + c] = in(i, c) ? (uint32_t)lab_p[c] : 0u;
         }
         const uint32_t n_used = min(n_loaded, NS);
         const uint32_t nj = lane * NW + wave;   // this lane's node
         const bool is_node = nj < n_used;
         const uint64_t nw = is_node ? nodes[node0 + nj] : 0ull;
 
-        // row j of this wave: tile index li0 + j NW TX.  The labels go to E.  A
+        // Site c of step i: tile index li(i W + c).  The labels go to E.  A
         // pointer to a larger site is found by the walk below.
-        const uint32_t li0 = wave * TX + col;
+        const uint32_t li0 = (W * wave + lr) * TX + col;
+        auto li = [&](uint32_t j) { return li0 + (j / W) * (W * NW * TX) + j % W; };
 #pragma unroll
-        for (uint32_t j = 0; j < PER; ++j) {
-            const uint32_t r = wave + NW * j;
-            if (!FULL && r >= h) continue;
-            if (vcol) E[li0 + j * NW * TX] = (uint16_t)v[j];
+        for (uint32_t i = 0; i < STEPS; ++i) {
+            if constexpr (W == 4) {   // (entries outside the tile are not read)
+                uint64_t q4 = 0;
+#pragma unroll
+                for (uint32_t c = 0; c < W; ++c) q4 |= (uint64_t)v[i * W + c] << (16 * c);
+                *reinterpret_cast<uint64_t*>(&E[li(i * W)]) = q4;
+            } else if (in(i, 0)) {
+                E[li(i)] = (uint16_t)v[i];
+            }
         }
         SW_PHASE(pc, 0);   // labels in
         // The roots (tagged), one ballot per row: that of a cluster inside the tile
@@ -1134,11 +1159,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
         uint32_t most = 0;
 #pragma unroll
         for (uint32_t j = 0; j < PER; ++j) {
-            const uint32_t r = wave + NW * j;
-            if (!FULL && r >= h) continue;
             const uint64_t m = ballot(v[j] == ROOT16);
             most = max(most, v[j]);
-            my_list[lane_in(m) ? nterm + lanes_below(m) : PER * TX + 64 + lane] = (uint16_t)(li0 + j * NW * TX);
+            my_list[lane_in(m) ? nterm + lanes_below(m) : PER * TX + 64 + lane] = (uint16_t)li(j);
             nterm += popc64(m);
         }
         bad |= most >= NODE16 + n_used;
@@ -1182,7 +1205,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
         // label still in its register: a pointer leads to its target, a root's
         // tag back to the site itself (one of two to three steps saved a row).
         auto walk = [&](uint32_t j, uint32_t& at) -> uint32_t {
-            uint32_t cur = min(v[j], li0 + j * NW * TX), x = E[cur];
+            uint32_t cur = min(v[j], li(j)), x = E[cur];
             while (x < cur) {
                 cur = x;
                 x = E[cur];
@@ -1196,32 +1219,54 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
             // one bit per row (reflect or not) keeps the loop's registers few
             uint32_t bits = 0;
 #pragma unroll
-            for (uint32_t j = 0; j < PER; ++j) {
-                const uint32_t r = wave + NW * j;
-                if (vcol && (FULL || r < h)) bits |= (walk(j, at) & 1u) << j;
-            }
+            for (uint32_t j = 0; j < PER; ++j)
+                if (in(j / W, j % W)) bits |= (walk(j, at) & 1u) << j;
             SW_PHASE(pc, 5);   // walks
-            // the reflected sites' angles in batches of eight: all loads of a
-            // batch in flight together, then its stores
+            // the angles of the steps with a reflected site, two steps at a time:
+            // their loads in flight together, then their stores
             const gptr<char> a_tile = (gptr<char>)(glb(d.ang) + (size_t)y0 * L + x0);
-            constexpr uint32_t B = PER < 8 ? PER : 8;
+            constexpr uint32_t B = STEPS < 2 ? STEPS : 2;
 #pragma unroll 1
-            for (uint32_t j0 = 0; j0 < PER; j0 += B) {
-                uint32_t av[B];
+            for (uint32_t i0 = 0; i0 < STEPS; i0 += B) {
+                u32x4 av[B];
 #pragma unroll
-                for (uint32_t j = 0; j < B; ++j)
-                    av[j] = ((bits >> (j0 + j)) & 1u) ? *(gptr<const uint32_t>)(a_tile + (site0 + (j0 + j) * wave_step) * 4u) : 0u;
+                for (uint32_t i = 0; i < B; ++i) {
+                    const uint32_t m = (bits >> ((i0 + i) * W)) & 15u;
+                    const gptr<const uint32_t> a = (gptr<const uint32_t>)(a_tile + (site0 + (i0 + i) * wave_step) * 4u);
+                    av[i] = u32x4{0u, 0u, 0u, 0u};
+                    if (FULL ? m != 0u : m == 15u) {
+                        const any_u32x4 q = *reinterpret_cast<gptr<const any_u32x4>>(a);
+                        av[i] = u32x4{q[0], q[1], q[2], q[3]};
+                    } else if (!FULL && m) {
+                        if (m & 1u) av[i].x = a[0];
+                        if (m & 2u) av[i].y = a[1];
+                        if (m & 4u) av[i].z = a[2];
+                        if (m & 8u) av[i].w = a[3];
+                    }
+                }
 #pragma unroll
-                for (uint32_t j = 0; j < B; ++j)
-                    if ((bits >> (j0 + j)) & 1u)
-                        *(gptr<uint32_t>)(a_tile + (site0 + (j0 + j) * wave_step) * 4u) = xy_reflect(av[j], phi);
+                for (uint32_t i = 0; i < B; ++i) {
+                    const uint32_t m = (bits >> ((i0 + i) * W)) & 15u;
+                    const gptr<uint32_t> a = (gptr<uint32_t>)(a_tile + (site0 + (i0 + i) * wave_step) * 4u);
+                    if (m & 1u) av[i].x = xy_reflect(av[i].x, phi);
+                    if (m & 2u) av[i].y = xy_reflect(av[i].y, phi);
+                    if (m & 4u) av[i].z = xy_reflect(av[i].z, phi);
+                    if (m & 8u) av[i].w = xy_reflect(av[i].w, phi);
+                    if (FULL ? m != 0u : m == 15u) {
+                        *reinterpret_cast<gptr<any_u32x4>>(a) = any_u32x4{av[i].x, av[i].y, av[i].z, av[i].w};
+                    } else if (!FULL && m) {
+                        if (m & 1u) a[0] = av[i].x;
+                        if (m & 2u) a[1] = av[i].y;
+                        if (m & 4u) a[2] = av[i].z;
+                        if (m & 8u) a[3] = av[i].w;
+                    }
+                }
             }
         } else {
 #pragma unroll
             for (uint32_t j = 0; j < PER; ++j) {
-                const uint32_t r = wave + NW * j;
                 at = INVALID;
-                if (vcol && (FULL || r < h)) v[j] = walk(j, at);   // (the new state)
+                if (in(j, 0)) v[j] = walk(j, at);   // (the new state)
                 if (CS && count) {
                     const uint32_t left = (uint32_t)__shfl_up((int)at, 1);
                     const uint64_t heads = ballot(lane == 0 || at != left);
@@ -1233,11 +1278,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
             SW_PHASE(pc, 5);   // walks
             gptr<uint8_t> s_p = (gptr<uint8_t>)s_tile + site0;
 #pragma unroll
-            for (uint32_t j = 0; j < PER; ++j) {
-                const uint32_t r = wave + NW * j;
-                if (vcol && (FULL || r < h)) *s_p = (uint8_t)v[j];
-                s_p += wave_step;
-            }
+            for (uint32_t j = 0; j < PER; ++j, s_p += wave_step)
+                if (in(j, 0)) *s_p = (uint8_t)v[j];
         }
         if constexpr (CS) {
             if (!count) return;
