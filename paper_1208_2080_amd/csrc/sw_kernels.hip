@@ -412,7 +412,7 @@ __device__ __forceinline__ uint32_t row_labels(uint16_t* P, uint32_t* rl, UnionQ
     const uint32_t offer = lane_in(V) ? lp : fresh;
     if (lane_in(S | V)) lds_st(slot, offer);
     const uint32_t lab = lds_ld(slot);
-    lds_st(&P[fresh], lab);   // columns outside the tile write entries no one reads
+    lds_set(P, fresh, lab);   // columns outside the tile write entries no one reads
     // bonds x-1 and x from the same run above into the same run here add nothing
     const uint64_t R = (V & C) & ((V & hprev) << 1);
     enqueue(uq, V & ~R, lp, lab);
@@ -467,11 +467,12 @@ extern "C" int sw_phase_clocks(unsigned long long* host, int clear)
 // (2m, 2m+1) of one row; lane 2m draws for row r and lane 2m+1 for row r+1,
 // and the two lanes swap the halves the other one needs.
 //
-// What bounds it: vector issue (1580 instructions a wave of 16 rows at eight
-// waves a SIMD; 8 x 88 of them the row loop, of which Philox 37) and, where a
-// wave waits, latency (a quarter more time at six waves a SIMD than at eight).
-// L = 16384, q = 2 at K_c: 0.66 ms (0.74 with 1870 vector instructions, loads
-// staged row by row and paths split at every step of a find).
+// What bounds it: vector issue (1300 instructions a wave of 16 rows at eight
+// waves a SIMD, about four cycles each; 8 x 88 of them the row loop, of which
+// Philox 37).  L = 16384, q = 2 at K_c: 0.575 ms (0.74 with 1870 vector
+// instructions, loads staged row by row and paths split at every step of a find;
+// 0.66 with 1580, before the edge sites were taken one a thread and the forest
+// held byte offsets).
 //
 // flags bit 0: also measure the configuration the bonds are drawn on (the
 // result of the previous sweep, t - 1).
@@ -609,9 +610,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             write_rows(words, k, BX0, BY0, BX1, BY1);
 
             const uint64_t hx0 = BX0 & ~cross, hx1 = BX1 & ~cross;
-            const uint32_t fresh = r * TX + x;
+            const uint32_t fresh = 2 * (r * TX + x);
             lp = row_labels(P, rl, uq, fresh, ~0ull, hx0, vprev, hprev, lp);
-            lp = row_labels(P, rl, uq, fresh + TX, ~0ull, hx1, BY0, hx0, lp);
+            lp = row_labels(P, rl, uq, fresh + 2 * TX, ~0ull, hx1, BY0, hx0, lp);
             hprev = hx1;
             vprev = BY1;
         }
@@ -675,13 +676,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             }
 
             const uint64_t hx0 = BX0 & ~cross;
-            const uint32_t fresh = r * TX + x;
+            const uint32_t fresh = 2 * (r * TX + x);
             lp = row_labels(P, rl, uq, fresh, validm, hx0, vprev, hprev, lp);
             hprev = hx0;
             vprev = BY0;
             if (two) {
                 const uint64_t hx1 = BX1 & ~cross;
-                lp = row_labels(P, rl, uq, fresh + TX, validm, hx1, vprev, hprev, lp);
+                lp = row_labels(P, rl, uq, fresh + 2 * TX, validm, hx1, vprev, hprev, lp);
                 hprev = hx1;
                 vprev = BY1;
             }
@@ -692,7 +693,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         for (uint32_t r = r0; r < r1; ++r) {
             if (uq.n > QCAP - 64) drain(uq, P, lane, bad);
             const uint64_t hx = lane_value64(preset[0], r - r0) & ~cross;
-            lp = row_labels(P, rl, uq, r * TX + x, validm, hx, vprev, hprev, lp);
+            lp = row_labels(P, rl, uq, 2 * (r * TX + x), validm, hx, vprev, hprev, lp);
             hprev = hx;
             vprev = lane_value64(preset[1], r - r0);
         }
@@ -718,7 +719,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         const uint64_t R = V & (V << 1) & (hc << 1) & (hu << 1);
         const uint32_t up = seam[wave - 1][lane];
         // the site's entry is its label or, after path halving, an ancestor of it
-        const uint32_t first_prov = lds_ld(&P[r0 * TX + x]);
+        const uint32_t first_prov = lds_get(P, 2 * (r0 * TX + x));
         if (uq.n > QCAP - 64) drain(uq, P, lane, bad);
         enqueue(uq, V & ~R, up, first_prov);
     }
@@ -768,31 +769,32 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     // The first lane to reach a root claims it as a node of the tile's edge
     // forest: it takes the next slot (in no particular order: a node's word
     // carries its key), writes the node's word (a root of its own, keyed by its
-    // site index) and makes the root's LDS entry NODE16 + slot, which the labels
+    // site index) and makes the root's LDS entry ROOT16 + 2 (slot + 1), which halved
+    // like an offset, as a signed number, is NODE16 + slot: that the labels
     // and the edge record carry on.  Walks stop at tagged entries (all walks end
     // before the first claim).
     // a site index fits 32 bits (N <= 2^32) and y, L fit 24 bits
     auto global_index = [&](uint32_t la) { return __umul24(y0 + la / TX, L) + x0 + la % TX; };
     const uint32_t node0 = tile * nslot(TY);
-    auto edge_root = [&](uint32_t li) {
-        uint32_t p = lds_ld(&P[li]);
-        while (!(p & ROOT16) && p < li) {
-            li = p;
-            p = lds_ld(&P[li]);
+    auto edge_root = [&](uint32_t at) {
+        uint32_t p = lds_get(P, at);
+        while (!(p & ROOT16) && p < at) {
+            at = p;
+            p = lds_get(P, at);
         }
-        bad |= !(p & ROOT16) && p != li;
-        return li;
+        bad |= !(p & ROOT16) && p != at;
+        return at;
     };
     // A claim of root r sets the ROOT16 bit of its entry with one LDS atomic
     // OR on the entry's 32-bit word: the lane that finds the bit clear is the
     // first and wins; an entry tagged already keeps its value (a slot stored
     // by another winner is never overwritten).  Then the wave's winners take
     // consecutive slots with one LDS atomic and make their roots' entries
-    // NODE16 + slot.
+    // ROOT16 + 2 (slot + 1).
     auto claim = [&](bool want, uint32_t r) {
         if (!want) return false;
-        const uint32_t sh = (r & 1u) * 16u;
-        const uint32_t old = atomicOr(reinterpret_cast<uint32_t*>(P) + (r >> 1), ROOT16 << sh);
+        const uint32_t sh = (r & 2u) * 8u;
+        const uint32_t old = atomicOr(reinterpret_cast<uint32_t*>(lds_entry(P, r & ~3u)), ROOT16 << sh);
         return ((old >> sh) & 0xFFFFu) == r;
     };
     static_assert(nslot(TY) <= NT, "one thread per edge site");
@@ -808,7 +810,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
             edge = c < w && tid < nslot(TY);
             site = (tid < 2 * TY + TX ? (h - 1) * TX : 0u) + c;
         }
-        if (edge) root = edge_root(site);
+        if (edge) root = edge_root(2 * site);
         const bool won = claim(edge, root);
         const uint64_t m = ballot(won);
         uint32_t base = 0;
@@ -816,9 +818,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
         base = __builtin_amdgcn_readfirstlane(base);
         if (won) {
             const uint32_t slot = base + lanes_below(m);
-            glb(d.nodes)[node0 + slot] = ((uint64_t)global_index(root) << 32) | (node0 + slot);
+            glb(d.nodes)[node0 + slot] = ((uint64_t)global_index(root >> 1) << 32) | (node0 + slot);
             if (!PRESET && d.csize) glb(d.csize)[node0 + slot] = 0;   // for the flip to gather in
-            lds_st(&P[root], NODE16 + slot);
+            lds_set(P, root, ROOT16 + 2 * (slot + 1));
         }
     }
     __syncthreads();
@@ -828,13 +830,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     // Tile labels out (16 bits), per site: the tile-local index of its
     // union-find grandparent (a smaller site of its tile-local cluster; the
     // flip follows these pointers inside the tile), or, for a tile-local root,
-    // ROOT16 or NODE16 + its slot.  A grandparent that is a node is not
+    // ROOT16 or NODE16 + its slot (the entry halved: see above).  A grandparent that is a node is not
     // copied (its entry carries a slot, not an index): the parent is.  Tagged
     // entries are larger than every index, so two minima do it: the entry of
     // min(entry, own index) (its own entry again for a root), then the smaller
     // of the two entries; a root inside the tile ends at its own index.
     // Entries of columns outside the tile are never stored (full-width tiles,
     // the common case, need no mask at all).
+    auto halved = [](uint32_t entry) { return (uint16_t)((int16_t)entry >> 1); };
+    auto out_label = [&](uint32_t at, uint32_t p, uint32_t gp) {
+        return p == at ? (uint16_t)ROOT16 : halved(min(p, gp));
+    };
     if (w == TX && r1 - r0 == RPW) {
         // a full strip: all parent reads first, then all grandparent reads, so
         // the LDS round trips overlap; each row is stored from its own
@@ -843,23 +849,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
 #pragma unroll
         for (uint32_t k = 0; k < RPW; ++k) p[k] = P[(r0 + k) * TX + x];   // (16-bit entries)
 #pragma unroll
-        for (uint32_t k = 0; k < RPW; ++k) gp[k] = P[min(p[k], (r0 + k) * TX + x)];
+        for (uint32_t k = 0; k < RPW; ++k) gp[k] = *lds_entry(P, min(p[k], 2 * ((r0 + k) * TX + x)));
         gptr<uint16_t> out = glb(d.tlab) + (size_t)(y0 + r0) * L + x0 + x;   // this lane's site, row by row
 #pragma unroll
         for (uint32_t k = 0; k < RPW; ++k, out += L) {
-            const uint32_t li = (r0 + k) * TX + x;
-            *out = (uint16_t)(p[k] == li ? ROOT16 : min(p[k], gp[k]));
+            const uint32_t at = 2 * ((r0 + k) * TX + x);
+            *out = out_label(at, p[k], gp[k]);
         }
     } else if (vx) {
         for (uint32_t r = r0; r < r1; ++r) {
-            const uint32_t li = r * TX + x, p = P[li];
-            glb(d.tlab)[(size_t)(y0 + r) * L + x0 + x] =
-                (uint16_t)(p == li ? ROOT16 : min(p, (uint32_t)P[min(p, li)]));
+            const uint32_t at = 2 * (r * TX + x), p = P[r * TX + x];
+            glb(d.tlab)[(size_t)(y0 + r) * L + x0 + x] = out_label(at, p, *lds_entry(P, min(p, at)));
         }
     }
     SW_PHASE(pc, 7);   // tile labels out
     // The edge record's slots, for the merge.
-    if (edge) ((gptr<uint16_t>)(rec + 8))[tid] = P[root] - NODE16;
+    if (edge) ((gptr<uint16_t>)(rec + 8))[tid] = halved(*lds_entry(P, root)) - NODE16;
     if (bad) flag_error(d.err);
 
     // the workgroup's sums into the ring, by wave 0 alone (the slot's modulo is
@@ -1055,7 +1060,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
     constexpr uint32_t W = XY ? 4 : 1;      // neighbouring columns per lane: W rows a step
     constexpr uint32_t STEPS = PER / W;
     static_assert(PER % W == 0, "whole steps");
-    constexpr uint32_t RES16 = 0x4000u;     // a resolved root inside the tile
+    constexpr uint32_t RES16 = 0x2000u;     // a resolved root inside the tile
     constexpr uint32_t NKN = 512;           // node table (>= nslot(TY), a power of two)
     constexpr uint32_t NODE_ENTRY = 0x8000u;   // a list entry that names a node
     static_assert(nslot(TY) < NKN && nslot(TY) <= NT && nslot(TY) < RES16, "one thread per node");

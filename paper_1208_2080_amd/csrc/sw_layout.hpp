@@ -45,7 +45,7 @@ namespace swmi {
 constexpr uint32_t TX = 64;           // tile width: one wave, one column per lane
 constexpr uint32_t NCOPY = 64;        // partial copies of each ring record
 constexpr uint32_t ROOT16 = 0x8000u;       // tag of tile-local roots in 16-bit entries and tile labels
-constexpr uint32_t NODE16 = ROOT16 + 1u;   // plus a slot: a root with a node
+constexpr uint32_t NODE16 = ROOT16 + 0x4001u;   // plus a slot: a root with a node
 constexpr uint32_t INVALID = 0xFFFFFFFFu;
 constexpr uint32_t WHOLE_LMAX = 128;       // largest L swept whole in one workgroup's LDS
 
