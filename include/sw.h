@@ -63,7 +63,11 @@ typedef struct sw_params {
     uint32_t tile_rows;    /* labelling tile height: 32, 64 or 128; SW_TILE_WHOLE
                               (L <= 128, no cluster sums): the whole lattice in
                               one workgroup's LDS, many sweeps per launch; 0
-                              (default): SW_TILE_WHOLE where it applies, else 64 */
+                              (default): SW_TILE_WHOLE where it applies, else 64
+                              (a batch sweeps such small replicas by 64-row tiles
+                              where other replicas need those launches anyway, or
+                              where they are too many for one a compute unit;
+                              results do not depend on it) */
     uint32_t flags;        /* 0, or SW_CLUSTER_SUMS */
 } sw_params;
 
@@ -234,8 +238,7 @@ int sw_batch_destroy(sw_batch* b);
  * every draw is keyed by site and sweep), so it is a pure performance choice.
  * For each of the n_candidates (1..8) heights in candidates[] (each 32, 64,
  * 128, SW_TILE_WHOLE -- every replica swept whole in LDS, which needs
- * L <= 128 and no cluster sums -- or 0, the default rule: whole where that
- * applies, 64 elsewhere), this initialises the n replicas params[] (their own
+ * L <= 128 and no cluster sums -- or 0, the default rule of sw_params), this initialises the n replicas params[] (their own
  * tile_rows is ignored) in dev_ws, runs `sweeps` (1..4096) untimed sweeps of every replica,
  * then times `sweeps` more with HIP events on hip_stream, and writes the
  * fastest height into *tile_rows and, if ms_per_sweep is not NULL, the measured

@@ -55,6 +55,7 @@ struct Geometry {
     bool csum;   // cluster-size sums measured
     bool xy = false;         // an XY lattice (q unused)
     bool whole = false;      // swept whole in one workgroup's LDS (k_whole); ty is the bond-word layout
+    bool chosen = false;     // ... by the default rule, not because the caller asked for it
     uint32_t dir_bits = 0;   // XY: bits of the direction draw kept
     double K = 0.0;          // XY: the coupling
     bool spans = false;      // the coupling is where clusters span the lattice
@@ -137,7 +138,8 @@ int check_params(const sw_params* p, Geometry* g)
     const bool fits = p->L <= WHOLE_LMAX && !g->csum;
     if (p->tile_rows == SW_TILE_WHOLE && !fits)
         return fail(SW_EINVAL, "SW_TILE_WHOLE needs L <= %u and no cluster sums", WHOLE_LMAX);
-    g->whole = p->tile_rows == SW_TILE_WHOLE || (p->tile_rows == 0 && fits);
+    g->chosen = p->tile_rows == 0 && fits;
+    g->whole = p->tile_rows == SW_TILE_WHOLE || g->chosen;
     return SW_OK;
 }
 
@@ -626,12 +628,32 @@ static int whole_sweeps(sw_lattice* h, uint32_t n)
     return SW_OK;
 }
 
+// Whether n sweeps of a lattice that fits LDS are faster by tiles.  Whole, one CU
+// does all the work; by tiles three launches over its four tiles take as long at
+// any size.  Measured, q = 2 at K_c, us a sweep whole / by tiles, then one sweep
+// with its row read: L = 64 9.2 / 17.2, 27.8 / 49.6; L = 88 19.5 / 20.2, 43.6 / 46.7;
+// L = 96 20.1 / 20.3, 44.5 / 48.5; L = 104 22.7 / 20.7, 47.8 / 47.0; L = 128 26.9 /
+// 20.6, 54.1 / 46.4.  So the line is L = 96.  On a stream that replays captured
+// steps, capturing them takes 0.15 ms, about what GRAPH_SWEEPS of them gain; a stream that the caller
+// is capturing takes the one launch of the whole kernel.
+constexpr uint32_t WHOLE_FAST = 96;
+constexpr uint32_t GRAPH_SWEEPS = 100;
+
+static bool faster_by_tiles(const sw_lattice* h, uint32_t n)
+{
+    if (!h->g.chosen || h->g.L <= WHOLE_FAST) return false;
+    if (!h->stream) return true;
+    if (!h->graphs.first && n < GRAPH_SWEEPS) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(h->stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+}
+
 int sw_sweep(sw_lattice* h, uint32_t n_sweeps)
 {
     if (!h) return fail(SW_EINVAL, "handle is NULL");
     if (n_sweeps == 0) return SW_OK;
     if ((uint64_t)h->done + n_sweeps > 0xFFFFFFFFull) return fail(SW_ESTATE, "sweep counter would overflow");
-    if (h->g.whole) return whole_sweeps(h, n_sweeps);
+    if (h->g.whole && !faster_by_tiles(h, n_sweeps)) return whole_sweeps(h, n_sweeps);
     const Work w{h->d_desc, nullptr, h->g.ntiles, h->g.ty, h->stream, h->g.csum, h->g.xy, h->g.spans};
     // the legacy NULL stream cannot be captured: launch directly
     const int rc = h->stream ? run_steps(h->graphs, w, n_sweeps, h->g.cap != 0)
@@ -1038,23 +1060,24 @@ int batch_layout(const sw_params* params, uint32_t n, BatchLayout* out)
 
 // Whether sweeping the replicas that fit LDS whole is faster than by tiles, for
 // the same number of sweeps of every replica.  Whole, one after another on 256
-// CUs: 9.7 us a sweep per lattice and CU up to L = 64 and 28 us up to L = 128.
-// By tiles: their sites at 240 a ns, plus the 25 us that three launches over few
+// CUs: 9.4 us a sweep per lattice and CU up to L = 64 and 27.5 us up to L = 128.
+// By tiles: their sites at 240 a ns, plus the 21 us that three launches over few
 // tiles take, unless other replicas need those launches anyway.  Measured, us a
-// sweep whole / by tiles: 256 lattices of L = 64 9.8 / 25.3, 1024 37.5 / 41.5,
-// 2048 74.8 / 59.3; 256 of L = 128 27.7 / 42.4, 512 54.8 / 60.9, 1024 109 / 96;
-// 256 uneven replicas of which 81 fit LDS, 50 sweeps: 63.6 / 61.8 ms.
+// sweep whole / by tiles: 256 lattices of L = 64 9.7 / 23.4, 1024 37.4 / 39.4,
+// 2048 74.5 / 55.9; 64 of L = 128 27.2 / 24.7, 256 27.6 / 40.0, 512 54.6 / 57.4,
+// 1024 109 / 88; 256 uneven replicas of which 81 fit LDS, 50 sweeps: 63.6 / 61.8 ms
+// when the line was drawn.
 bool whole_is_faster(const BatchLayout& lay, bool others)
 {
-    double whole_us = 0.0, tiles_us = others ? 0.0 : 25.0;
+    double whole_us = 0.0, tiles_us = others ? 0.0 : 21.0;
     uint64_t n64 = 0, n128 = 0;
     for (const Geometry& g : lay.g) {
         if (!g.whole) continue;
         ++(g.L <= 64 ? n64 : n128);
         tiles_us += (double)g.N / 240e3;
     }
-    if (n64) whole_us += 9.7 * std::max(1.0, (double)n64 / 256.0);
-    if (n128) whole_us += 28.0 * std::ceil((double)n128 / 256.0);
+    if (n64) whole_us += 9.4 * std::max(1.0, (double)n64 / 256.0);
+    if (n128) whole_us += 27.5 * std::ceil((double)n128 / 256.0);
     return whole_us < tiles_us;
 }
 

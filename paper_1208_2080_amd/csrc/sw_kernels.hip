@@ -1033,9 +1033,10 @@ __device__ __forceinline__ void cs_flush(const LatDesc& d, uint32_t t, const uns
 // loaded first.  LDS entries are 16 bits (so more workgroups fit a CU): a
 // tile-local index, NODE16 + slot for a node, ROOT16 | RES16 | state for a
 // resolved root inside the tile.
-// Bound by vector issue (662 instructions a wave; L = 16384, q = 2 at K_c: 0.306
-// ms at eight workgroups a CU; 0.324 with the first step of every walk read back
-// from LDS); the XY form by HBM (2.7 GB in 0.585 ms).
+// Bound by the latency of its loads at eight workgroups a CU (L = 16384, q = 2
+// at K_c: 0.312 ms, 0.91 GB; 0.35 and 0.39 at seven and six workgroups; 14 % fewer
+// vector instructions, node words a round trip earlier or wider label loads
+// change nothing); the XY form by HBM (2.7 GB in 0.585 ms).
 // XY: the draw per cluster is a reflection bit instead of a state, and each
 // site of a reflected cluster has its angle reflected across the line
 // perpendicular to the sweep's direction.  A lane takes four neighbouring columns
@@ -1572,14 +1573,14 @@ uint32_t init_grid(size_t N)
 // seams and leave fewer workgroups per CU to cover each other's barriers.
 // Whole sweeps measured at 64-row tiles, q = 2 (us; labelling with 4 / 16 waves,
 // then flip with 4 / 8 / 16 waves):
-//   16 tiles (L = 200)     31.8 / 28.9    31.8 / 29.6 / 28.5
-//   256 tiles (L = 1001)   43.8 / 39.4    43.8 / 41.5 / 40.4
-//   529 tiles (L = 1448)   49.6 / 55.5    49.6 / 47.3 / 48.0
-//   1024 tiles (L = 2048)  59.2 / 69.2    59.2 / 57.9 / 60.2
-//   2116 tiles (L = 2900)  87.9 / 117.4   87.9 / 89.5 / 95.3
+//   16 tiles (L = 200)     27.4 / 25.1    27.4 / 25.7 / 24.8
+//   256 tiles (L = 1001)   35.4 / 32.5    35.4 / 33.7 / 32.7
+//   529 tiles (L = 1448)   38.9 / 42.9    38.9 / 37.3 / 38.4
+//   1024 tiles (L = 2048)  44.1 / 50.6    44.1 / 43.2 / 46.2
+//   2116 tiles (L = 2900)  65.2 / 84.6    65.2 / 66.7 / 72.2
 // so the lines lie at one workgroup per CU (256 tiles) and, for the flip, four.
-// (Labelling with 8 waves: 40.5, 50.0 and 60.6 us at 256, 529 and 1024 tiles,
-// between the other two or no better.)
+// (Labelling with 8 waves, when the line was drawn: between the other two at 256
+// and 529 tiles, no better than four at 1024.)
 constexpr uint32_t CUS = 256;
 
 template <int TY, bool PRESET>

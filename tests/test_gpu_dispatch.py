@@ -295,3 +295,38 @@ def test_merges_of_spanning_clusters_xy(L, K):
         assert np.array_equal(lat.angles(), ref.a)
         assert np.array_equal(lat.labels(), out["labels"])
     lat.close()
+
+
+@pytest.mark.parametrize("L", [96, 97, 117, 128])
+@pytest.mark.parametrize("null_stream", [False, True])
+def test_lattices_that_fit_lds_whole_or_by_tiles(L, null_stream):
+    """Both sides of the line for plain lattices (L = 96) and of the number of
+    sweeps from which the captured steps are made (100): calls of one lattice go
+    from the whole kernel to the tiles, and a call that the caller captures goes
+    back to one launch."""
+    q, K = 3, wl.critical_coupling(3)
+    print(f"case L={L} null_stream={null_stream}", flush=True)
+    stream = torch.cuda.default_stream() if null_stream else torch.cuda.Stream()
+    lat = binding.Lattice(L, q, K, seed=5, obs_capacity=256, stream=stream)
+    ref = oracle.OracleLattice(L, q, K, 5)
+    rows = []
+    for n in (1, 99, 100, 1, 3):
+        lat.sweep(n)
+        for _ in range(n):
+            out = ref.sweep()
+            rows.append(out["obs"])
+        assert np.array_equal(lat.spins(), ref.s), f"spins after {n}"
+        assert np.array_equal(lat.labels(), out["labels"]), f"labels after {n}"
+        bx, by = lat.bonds()
+        assert np.array_equal(bx, oracle.pack_bonds(out["bx"])) and np.array_equal(by, oracle.pack_bonds(out["by"]))
+    assert np.array_equal(lat.measure(0, 204), np.array(rows))
+    if not null_stream:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            lat.sweep(1)
+        for _ in range(3):
+            with torch.cuda.stream(stream):
+                graph.replay()
+            ref.sweep()
+            assert np.array_equal(lat.spins(), ref.s), "spins after a replay"
+    lat.close()
