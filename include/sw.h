@@ -63,11 +63,11 @@ typedef struct sw_params {
     uint32_t tile_rows;    /* labelling tile height: 32, 64 or 128; SW_TILE_WHOLE
                               (L <= 128, no cluster sums): the whole lattice in
                               one workgroup's LDS, many sweeps per launch; 0
-                              (default): SW_TILE_WHOLE where it applies, else 64
-                              (a batch sweeps such small replicas by 64-row tiles
-                              where other replicas need those launches anyway, or
-                              where they are too many for one a compute unit;
-                              results do not depend on it) */
+                              (default): whole where that applies and is faster
+                              (a plain lattice of L <= 96; in a batch up to 128,
+                              unless other replicas need the tile launches anyway
+                              or such replicas are too many for one a compute
+                              unit), else 64; results do not depend on it */
     uint32_t flags;        /* 0, or SW_CLUSTER_SUMS */
 } sw_params;
 
