@@ -217,6 +217,7 @@ LatDesc make_desc(const Geometry& g, uint64_t seed, char* base, const Carve& c)
     d.obs = g.cap ? reinterpret_cast<int64_t*>(base + c.obs) : nullptr;
     d.counter = &st->counter;
     d.err = &st->err;
+    d.labels = &st->labels;
     d.L = g.L;
     d.q = g.q;
     d.W = g.W;
@@ -265,7 +266,6 @@ struct sw_lattice {
     uint32_t done;           // sweeps done since init (index of the next sweep)
     uint32_t first_obs;      // first sweep whose observables exist
     bool have_sweep;         // labels and bonds of a sweep are in place
-    bool labels_resolved;    // the label region holds all N smallest site indices (a whole-lattice sweep)
     StepGraphs graphs;       // captured sweeps (streams other than the legacy NULL stream)
 };
 
@@ -624,7 +624,6 @@ static int whole_sweeps(sw_lattice* h, uint32_t n)
     }
     h->done += n;
     h->have_sweep = true;
-    h->labels_resolved = true;   // k_whole writes smallest site indices
     return SW_OK;
 }
 
@@ -661,7 +660,6 @@ int sw_sweep(sw_lattice* h, uint32_t n_sweeps)
     if (rc) return rc;
     h->done += n_sweeps;
     h->have_sweep = true;
-    h->labels_resolved = false;
     return SW_OK;
 }
 
@@ -702,7 +700,6 @@ int sw_sweep_profiled(sw_lattice* h, uint32_t n_sweeps, double* phase_ms)
     if (rc == SW_OK) {
         h->done += n_sweeps;
         h->have_sweep = true;
-        h->labels_resolved = false;
         if (hipEventSynchronize(ev.back()) != hipSuccess) rc = fail(SW_EHIP, "hipEventSynchronize failed");
     }
     // events of sweep k: 4k start, 4k+1 after the bond kernel, 4k+2 after the
@@ -796,14 +793,14 @@ int sw_load_spins(sw_lattice* h, const uint8_t* host_in, uint32_t sweep)
     for (size_t i = 0; i < h->g.N; ++i)
         if (host_in[i] >= h->g.q) return fail(SW_EINVAL, "spin %u at site %zu is not below q", host_in[i], i);
     HIP_TRY(hipMemcpyAsync(h->desc.s, host_in, h->g.N, hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(hipMemcpyAsync(h->desc.counter, &sweep, sizeof sweep, hipMemcpyHostToDevice, h->stream));
+    const uint32_t at[2] = {sweep, LABELS_NONE};   // DevState::counter and, after it, labels
+    HIP_TRY(hipMemcpyAsync(h->desc.counter, at, sizeof at, hipMemcpyHostToDevice, h->stream));
     if (h->g.cap)
         HIP_TRY(hipMemsetAsync(h->desc.ring, 0, (size_t)ring_slots(h->g) * NCOPY * rec_stride(h->g) * 8, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     h->done = sweep;
     h->first_obs = sweep;
     h->have_sweep = false;
-    h->labels_resolved = false;
     return SW_OK;
 }
 
@@ -812,9 +809,18 @@ int sw_read_labels(sw_lattice* h, uint32_t* host_out)
     if (!h || !host_out) return fail(SW_EINVAL, "NULL argument");
     if (!h->have_sweep) return fail(SW_ESTATE, "no sweep since init / load");
     const Geometry& g = h->g;
-    if (h->labels_resolved) {
-        HIP_TRY(hipMemcpyAsync(host_out, h->desc.lab, g.N * 4, hipMemcpyDeviceToHost, h->stream));
-        return check_device_error(h->desc, h->stream);
+    if (g.whole) {
+        // swept whole or by tiles: the sweep that ran last says
+        DevState st;
+        HIP_TRY(hipMemcpyAsync(&st, h->base + h->c.state, sizeof st, hipMemcpyDeviceToHost, h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
+        if (st.err) return converge_error();
+        if (st.labels == LABELS_NONE) return fail(SW_ESTATE, "no sweep has run since init / load");
+        if (st.labels == LABELS_SITE) {
+            HIP_TRY(hipMemcpyAsync(host_out, h->desc.lab, g.N * 4, hipMemcpyDeviceToHost, h->stream));
+            HIP_TRY(hipStreamSynchronize(h->stream));
+            return SW_OK;
+        }
     }
     // resolved in bands of at most N/2 sites, below the tile labels they read
     const uint32_t band = std::max(1u, g.L / 2);
@@ -944,14 +950,14 @@ int sw_xy_load_angles(sw_lattice* h, const uint32_t* host_in, uint32_t sweep)
     if (!h || !host_in) return fail(SW_EINVAL, "NULL argument");
     if (!h->g.xy) return fail(SW_EINVAL, "not an XY lattice");
     HIP_TRY(hipMemcpyAsync(h->desc.ang, host_in, h->g.N * 4, hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(hipMemcpyAsync(h->desc.counter, &sweep, sizeof sweep, hipMemcpyHostToDevice, h->stream));
+    const uint32_t at[2] = {sweep, LABELS_NONE};   // DevState::counter and, after it, labels
+    HIP_TRY(hipMemcpyAsync(h->desc.counter, at, sizeof at, hipMemcpyHostToDevice, h->stream));
     if (h->g.cap)
         HIP_TRY(hipMemsetAsync(h->desc.ring, 0, (size_t)ring_slots(h->g) * NCOPY * rec_stride(h->g) * 8, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     h->done = sweep;
     h->first_obs = sweep;
     h->have_sweep = false;
-    h->labels_resolved = false;
     return SW_OK;
 }
 
@@ -1599,7 +1605,6 @@ int sw_group_sweep(sw_group* g, sw_lattice* const* lats, const uint32_t* n_sweep
         if (n_sweeps[i]) {
             lats[i]->done += n_sweeps[i];
             lats[i]->have_sweep = true;
-            lats[i]->labels_resolved = false;
         }
     return SW_OK;
 }

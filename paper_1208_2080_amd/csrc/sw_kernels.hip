@@ -907,7 +907,10 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
     uint32_t tile, lat;
     if (!pick(descs, map, idx, false, d, tile, lat)) return;
     SW_PHASE_START(pc);
-    if (bump && tile == 0 && lane == 0) *glb(d.counter) += bump;
+    if (tile == 0 && lane == 0) {
+        if (bump) *glb(d.counter) += bump;
+        *glb(d.labels) = LABELS_TILE;
+    }
     const TileGeom g = tile_geom(d, tile, TY);
     const uint32_t EW = edge_words(TY), NS = nslot(TY);
     const uint32_t n = d.ntiles * NS;

@@ -34,7 +34,7 @@
 //                             own, spread the workgroups' atomics
 //   obs     int64  [slots][q + 1]  staging for reads: the NCOPY partial copies of
 //                             the records being read, summed on the device
-//   state   DevState          sweep counter and error flag
+//   state   DevState          sweep counter, error flag and the labels' form
 // TY = 32, 64 or 128.
 #pragma once
 
@@ -87,10 +87,19 @@ __host__ __device__ constexpr uint32_t ring_stride(uint32_t q) { return (ring_wo
 constexpr uint32_t XY_WORDS = 7;
 constexpr uint32_t XY_STRIDE = (XY_WORDS + 1u + 31u) & ~31u;
 
+// Forms of the label region of a lattice that may be swept whole or by tiles.
+// Kernels keep the form, not the host: a call that a stream capture records runs
+// only when its graph is replayed.
+constexpr uint32_t LABELS_NONE = 0;    // no sweep since the start or a load
+constexpr uint32_t LABELS_TILE = 1;    // tile labels (k_merge: every sweep by tiles has one)
+constexpr uint32_t LABELS_SITE = 2;    // all N smallest site indices (k_whole)
+
 struct DevState {
     uint32_t err;          // nonzero: a safety cap tripped
     uint32_t counter;      // sweeps done (plain lattice)
-    uint32_t pad[62];
+    uint32_t labels;       // what the label region holds, written by the sweep that ran last;
+                           // behind the counter: a load sets both in one copy
+    uint32_t pad[61];
 };
 
 struct LatDesc {
@@ -105,6 +114,7 @@ struct LatDesc {
     int64_t* obs;          // staging of summed ring records (reads only)
     uint32_t* counter;     // sweeps done
     uint32_t* err;         // -> DevState::err
+    uint32_t* labels;      // -> DevState::labels
     uint32_t L, q, W;
     uint32_t ntx, nty, ntiles;
     uint32_t cap;          // ring capacity in sweeps (0 = no measurement)

@@ -413,6 +413,7 @@ __global__ __launch_bounds__(WHOLE_NT) void k_whole(const LatDesc* descs, const 
         }
     }
     if (bad) flag_error(d.err);
+    if (tid == 0 && (flags & 1u)) *glb(d.labels) = LABELS_SITE;
     if (tid == 0 && !(flags & 2u)) *glb(d.counter) = t0 + n;
 }
 

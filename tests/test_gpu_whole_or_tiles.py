@@ -1,0 +1,116 @@
+"""Lattices that are swept whole by some calls and by tiles by others (the
+default height, L = 97 ... 128): what a call leaves for the next one, bit for bit
+against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1208_2080_amd import binding
+from paper_1208_2080_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+Q = 3
+K = wl.critical_coupling(Q)
+
+
+def same_labels(lat, out, when):
+    bx, by = lat.bonds()
+    assert np.array_equal(bx, oracle.pack_bonds(out["bx"])) and np.array_equal(by, oracle.pack_bonds(out["by"])), when
+    assert np.array_equal(lat.labels(), out["labels"]), when
+
+
+@pytest.mark.parametrize("L", [97, 128])
+def test_labels_follow_the_sweeps_that_ran(L):
+    """A sweep that the caller captures runs whole when its graph is replayed, not
+    when it is recorded, and the calls between go by tiles: the labels read are
+    those of the last sweep that ran, and a read does not change the next one."""
+    print(f"case L={L}", flush=True)
+    stream = torch.cuda.Stream()
+    lat = binding.Lattice(L, Q, K, seed=9, obs_capacity=512, stream=stream)
+    ref = oracle.OracleLattice(L, Q, K, 9)
+
+    def sweep(n):
+        lat.sweep(n)
+        for _ in range(n):
+            out = ref.sweep()
+        return out
+
+    def replay():
+        with torch.cuda.stream(stream):
+            graph.replay()
+        return ref.sweep()
+
+    out = sweep(150)
+    same_labels(lat, out, "before the capture")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        lat.sweep(1)
+    same_labels(lat, out, "recorded, not run")
+    same_labels(lat, replay(), "first replay")
+    same_labels(lat, replay(), "second replay")
+    out = sweep(120)
+    same_labels(lat, out, "after the replays")
+    out = replay()
+    same_labels(lat, out, "replay after a call by tiles")
+    same_labels(lat, out, "the same labels again")
+    out = sweep(1)
+    same_labels(lat, out, "one sweep")
+    assert np.array_equal(lat.spins(), ref.s)
+    lat.close()
+
+
+@pytest.mark.parametrize("tile_rows", [0, binding.SW_TILE_WHOLE])
+def test_labels_of_a_capture_that_never_ran(tile_rows):
+    """No sweep has run since the start (or a load): there are no labels."""
+    L = 40
+    stream = torch.cuda.Stream()
+    lat = binding.Lattice(L, Q, K, seed=4, obs_capacity=8, stream=stream, tile_rows=tile_rows)
+    ref = oracle.OracleLattice(L, Q, K, 4)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        lat.sweep(1)
+    with pytest.raises(binding.SwError) as e:
+        lat.labels()
+    assert e.value.code == binding.SW_ESTATE
+    with torch.cuda.stream(stream):
+        graph.replay()
+    out = ref.sweep()
+    same_labels(lat, out, "after a replay")
+    lat.load_spins(ref.s, 1)
+    with pytest.raises(binding.SwError) as e:
+        lat.labels()
+    assert e.value.code == binding.SW_ESTATE
+    lat.sweep(1)
+    same_labels(lat, ref.sweep(), "after a load")
+    lat.close()
+
+
+def test_labels_after_group_sweeps_and_replays():
+    """A group sweeps its lattices by tiles, a captured call of one of them whole."""
+    stream = torch.cuda.Stream()
+    Ls = [33, 100]
+    lats = [binding.Lattice(L, Q, K, seed=L, obs_capacity=64, stream=stream) for L in Ls]
+    refs = [oracle.OracleLattice(L, Q, K, L) for L in Ls]
+    group = binding.Group(2, sum(binding.tile_count(L, Q) for L in Ls), stream=stream)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for lat in lats:
+            lat.sweep(1)
+    for step in range(3):
+        group.sweep(lats, [2, 1])
+        for lat, ref, n in zip(lats, refs, (2, 1)):
+            for _ in range(n):
+                out = ref.sweep()
+            same_labels(lat, out, f"group, step {step}, L={lat.L}")
+        with torch.cuda.stream(stream):
+            graph.replay()
+        for lat, ref in zip(lats, refs):
+            same_labels(lat, ref.sweep(), f"replay, step {step}, L={lat.L}")
+    group.close()
+    for lat in lats:
+        lat.close()
