@@ -258,7 +258,9 @@ __global__ __launch_bounds__(WHOLE_NT) void k_whole(const LatDesc* descs, const 
         }
         {
             // (a run's first site is its node: column 0 and column 64 start runs,
-            // the node of a row's last site was kept by its lane)
+            // the node of a row's last site was kept by its lane; the rows may
+            // have left the queue full)
+            if (qn > QCAP - CH * RP) drain();
             const uint32_t row = (y0 + lane) * L;
             push(wrap, LN[wave][last_c][lane & (RP - 1)], row);
             if (CH > 1) push(join, LN[wave][0][lane & (RP - 1)], row + 64);
