@@ -26,7 +26,10 @@
  * sw_workspace_bytes(), 256-byte aligned) and the HIP stream; both must stay
  * alive until sw_destroy.  The library never allocates device memory.  A handle
  * is bound to one stream and is not thread safe.  Host buffers are ordinary
- * (pageable) host memory owned by the caller.
+ * (pageable) host memory owned by the caller.  Of pinned host memory the library
+ * makes up to two buffers of 128 KB with the first handles, for small reads, and
+ * keeps them until the process ends; the destroy calls neither wait for the
+ * device nor free anything that a stream capture would refuse.
  *
  * Errors: every int function returns SW_OK (0) or a negative SW_E* code and
  * never throws; sw_last_error() gives a message for the calling thread.

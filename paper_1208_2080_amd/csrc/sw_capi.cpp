@@ -276,9 +276,10 @@ namespace {
 // copies through the runtime's staging and two waits took longer (one sweep of
 // L = 64 with its row and spins 91 us, now 41; 256 replicas' rows 61.8 ms with
 // their 50 sweeps, now 53.7).
-// Made with the first handles (at most READ_BUFFERS), lent to one read at a
-// time, given back when the last handle is destroyed; a read that finds none
-// free, or is larger, copies.
+// Made with the first handles (one for each alive, at most READ_BUFFERS), lent to
+// one read at a time and kept until the process ends: to free one is refused
+// while any stream is captured, and ends that capture, so sw_destroy must not.  A
+// read that finds none free, or is larger, copies.
 constexpr size_t READ_BYTES = 128u << 10;
 constexpr size_t READ_BUFFERS = 2;
 
@@ -298,7 +299,18 @@ void read_pool_add_handle()
 {
     ReadPool& p = read_pool();
     std::lock_guard<std::mutex> lock(p.mu);
-    ++p.handles;
+    if (p.handles++ == 0) {
+        // (a reset of the device since the last handle took them along)
+        const auto gone = [](void* b) {
+            hipPointerAttribute_t a{};
+            if (hipPointerGetAttributes(&a, b) == hipSuccess && a.type == hipMemoryTypeHost) return false;
+            (void)hipGetLastError();
+            return true;
+        };
+        const auto end = std::remove_if(p.free.begin(), p.free.end(), gone);
+        p.made -= (size_t)(p.free.end() - end);
+        p.free.erase(end, p.free.end());
+    }
     if (p.made >= READ_BUFFERS || p.made >= p.handles) return;
     void* b = nullptr;
     if (hipHostMalloc(&b, READ_BYTES, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
@@ -318,10 +330,7 @@ void read_pool_drop_handle()
 {
     ReadPool& p = read_pool();
     std::lock_guard<std::mutex> lock(p.mu);
-    if (--p.handles) return;
-    for (void* b : p.free) (void)hipHostFree(b);
-    p.made -= p.free.size();   // (one lent at the moment stays in the pool)
-    p.free.clear();
+    --p.handles;
 }
 
 // One buffer of the pool, or none.
