@@ -907,10 +907,7 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
     uint32_t tile, lat;
     if (!pick(descs, map, idx, false, d, tile, lat)) return;
     SW_PHASE_START(pc);
-    if (tile == 0 && lane == 0) {
-        if (bump) *glb(d.counter) += bump;
-        *glb(d.labels) = LABELS_TILE;
-    }
+    if (bump && tile == 0 && lane == 0) *glb(d.counter) += bump;
     const TileGeom g = tile_geom(d, tile, TY);
     const uint32_t EW = edge_words(TY), NS = nslot(TY);
     const uint32_t n = d.ntiles * NS;
@@ -1342,6 +1339,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
     if (bad) flag_error(d.err);
     SW_PHASE_FLUSH(pc, phase_table(XY ? 4u : 2u));
 
+    if (tile == 0 && tid == 0) *glb(d.labels) = LABELS_TILE;
     // The ring record of the next sweep starts from zero.
     if (d.cap && tile == 0) {
         const uint32_t words = NCOPY * (XY ? XY_STRIDE : ring_stride(d.q));
