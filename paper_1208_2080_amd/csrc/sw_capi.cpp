@@ -236,7 +236,7 @@ LatDesc make_desc(const Geometry& g, uint64_t seed, char* base, const Carve& c)
     return d;
 }
 
-// Captured sweeps: the first sweep of a call (nothing to measure before it),
+// Sweeps as graphs: the first sweep of a call (nothing to measure before it),
 // and the next ones one and STEP_CHUNK at a time.  Any number of sweeps
 // replays these three graphs; kernels only, no copies or fills.
 constexpr uint32_t STEP_CHUNK = 16;
@@ -266,7 +266,7 @@ struct sw_lattice {
     uint32_t done;           // sweeps done since init (index of the next sweep)
     uint32_t first_obs;      // first sweep whose observables exist
     bool have_sweep;         // labels and bonds of a sweep are in place
-    StepGraphs graphs;       // captured sweeps (streams other than the legacy NULL stream)
+    StepGraphs graphs;       // sweeps as graphs (streams other than the legacy NULL stream)
 };
 
 namespace {
@@ -499,7 +499,7 @@ int enqueue_sweeps(const Work& w, uint32_t n, bool measure, const LatDesc* descs
 
 // One sweep of every lattice in w with its sweep counter moved on by the merge
 // (so the flip and the cluster sums after it are sweep counter - 1), so that a
-// captured step replays as the next sweep each time.  flags as for
+// step's graph replays as the next sweep each time.  flags as for
 // launch_bond_label (bit 0: measure the configuration the bonds are drawn on).
 int enqueue_step(const Work& w, uint32_t flags)
 {
@@ -512,29 +512,35 @@ int enqueue_step(const Work& w, uint32_t flags)
     return SW_OK;
 }
 
-int capture_steps(const Work& w, uint32_t flags, uint32_t steps, hipGraphExec_t* out)
+// A graph of so many steps, put together kernel by kernel: a capture of the
+// caller's stream would take in what another thread enqueues there meanwhile.
+int build_steps(const Work& w, uint32_t flags, uint32_t steps, hipGraphExec_t* out)
 {
-    hipGraph_t graph;
-    HIP_TRY(hipStreamBeginCapture(w.stream, hipStreamCaptureModeThreadLocal));
+    StepNodes nodes{};
+    HIP_TRY(hipGraphCreate(&nodes.graph, 0));
+    Work wn = w;
+    wn.nodes = &nodes;
     int rc = SW_OK;
-    for (uint32_t k = 0; k < steps && rc == SW_OK; ++k) rc = enqueue_step(w, flags);
-    const hipError_t ec = hipStreamEndCapture(w.stream, &graph);
+    for (uint32_t k = 0; k < steps && rc == SW_OK; ++k) rc = enqueue_step(wn, flags);
+    const hipError_t ei = rc == SW_OK ? hipGraphInstantiate(out, nodes.graph, nullptr, nullptr, 0) : hipSuccess;
+    (void)hipGraphDestroy(nodes.graph);
     if (rc != SW_OK) return rc;
-    if (ec != hipSuccess) return fail(SW_EHIP, "graph capture failed: %s", hipGetErrorString(ec));
-    const hipError_t ei = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
     if (ei != hipSuccess) return fail(SW_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(ei));
     return SW_OK;
 }
 
-// n sweeps from the captured steps (built on first use), then the
+// n sweeps from the steps' graphs (built on first use), then the
 // measurement of the last sweep (the one before the bumped counter).
 int run_steps(StepGraphs& G, const Work& w, uint32_t n, bool measure)
 {
     if (!G.first) {
-        int rc = capture_steps(w, 0u, 1, &G.first);
-        if (rc == SW_OK) rc = capture_steps(w, measure ? 1u : 0u, 1, &G.next);
-        if (rc == SW_OK) rc = capture_steps(w, measure ? 1u : 0u, STEP_CHUNK, &G.chunk);
+        // (not the place to begin a call by steps: a stream that the caller is capturing)
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(w.stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone)
+            return fail(SW_EHIP, "the stream is being captured");
+        int rc = build_steps(w, 0u, 1, &G.first);
+        if (rc == SW_OK) rc = build_steps(w, measure ? 1u : 0u, 1, &G.next);
+        if (rc == SW_OK) rc = build_steps(w, measure ? 1u : 0u, STEP_CHUNK, &G.chunk);
         if (rc) {
             G.clear();
             return rc;
@@ -641,9 +647,9 @@ static int whole_sweeps(sw_lattice* h, uint32_t n)
 // any size.  Measured, q = 2 at K_c, us a sweep whole / by tiles, then one sweep
 // with its row read: L = 64 9.2 / 17.2, 27.8 / 49.6; L = 88 19.5 / 20.2, 43.6 / 46.7;
 // L = 96 20.1 / 20.3, 44.5 / 48.5; L = 104 22.7 / 20.7, 47.8 / 47.0; L = 128 26.9 /
-// 20.6, 54.1 / 46.4.  So the line is L = 96.  On a stream that replays captured
-// steps, capturing them takes 0.15 ms, about what GRAPH_SWEEPS of them gain; a stream that the caller
-// is capturing takes the one launch of the whole kernel.
+// 20.6, 54.1 / 46.4.  So the line is L = 96.  On a stream that replays the
+// steps' graphs, building them takes 0.15 ms, about what GRAPH_SWEEPS of them gain;
+// a stream that the caller is capturing takes the one launch of the whole kernel.
 constexpr uint32_t WHOLE_FAST = 96;
 constexpr uint32_t GRAPH_SWEEPS = 100;
 
@@ -663,7 +669,7 @@ int sw_sweep(sw_lattice* h, uint32_t n_sweeps)
     if ((uint64_t)h->done + n_sweeps > 0xFFFFFFFFull) return fail(SW_ESTATE, "sweep counter would overflow");
     if (h->g.whole && !faster_by_tiles(h, n_sweeps)) return whole_sweeps(h, n_sweeps);
     const Work w{h->d_desc, nullptr, h->g.ntiles, h->g.ty, h->stream, h->g.csum, h->g.xy, h->g.spans};
-    // the legacy NULL stream cannot be captured: launch directly
+    // (on the legacy NULL stream the kernels are launched directly)
     const int rc = h->stream ? run_steps(h->graphs, w, n_sweeps, h->g.cap != 0)
                              : enqueue_sweeps(w, n_sweeps, h->g.cap != 0, h->d_desc, 1, nullptr);
     if (rc) return rc;
@@ -1012,7 +1018,7 @@ struct sw_batch {
     std::vector<WorkItem> h_map;    // host copy of the last uploaded map
     std::vector<uint32_t> h_n, h_nw;
     std::vector<uint32_t> map_order;  // replica order of the uploaded map
-    StepGraphs steps;                            // captured sweeps of every replica (sweep_all)
+    StepGraphs steps;                            // sweeps of every replica as graphs (sweep_all)
     bool csum = false;                           // some replica measures cluster-size sums
     // replicas that may be swept whole (k_whole): device list, L <= 64 first, then
     // the rest, and a call's sweep counts of those it sweeps so
@@ -1314,7 +1320,7 @@ int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps)
             return fail(SW_ESTATE, "replica %u: sweep counter would overflow", r);
     std::vector<uint32_t> all(b->n, n_sweeps);
     if (b->stream == nullptr) {
-        // the legacy default stream cannot be captured: launch directly
+        // the legacy default stream: launched directly
         const int rc = batch_enqueue(b, all.data());
         if (rc) return rc;
         for (uint32_t r = 0; r < b->n; ++r) b->done[r] += n_sweeps;
@@ -1334,7 +1340,7 @@ int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps)
             return SW_OK;
         }
     }
-    // the captured steps bake in the work map of every replica swept by
+    // the steps' graphs bake in the work map of every replica swept by
     // tiles; make sure it is the one uploaded
     std::vector<uint32_t> order;
     std::vector<char> by_tiles(b->n);
@@ -1441,7 +1447,7 @@ int sw_batch_autotune(const sw_params* params, uint32_t n, const uint32_t* candi
         sw_batch* b = nullptr;
         rc = sw_batch_init(p.data(), n, dev_ws, ws_bytes, hip_stream, &b);
         if (rc) break;
-        // one untimed pass (graph capture, caches), then the timed one
+        // one untimed pass (graphs built, caches), then the timed one
         rc = sw_batch_sweep_all(b, sweeps);
         if (rc == SW_OK && hipEventRecord(ev[0], b->stream) != hipSuccess) rc = fail(SW_EHIP, "hipEventRecord failed");
         if (rc == SW_OK) rc = sw_batch_sweep_all(b, sweeps);

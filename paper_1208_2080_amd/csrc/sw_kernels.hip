@@ -894,7 +894,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
 //
 // bump: sweeps to advance each lattice's counter by (0: leave it), done by the
 // wave of its tile 0.  This kernel alone does not read the counter, so a
-// captured step needs no launch of its own to move on to the next sweep; the
+// step's graph needs no launch of its own to move on to the next sweep; the
 // kernels after it in the step see the counter already moved.
 template <int TY, bool BOTH>
 __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkItem* map, uint32_t nitems, uint32_t bump)
@@ -1589,16 +1589,14 @@ hipError_t start_bond_label(const Work& w, uint32_t k, uint32_t flags)
 {
     auto go = [&](auto nw) {
         constexpr uint32_t NW = decltype(nw)::value;
-        hipLaunchKernelGGL((k_bond_label<TY, NW, PRESET>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k,
-                           flags);
+        return start_kernel(w, k_bond_label<TY, NW, PRESET>, dim3(w.nitems), dim3(64 * NW), w.descs, w.map, k, flags);
     };
     if constexpr (TY == 64) {
-        if (w.nitems <= CUS) go(std::integral_constant<uint32_t, 16>{});
-        else go(std::integral_constant<uint32_t, 4>{});
+        if (w.nitems <= CUS) return go(std::integral_constant<uint32_t, 16>{});
+        return go(std::integral_constant<uint32_t, 4>{});
     } else {
-        go(std::integral_constant<uint32_t, waves_of<TY>()>{});
+        return go(std::integral_constant<uint32_t, waves_of<TY>()>{});
     }
-    return hipGetLastError();
 }
 
 template <int TY, bool XY>
@@ -1608,18 +1606,16 @@ hipError_t start_flip(const Work& w, uint32_t k)
         constexpr uint32_t NW = decltype(nw)::value;
         const dim3 grid(w.nitems), block(64 * NW);
         if (!XY && w.cluster)
-            hipLaunchKernelGGL((k_flip<TY, NW, XY, !XY>), grid, block, 0, w.stream, w.descs, w.map, k);
-        else
-            hipLaunchKernelGGL((k_flip<TY, NW, XY>), grid, block, 0, w.stream, w.descs, w.map, k);
+            return start_kernel(w, k_flip<TY, NW, XY, !XY>, grid, block, w.descs, w.map, k);
+        return start_kernel(w, k_flip<TY, NW, XY>, grid, block, w.descs, w.map, k);
     };
     if constexpr (TY == 64) {
-        if (w.nitems <= CUS) go(std::integral_constant<uint32_t, 16>{});
-        else if (w.nitems <= 4 * CUS) go(std::integral_constant<uint32_t, 8>{});
-        else go(std::integral_constant<uint32_t, 4>{});
+        if (w.nitems <= CUS) return go(std::integral_constant<uint32_t, 16>{});
+        if (w.nitems <= 4 * CUS) return go(std::integral_constant<uint32_t, 8>{});
+        return go(std::integral_constant<uint32_t, 4>{});
     } else {
-        go(std::integral_constant<uint32_t, waves_of<TY>()>{});
+        return go(std::integral_constant<uint32_t, waves_of<TY>()>{});
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_bond_label(const Work& w, uint32_t k, uint32_t flags)
@@ -1685,18 +1681,15 @@ hipError_t launch_merge(const Work& w, uint32_t bump)
     auto go = [&](auto ty) {
         constexpr int TY = decltype(ty)::value;
         const dim3 grid((w.nitems + 3) / 4), block(256);
-        if (both)
-            hipLaunchKernelGGL((k_merge<TY, true>), grid, block, 0, w.stream, w.descs, w.map, w.nitems, bump);
-        else
-            hipLaunchKernelGGL((k_merge<TY, false>), grid, block, 0, w.stream, w.descs, w.map, w.nitems, bump);
+        return both ? start_kernel(w, k_merge<TY, true>, grid, block, w.descs, w.map, w.nitems, bump)
+                    : start_kernel(w, k_merge<TY, false>, grid, block, w.descs, w.map, w.nitems, bump);
     };
     switch (w.ty) {
-    case 32: go(std::integral_constant<int, 32>{}); break;
-    case 64: go(std::integral_constant<int, 64>{}); break;
-    case 128: go(std::integral_constant<int, 128>{}); break;
+    case 32: return go(std::integral_constant<int, 32>{});
+    case 64: return go(std::integral_constant<int, 64>{});
+    case 128: return go(std::integral_constant<int, 128>{});
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_measure(const Work& w, uint32_t k)

@@ -5,9 +5,17 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <tuple>
+
 #include "sw_layout.hpp"
 
 namespace swmi {
+
+// The kernels of a step as the nodes of a graph, each after the one before.
+struct StepNodes {
+    hipGraph_t graph;
+    hipGraphNode_t last = nullptr;
+};
 
 // What one sweep phase runs over: the tiles of descs[0] when map is null
 // (nitems = its tile count), else the work items of map (batched form).
@@ -20,7 +28,34 @@ struct Work {
     bool cluster = false;  // some lattice measures cluster-size sums
     bool xy = false;       // XY lattices (Wolff's embedded clusters)
     bool spans = false;    // one lattice, at a coupling where clusters span it
+    StepNodes* nodes = nullptr;   // the sweep phases' launchers add nodes here instead of launching
 };
+
+// A kernel of a sweep phase, launched on w.stream or added to w.nodes.
+template <class... P, class... A>
+hipError_t start_kernel(const Work& w, void (*kernel)(P...), dim3 grid, dim3 block, A... args)
+{
+    if (!w.nodes) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, w.stream, static_cast<P>(args)...);
+        return hipGetLastError();
+    }
+    std::tuple<P...> held{static_cast<P>(args)...};
+    hipGraphNode_t node;
+    const hipError_t e = std::apply(
+        [&](P&... p) {
+            void* params[] = {&p...};
+            hipKernelNodeParams k{};
+            k.func = reinterpret_cast<void*>(kernel);
+            k.gridDim = grid;
+            k.blockDim = block;
+            k.kernelParams = params;   // (copied into the node)
+            return hipGraphAddKernelNode(&node, w.nodes->graph, w.nodes->last ? &w.nodes->last : nullptr,
+                                         w.nodes->last ? 1 : 0, &k);
+        },
+        held);
+    if (e == hipSuccess) w.nodes->last = node;
+    return e;
+}
 
 hipError_t launch_bond_label(const Work& w, uint32_t k, uint32_t flags);
 // bump: sweeps the merge advances the counter of every lattice in w by (it does

@@ -316,15 +316,14 @@ static hipError_t start_xy_bonds(const Work& w, uint32_t k, uint32_t flags)
 {
     auto go = [&](auto nw) {
         constexpr uint32_t NW = decltype(nw)::value;
-        hipLaunchKernelGGL((k_xy_bonds<TY, NW>), dim3(w.nitems), dim3(64 * NW), 0, w.stream, w.descs, w.map, k, flags);
+        return start_kernel(w, k_xy_bonds<TY, NW>, dim3(w.nitems), dim3(64 * NW), w.descs, w.map, k, flags);
     };
     if constexpr (TY == 64) {
-        if (w.nitems <= XY_FEW_TILES) go(std::integral_constant<uint32_t, 8>{});
-        else go(std::integral_constant<uint32_t, 4>{});
+        if (w.nitems <= XY_FEW_TILES) return go(std::integral_constant<uint32_t, 8>{});
+        return go(std::integral_constant<uint32_t, 4>{});
     } else {
-        go(std::integral_constant<uint32_t, waves_of<TY>()>{});
+        return go(std::integral_constant<uint32_t, waves_of<TY>()>{});
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_xy_bonds(const Work& w, uint32_t k, uint32_t flags)

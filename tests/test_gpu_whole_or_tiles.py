@@ -114,3 +114,59 @@ def test_labels_after_group_sweeps_and_replays():
     group.close()
     for lat in lats:
         lat.close()
+
+
+@pytest.mark.parametrize("L", [64, 97, 128, 200])
+def test_two_threads_on_one_stream(L):
+    """Two threads with a lattice each sweep on one stream in calls of many
+    sweeps: no call takes up what the other thread enqueues meanwhile."""
+    import threading
+
+    stream = torch.cuda.Stream()
+    lats = [binding.Lattice(L, Q, K, seed=s, obs_capacity=8, stream=stream) for s in (1, 2)]
+    errors = []
+    start = threading.Barrier(2)
+
+    def use(lat):
+        try:
+            start.wait(60)
+            for n in (120, 3, 150, 101, 1):
+                lat.sweep(n)
+        except BaseException as e:   # reported by the test's thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=use, args=(lat,)) for lat in lats]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for lat, seed in zip(lats, (1, 2)):
+        ref = oracle.OracleLattice(L, Q, K, seed)
+        rows = ref.run(375)
+        assert np.array_equal(lat.measure(370, 5), rows[370:]), seed
+        assert np.array_equal(lat.spins(), ref.s), seed
+        lat.close()
+
+
+def test_sweeps_while_another_stream_is_captured():
+    """A call on one stream, of any number of sweeps, while this thread captures
+    another in the strictest mode."""
+    for L in (64, 117, 200):
+        stream = torch.cuda.Stream()
+        lat = binding.Lattice(L, Q, K, seed=3, obs_capacity=8, stream=stream)
+        x = torch.zeros(64, device="cuda")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream(), capture_error_mode="global"):
+            x += 1
+            lat.sweep(150)
+            x += 1
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(x[0]) == 2.0
+        ref = oracle.OracleLattice(L, Q, K, 3)
+        rows = ref.run(150)
+        assert np.array_equal(lat.measure(143, 7), rows[143:])
+        assert np.array_equal(lat.spins(), ref.s)
+        lat.close()
