@@ -685,7 +685,7 @@ int sw_sweep_profiled(sw_lattice* h, uint32_t n_sweeps, double* phase_ms)
     if (n_sweeps == 0) return SW_OK;
     if ((uint64_t)h->done + n_sweeps > 0xFFFFFFFFull) return fail(SW_ESTATE, "sweep counter would overflow");
     if (n_sweeps > (1u << 20)) return fail(SW_EINVAL, "profile at most 2^20 sweeps per call");
-    if (h->g.whole) {
+    if (h->g.whole && !faster_by_tiles(h, n_sweeps)) {   // (as sw_sweep)
         // one kernel does every phase: its time is the bond-and-label phase
         hipEvent_t e[2] = {nullptr, nullptr};
         for (auto& x : e) HIP_TRY(hipEventCreate(&x));

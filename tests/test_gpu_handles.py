@@ -56,3 +56,25 @@ def test_destroy_while_another_stream_is_captured():
     again.sweep(2)
     assert np.array_equal(again.measure(0, 2), rows)
     again.close()
+
+
+def test_sweep_by_steps_on_a_stream_under_capture_is_refused():
+    """The call fails before it has touched the stream, so the capture goes on."""
+    stream = torch.cuda.Stream()
+    lat = binding.Lattice(200, 2, K2, seed=2, obs_capacity=4, stream=stream)
+    x = torch.zeros(64, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        x += 1
+        with pytest.raises(binding.SwError) as e:
+            lat.sweep(1)
+        x += 1
+    assert e.value.code == binding.SW_EHIP and lat.sweeps_done == 0
+    for _ in range(2):
+        graph.replay()
+    lat.sweep(3)
+    torch.cuda.synchronize()
+    assert float(x[0]) == 4.0
+    assert np.array_equal(lat.measure(0, 3), oracle.OracleLattice(200, 2, K2, 2).run(3))
+    lat.close()

@@ -170,3 +170,22 @@ def test_sweeps_while_another_stream_is_captured():
         assert np.array_equal(lat.measure(143, 7), rows[143:])
         assert np.array_equal(lat.spins(), ref.s)
         lat.close()
+
+
+@pytest.mark.parametrize("L,n,null_stream,by_tiles", [
+    (96, 120, False, False), (97, 99, False, False), (97, 100, False, True), (128, 150, False, True),
+    (128, 5, False, False), (96, 3, True, False), (97, 3, True, True), (128, 1, True, True)])
+def test_profiled_sweeps_take_the_way_of_plain_ones(L, n, null_stream, by_tiles):
+    """By tiles every phase has its time; whole, one kernel has it all."""
+    stream = torch.cuda.default_stream() if null_stream else torch.cuda.Stream()
+    lat = binding.Lattice(L, Q, K, seed=6, obs_capacity=8, stream=stream)
+    ms = lat.sweep_profiled(n)
+    assert 0 < ms[4] <= ms[0]
+    assert (ms[1:4] > 0).all() if by_tiles else (ms[1:4] == 0).all(), ms
+    ref = oracle.OracleLattice(L, Q, K, 6)
+    for _ in range(n):
+        out = ref.sweep()
+    assert np.array_equal(lat.spins(), ref.s)
+    same_labels(lat, out, "profiled")
+    assert np.array_equal(lat.measure(n - 1, 1)[0], out["obs"])
+    lat.close()
