@@ -827,6 +827,19 @@ int sw_read_labels(sw_lattice* h, uint32_t* host_out)
     if (g.whole) {
         // swept whole or by tiles: the sweep that ran last says
         DevState st;
+        const size_t bytes = g.N * 4, said = offsetof(DevState, labels) + 4;
+        ReadBuffer pin(bytes + said + 4);
+        if (pin.get()) {
+            uint32_t* const to = static_cast<uint32_t*>(pin.get());
+            HIP_TRY(launch_resolve(h->d_desc, 0, g.ntiles, g.ty, 0, g.L, to, h->stream));
+            HIP_TRY(launch_read_out(h->base + h->c.state, said, to + g.N, h->desc.err, h->stream));
+            HIP_TRY(hipStreamSynchronize(h->stream));
+            std::memcpy(&st, to + g.N, said);
+            if (st.err) return converge_error();
+            if (st.labels == LABELS_NONE) return fail(SW_ESTATE, "no sweep has run since init / load");
+            std::memcpy(host_out, to, bytes);
+            return SW_OK;
+        }
         HIP_TRY(hipMemcpyAsync(&st, h->base + h->c.state, sizeof st, hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         if (st.err) return converge_error();
@@ -841,7 +854,7 @@ int sw_read_labels(sw_lattice* h, uint32_t* host_out)
     const uint32_t band = std::max(1u, g.L / 2);
     for (uint32_t ya = 0; ya < g.L; ya += band) {
         const uint32_t yb = std::min(g.L, ya + band);
-        HIP_TRY(launch_resolve(h->d_desc, 0, g.ntiles, g.ty, ya, yb, h->stream));
+        HIP_TRY(launch_resolve(h->d_desc, 0, g.ntiles, g.ty, ya, yb, nullptr, h->stream));
         HIP_TRY(hipMemcpyAsync(host_out + (size_t)ya * g.L, h->desc.lab, (size_t)(yb - ya) * g.L * 4,
                                hipMemcpyDeviceToHost, h->stream));
     }

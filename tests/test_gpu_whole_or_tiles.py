@@ -189,3 +189,38 @@ def test_profiled_sweeps_take_the_way_of_plain_ones(L, n, null_stream, by_tiles)
     same_labels(lat, out, "profiled")
     assert np.array_equal(lat.measure(n - 1, 1)[0], out["obs"])
     lat.close()
+
+
+@pytest.mark.parametrize("L,tile_rows", [(2, 0), (3, 0), (63, 0), (96, 0), (97, 0), (128, 0), (65, binding.SW_TILE_WHOLE)])
+def test_labels_read_with_and_without_a_pinned_buffer(L, tile_rows):
+    """Labels left by the whole kernel and by tiles, by more readers at once than
+    there are buffers."""
+    import threading
+
+    stream = torch.cuda.Stream()
+    group = binding.Group(6, 6 * binding.tile_count(L, Q), stream=stream)
+    lats = [binding.Lattice(L, Q, K, seed=s, obs_capacity=8, stream=stream, tile_rows=tile_rows) for s in range(6)]
+    refs = [oracle.OracleLattice(L, Q, K, s) for s in range(6)]
+    for n in (1, 120):
+        for lat in lats:
+            lat.sweep(n)
+        outs = []
+        for ref in refs:
+            for _ in range(n):
+                out = ref.sweep()
+            outs.append(out["labels"])
+        if n == 120:
+            group.sweep(lats[:3], [1] * 3)
+            outs[:3] = [ref.sweep()["labels"] for ref in refs[:3]]
+        got = {}
+        threads = [threading.Thread(target=lambda i=i: got.update({i: [lats[i].labels() for _ in range(4)]}))
+                   for i in range(6)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for i in range(6):
+            assert all(np.array_equal(g, outs[i]) for g in got[i]), (n, i)
+    group.close()
+    for lat in lats:
+        lat.close()
