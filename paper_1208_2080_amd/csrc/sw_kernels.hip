@@ -1593,7 +1593,6 @@ uint32_t init_grid(size_t N)
 // so the lines lie at one workgroup per CU (256 tiles) and, for the flip, four.
 // (Labelling with 8 waves, when the line was drawn: between the other two at 256
 // and 529 tiles, no better than four at 1024.)
-constexpr uint32_t CUS = 256;
 
 template <int TY, bool PRESET>
 hipError_t start_bond_label(const Work& w, uint32_t k, uint32_t flags)

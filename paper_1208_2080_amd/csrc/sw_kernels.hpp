@@ -11,6 +11,8 @@
 
 namespace swmi {
 
+constexpr uint32_t CUS = 256;   // compute units of the device
+
 // The kernels of a step as the nodes of a graph, each after the one before.
 struct StepNodes {
     hipGraph_t graph;

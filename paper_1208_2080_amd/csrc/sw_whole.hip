@@ -9,12 +9,13 @@
 //
 // What bounds it is one CU: about 400 SIMD cycles of vector, scalar and LDS
 // instructions per 64 sites in the row step below, and in the other steps
-// chains of dependent LDS accesses.  (L = 64, q = 2 at K_c: 9.6 us a sweep, of
+// chains of dependent LDS accesses.  (L = 64, q = 2 at K_c: 9.2 us a sweep, of
 // which the rows take a quarter, the seams a fifth; 25.2 us for the kernel
 // before, which walked every site to its root through the rows' chains and
-// had seven barriers.  L = 128: 27.7 us, before 54.9.)  So the work is cut to keep chains short: sixteen
-// waves own a strip of whole rows each (one column per lane, 64 columns at a
-// time), everything a strip needs is loaded first, and a sweep has four
+// had seven barriers.  L = 128: 26.9 us, before 54.9.)  So the work is cut to keep
+// chains short: sixteen waves (fewer where there are more lattices than CUs:
+// launch_whole) own a strip of whole rows each (one column per lane, 64 columns at
+// a time), everything a strip needs is loaded first, and a sweep has four
 // barriers:
 //   1. bonds and runs: the bonds of a row are wave ballots of its spins and
 //      draws; the runs of +x bonds of a row are bit arithmetic on them (no LDS),
@@ -47,8 +48,6 @@ namespace swmi {
 
 namespace {
 
-constexpr uint32_t WHOLE_NT = 1024;               // sixteen waves
-constexpr uint32_t WHOLE_NW = WHOLE_NT / 64;
 constexpr uint32_t TAG = 0x8000u;                 // a root's entry once it holds its state
 
 // A value that is the same in every lane, as a scalar.
@@ -63,22 +62,23 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
 // and bond words of the last sweep; bit 1: leave the sweep counter (the caller
 // advances it), else set it past the last sweep.  ty: tile height of the
 // lattice's bond-word layout.
-template <int LMAX>
-__global__ __launch_bounds__(WHOLE_NT) void k_whole(const LatDesc* descs, const uint32_t* list, uint32_t k0,
+template <int LMAX, uint32_t NW>
+__global__ __launch_bounds__(64 * NW) void k_whole(const LatDesc* descs, const uint32_t* list, uint32_t k0,
                                                     uint32_t n_uniform, const uint32_t* n_each, uint32_t flags,
                                                     uint32_t ty)
 {
-    constexpr uint32_t NT = WHOLE_NT, NW = WHOLE_NW;
-    constexpr uint32_t CH = LMAX / 64;                // 64-column passes of a row
+    constexpr uint32_t NT = 64 * NW;
+    constexpr uint32_t CH = (LMAX + 63) / 64;         // 64-column passes of a row
     constexpr uint32_t RP = LMAX / NW;                // rows of a strip, at most
+    static_assert(NT >= 256 && (RP & (RP - 1)) == 0 && RP <= 16, "a thread a state; rows by masked lanes");
     constexpr uint32_t NMAX = LMAX * LMAX;
     constexpr uint32_t SPS = LMAX + 4;                // row stride of the spins
     constexpr uint32_t QCAP = 256;
-    __shared__ uint8_t s[LMAX * SPS];                 // spins
+    __shared__ uint8_t s[LMAX * SPS + 64];            // spins (a pass reads 65 columns of any row)
     __shared__ __align__(16) uint8_t D[NMAX + 128];   // per site: bit 0 +x draw below the threshold, bit 1 +y
     __shared__ uint32_t P[NMAX];                      // union-find over the runs' first sites
     __shared__ uint32_t UQ[NW][QCAP];                 // per wave: queued unions (two 16-bit sites), then roots
-    __shared__ uint16_t HB[NW][LMAX];                 // per strip: the labels of its last row, by column
+    __shared__ uint16_t HB[NW][64 * CH];              // per strip: the labels of its last row, by column
     __shared__ uint16_t LN[NW][CH][RP];               // per strip: the node of the last site of each row's pass
     __shared__ uint64_t MB[NW][CH][2];                // per strip: its last row's +y bonds and run links
     __shared__ uint64_t BW[LMAX][CH][2];              // the last sweep's bond words
@@ -425,15 +425,23 @@ hipError_t launch_whole(const LatDesc* descs, const uint32_t* list, uint32_t cou
                         uint32_t n_uniform, const uint32_t* n_each, uint32_t flags, uint32_t ty, hipStream_t s)
 {
     if (count == 0) return hipSuccess;
-    if (lmax <= 64)
-        hipLaunchKernelGGL(k_whole<64>, dim3(count), dim3(WHOLE_NT), 0, s, descs, list, k0, n_uniform,
-                           n_each, flags, ty);
-    else if (lmax <= WHOLE_LMAX)
-        hipLaunchKernelGGL(k_whole<128>, dim3(count), dim3(WHOLE_NT), 0, s, descs, list, k0, n_uniform,
-                           n_each, flags, ty);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    const auto go = [&](auto kernel, uint32_t nw) {
+        hipLaunchKernelGGL(kernel, dim3(count), dim3(64 * nw), 0, s, descs, list, k0, n_uniform, n_each, flags, ty);
+        return hipGetLastError();
+    };
+    if (lmax > WHOLE_LMAX) return hipErrorInvalidValue;
+    if (lmax > 64) return go(k_whole<128, 16>, 16);
+    // Sixteen waves (80 registers) fill a CU's share alone; with more lattices than
+    // CUs, eight waves let two be swept side by side and four waves four, each
+    // longer than by itself.  us a sweep with 16 / 8 / 4 waves, and with the kernel
+    // of 256 threads that was before:
+    //   256 lattices    L = 8 4.1 / 4.5 / 6.0 (6.1)      L = 64 10.0 / 12.4 / 20.2 (26)
+    //   512             L = 8 7.8 / 5.2 / 6.7 (6.9)      L = 64 19.6 / 16.3 / 23.3 (31)
+    //   640             L = 8 11.5 / 8.7 / 7.3 (7.9)     L = 64 28.7 / 24.9 / 26.5 (38)
+    //   4096            L = 8 59.6 / 37.2 / 29.1 (37)    L = 64 150 / 111 / 108 (180)
+    if (count <= CUS) return go(k_whole<64, 16>, 16);
+    if (count <= 2 * CUS) return go(k_whole<64, 8>, 8);
+    return go(k_whole<64, 4>, 4);
 }
 
 }  // namespace swmi

@@ -155,3 +155,26 @@ def test_whole_lattice_path_limits():
     ref.run(3)
     assert np.array_equal(lat.spins(), ref.s)
     lat.close()
+
+
+@pytest.mark.parametrize("n", [256, 257, 512, 513])
+def test_waves_of_many_small_lattices(n):
+    """Sixteen, eight and four waves a lattice, by the number of lattices: every
+    strip length, full and partial passes, every way the states are counted."""
+    sizes = [2, 5, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64]
+    qs = [2, 3, 9, 17]
+    reps = [dict(L=sizes[i % len(sizes)], q=qs[i % 4], K=(0.0, 1.0, 1.05, float("inf"))[i // 16 % 4] or 0.0,
+                 seed=900 + i, random_start=i % 5 != 0) for i in range(n)]
+    for r in reps:
+        if 0 < r["K"] < 2:
+            r["K"] *= wl.critical_coupling(r["q"])
+    print(f"case {n} small lattices", flush=True)
+    b = binding.Batch(reps, obs_capacity=8, tile_rows=binding.SW_TILE_WHOLE)
+    for calls in (1, 3):
+        b.sweep_all(calls)
+    for i, r in enumerate(reps):
+        ref = oracle.OracleLattice(r["L"], r["q"], r["K"], r["seed"], random_start=r["random_start"])
+        rows = ref.run(4)
+        assert np.array_equal(b.measure(i, 0, 4), rows), (i, r)
+        assert np.array_equal(b.spins(i), ref.s), (i, r)
+    b.close()

@@ -9,7 +9,7 @@ import pytest
 SRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1208_2080_amd", "csrc",
                    "sw_whole.hip")
 TEXT = open(SRC).read()
-FORMS = sorted({(int(m[1]), int(m[2] or 16)) for m in re.finditer(r"hipLaunchKernelGGL\(\(?k_whole<(\d+)(?:, (\d+))?>", TEXT)})
+FORMS = sorted({(int(m[1]), int(m[2])) for m in re.finditer(r"\bk_whole<(\d+), (\d+)>", TEXT)})
 
 
 def steps(text):
