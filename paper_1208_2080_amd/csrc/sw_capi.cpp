@@ -1029,24 +1029,24 @@ struct sw_batch {
     uint32_t* d_n;
     size_t total_tiles;
     std::vector<WorkItem> h_map;    // host copy of the last uploaded map
-    std::vector<uint32_t> h_n, h_nw;
+    std::vector<uint32_t> h_n, h_some;
     std::vector<uint32_t> map_order;  // replica order of the uploaded map
     StepGraphs steps;                            // sweeps of every replica as graphs (sweep_all)
     bool csum = false;                           // some replica measures cluster-size sums
     // replicas that may be swept whole (k_whole): device list, L <= 64 first, then
-    // the rest, and a call's sweep counts of those it sweeps so
+    // the rest; and of these the ones that a call with uneven counts sweeps so
     uint32_t* d_list = nullptr;
-    uint32_t* d_nw = nullptr;
+    uint32_t* d_some = nullptr;
     uint32_t n_whole64 = 0, n_whole128 = 0;
     bool whole_all = false;                      // sweep_all sweeps them whole (else by tiles, like the others)
-    bool whole_alone = false;                    // and so does a call that sweeps no others
+    bool whole_asked = false;                    // the caller asked for it: every call does
     size_t tile_tiles = 0;                       // tiles of the replicas sweep_all sweeps by tiles
 };
 
 namespace {
 
 struct BatchLayout {
-    size_t descs, map, nvec, list, nwhole, header;
+    size_t descs, map, nvec, list, some, header;
     std::vector<size_t> off;
     std::vector<Geometry> g;
     std::vector<Carve> c;
@@ -1080,7 +1080,7 @@ int batch_layout(const sw_params* params, uint32_t n, BatchLayout* out)
     off = align_up(off + sizeof(uint32_t) * n);
     b.list = off;
     off = align_up(off + sizeof(uint32_t) * n);
-    b.nwhole = off;
+    b.some = off;
     off = align_up(off + sizeof(uint32_t) * n);
     b.header = off;
     for (uint32_t r = 0; r < n; ++r) {
@@ -1092,27 +1092,42 @@ int batch_layout(const sw_params* params, uint32_t n, BatchLayout* out)
     return SW_OK;
 }
 
-// Whether sweeping the replicas that fit LDS whole is faster than by tiles, for
-// the same number of sweeps of every replica.  Whole, one after another on 256
-// CUs: 9.4 us a sweep per lattice and CU up to L = 64 and 27.5 us up to L = 128.
-// By tiles: their sites at 240 a ns, plus the 21 us that three launches over few
-// tiles take, unless other replicas need those launches anyway.  Measured, us a
-// sweep whole / by tiles: 256 lattices of L = 64 9.7 / 23.4, 1024 37.4 / 39.4,
-// 2048 74.5 / 55.9; 64 of L = 128 27.2 / 24.7, 256 27.6 / 40.0, 512 54.6 / 57.4,
-// 1024 109 / 88; 256 uneven replicas of which 81 fit LDS, 50 sweeps: 63.6 / 61.8 ms
-// when the line was drawn.
-bool whole_is_faster(const BatchLayout& lay, bool others)
+// Whether sweeping the replicas `which` (all fit LDS) whole is faster than by
+// tiles: n[r] sweeps of replica r (one each without n).  Whole, a workgroup each:
+// the longest of them, or their sum over the CUs; up to 64 sites a side more than
+// 256 and 512 of them share a CU by two and four (launch_whole), which takes each
+// 1.3 and 1.4 times its time by itself, above 64 one has it alone, in rounds.  By
+// tiles: 16.5 ns a tile and sweep, plus the 21 us that three launches over few tiles
+// take, unless other replicas need those launches anyway (others).  Measured, us a
+// sweep whole / by tiles:
+//   L = 8    600 7.3 / 23    4096 29 / 54       L = 32   1024 17 / 34    4096 60 / 74
+//   L = 64   600 26 / 33     2048 58 / 57       4096 108 / 87
+//   L = 65   1 16 / 20.5     256 17 / 40        1024 65 / 91
+//   L = 96   64 20.5 / 25    300 41 / 43        1024 82 / 90
+//   L = 128  64 27.6 / 24.5  256 28 / 40        512 55 / 55      1024 109 / 88
+bool whole_is_faster(const std::vector<Geometry>& g, const std::vector<uint32_t>& which, const uint32_t* n, bool others)
 {
-    double whole_us = 0.0, tiles_us = others ? 0.0 : 21.0;
-    uint64_t n64 = 0, n128 = 0;
-    for (const Geometry& g : lay.g) {
-        if (!g.whole) continue;
-        ++(g.L <= 64 ? n64 : n128);
-        tiles_us += (double)g.N / 240e3;
+    uint64_t n64 = 0;
+    for (uint32_t r : which) n64 += g[r].L <= 64;
+    const double share = n64 <= CUS ? 1.0 : n64 <= 2 * CUS ? 2.0 : 4.0;
+    double longest = 0.0, most64 = 0.0, sum64 = 0.0, most = 0.0, sum = 0.0, tiles = 0.0;
+    for (uint32_t r : which) {
+        const double k = n ? n[r] : 1.0, L = g[r].L;
+        longest = std::max(longest, k);
+        tiles += k * g[r].ntiles;
+        if (L <= 64) {   // alone, with 16, 8 or 4 waves
+            const double us = k * (share == 1.0 ? 2.9 + 0.104 * L : share == 2.0 ? 3.2 + 0.136 * L : 4.3 + 0.24 * L);
+            most64 = std::max(most64, us);
+            sum64 += us;
+        } else {
+            const double us = k * (3.2 + 0.185 * L);
+            most = std::max(most, us);
+            sum += us;
+        }
     }
-    if (n64) whole_us += 9.4 * std::max(1.0, (double)n64 / 256.0);
-    if (n128) whole_us += 27.5 * std::ceil((double)n128 / 256.0);
-    return whole_us < tiles_us;
+    double whole_us = std::max(most64, sum64 / (CUS * share)) * (share == 1.0 ? 1.0 : share == 2.0 ? 1.3 : 1.4);
+    if (most > 0.0) whole_us += most * std::max(1.0, std::ceil(sum / (CUS * most) - 1e-9));
+    return whole_us < 0.0165 * tiles + (others ? 0.0 : 21.0 * longest);
 }
 
 // Upload the tile list of the replicas with n_each[r] > 0 among those swept by
@@ -1152,45 +1167,51 @@ int upload_map(sw_batch* b, const uint32_t* n_each, const std::vector<char>& by_
     return SW_OK;
 }
 
-// The replicas swept whole: n_each[r] (or n_uniform) sweeps from their
-// counters, which the kernel advances (bump) or leaves to the caller.
-int batch_whole(sw_batch* b, uint32_t n_uniform, const uint32_t* d_n_each, bool bump)
+// The replicas of a device list (n64 of L <= 64, then n128 larger ones) swept
+// whole: n_each[r] (or n_uniform) sweeps from their counters, which the kernel
+// advances (bump) or leaves to the caller.
+int batch_whole(sw_batch* b, const uint32_t* d_list, uint32_t n64, uint32_t n128, uint32_t n_uniform,
+                const uint32_t* d_n_each, bool bump)
 {
     const uint32_t flags = bump ? 0u : 2u;
-    HIP_TRY(launch_whole(b->d_descs, b->d_list, b->n_whole64, 64, 0, n_uniform, d_n_each, flags, b->ty, b->stream));
-    HIP_TRY(launch_whole(b->d_descs, b->d_list + b->n_whole64, b->n_whole128, WHOLE_LMAX, 0, n_uniform, d_n_each, flags,
-                         b->ty, b->stream));
+    HIP_TRY(launch_whole(b->d_descs, d_list, n64, 64, 0, n_uniform, d_n_each, flags, b->ty, b->stream));
+    HIP_TRY(launch_whole(b->d_descs, d_list + n64, n128, WHOLE_LMAX, 0, n_uniform, d_n_each, flags, b->ty, b->stream));
     return SW_OK;
 }
 
 int batch_enqueue(sw_batch* b, const uint32_t* n_each)
 {
-    // kt: steps that the replicas too large for LDS take anyway; the others join
-    // those steps unless they have more sweeps to do (or sweep_all has them whole)
+    // kt: steps that the replicas too large for LDS take anyway.  Of those that
+    // fit, as far as this call moves them, some may join these steps (with no such
+    // steps: make their own), the ones with more sweeps to do than kt do not.
     uint32_t kt = 0, kall = 0;
     for (uint32_t r = 0; r < b->n; ++r) {
         kall = std::max(kall, n_each[r]);
         if (!b->g[r].whole) kt = std::max(kt, n_each[r]);
     }
     if (kall == 0) return SW_OK;
+    std::vector<uint32_t> may;
+    for (uint32_t r = 0; r < b->n; ++r)
+        if (b->g[r].whole && n_each[r] && (kt == 0 || n_each[r] <= kt)) may.push_back(r);
+    const bool join = !b->whole_asked && !whole_is_faster(b->g, may, n_each, kt != 0);
     std::vector<char> by_tiles(b->n);
-    uint32_t kmax = 0;
-    bool any_whole = false;
-    b->h_nw.assign(b->n, 0u);
+    uint32_t kmax = 0, n64 = 0;
+    b->h_some.clear();
     for (uint32_t r = 0; r < b->n; ++r) {
-        by_tiles[r] = !b->g[r].whole || (kt == 0 ? !b->whole_alone : !b->whole_all && n_each[r] <= kt);
+        by_tiles[r] = !b->g[r].whole || (join && (kt == 0 || n_each[r] <= kt));
         if (by_tiles[r]) kmax = std::max(kmax, n_each[r]);
-        else if (n_each[r]) {
-            b->h_nw[r] = n_each[r];
-            any_whole = true;
-        }
+        else if (n_each[r] && b->g[r].L <= 64) b->h_some.push_back(r);
     }
+    n64 = (uint32_t)b->h_some.size();
+    for (uint32_t r = 0; r < b->n; ++r)
+        if (!by_tiles[r] && n_each[r] && b->g[r].L > 64) b->h_some.push_back(r);
     b->h_n.assign(n_each, n_each + b->n);
     HIP_TRY(hipMemcpyAsync(b->d_n, b->h_n.data(), b->n * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream));
     int rc = SW_OK;
-    if (any_whole) {
-        HIP_TRY(hipMemcpyAsync(b->d_nw, b->h_nw.data(), b->n * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream));
-        rc = batch_whole(b, 0, b->d_nw, false);
+    if (!b->h_some.empty()) {
+        HIP_TRY(hipMemcpyAsync(b->d_some, b->h_some.data(), b->h_some.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
+                               b->stream));
+        rc = batch_whole(b, b->d_some, n64, (uint32_t)b->h_some.size() - n64, 0, b->d_n, false);
         if (rc) return rc;
     }
     std::vector<uint32_t> prefix;
@@ -1268,12 +1289,10 @@ int sw_batch_init(const sw_params* params, uint32_t n, void* dev_ws, size_t ws_b
     for (uint32_t r = 0; r < n; ++r)
         if (lay.g[r].whole && lay.g[r].L > 64) list.push_back(r);
     b->n_whole128 = (uint32_t)list.size() - b->n_whole64;
-    b->d_nw = reinterpret_cast<uint32_t*>(b->base + lay.nwhole);
+    b->d_some = reinterpret_cast<uint32_t*>(b->base + lay.some);
     // (a replica made with SW_TILE_WHOLE keeps them all whole)
-    bool asked = false;
-    for (uint32_t r = 0; r < n; ++r) asked = asked || params[r].tile_rows == SW_TILE_WHOLE;
-    b->whole_all = asked || whole_is_faster(lay, list.size() < n);
-    b->whole_alone = asked || whole_is_faster(lay, false);
+    for (uint32_t r = 0; r < n; ++r) b->whole_asked = b->whole_asked || params[r].tile_rows == SW_TILE_WHOLE;
+    b->whole_all = b->whole_asked || whole_is_faster(lay.g, list, nullptr, list.size() < n);
     for (uint32_t r = 0; r < n; ++r)
         if (!lay.g[r].whole || !b->whole_all) b->tile_tiles += lay.g[r].ntiles;
     b->desc.resize(n);
@@ -1344,7 +1363,7 @@ int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps)
         // sweeps, each advancing their counters
         for (uint32_t done = 0; done < n_sweeps;) {
             const uint32_t k = std::min(WHOLE_CHUNK, n_sweeps - done);
-            const int rc = batch_whole(b, k, nullptr, true);
+            const int rc = batch_whole(b, b->d_list, b->n_whole64, b->n_whole128, k, nullptr, true);
             if (rc) return rc;
             done += k;
         }

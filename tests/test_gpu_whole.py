@@ -178,3 +178,37 @@ def test_waves_of_many_small_lattices(n):
         assert np.array_equal(b.measure(i, 0, 4), rows), (i, r)
         assert np.array_equal(b.spins(i), ref.s), (i, r)
     b.close()
+
+
+@pytest.mark.parametrize("n,large", [(40, 0), (600, 0), (600, 1)])
+def test_calls_that_move_some_of_many_small_lattices(n, large):
+    """The way a call takes follows from the replicas that it moves and how far:
+    a few of many, all of them, some further than others, with and without one
+    that does not fit LDS, in turn."""
+    sizes = [3, 16, 33, 64, 66, 97, 128]
+    reps = [dict(L=sizes[i % 7] if i < n else 150, q=2 + i % 3, K=wl.critical_coupling(2 + i % 3), seed=70 + i,
+                 random_start=True) for i in range(n + large)]
+    total = n + large
+    few = [3 if i in (0, 5, n - 1) else 0 for i in range(total)]
+    uneven = [(i * 7) % 5 for i in range(total)]
+    long_few = [9 if i % 50 == 4 else 1 for i in range(total)]
+    only_large = [0] * n + [2] * large
+    print(f"case {n} small, {large} large", flush=True)
+    b = binding.Batch(reps, obs_capacity=64)
+    done = np.zeros(total, dtype=int)
+    for each in (few, None, uneven, long_few, few, only_large, None, uneven):
+        if each is None:
+            b.sweep_all(2)
+            done += 2
+        elif any(each):
+            b.sweep(each)
+            done += each
+    for i, r in enumerate(reps):
+        if i % 7 and i % 11 and i < n - 3:
+            continue
+        ref = oracle.OracleLattice(r["L"], r["q"], r["K"], r["seed"], random_start=True)
+        rows = ref.run(int(done[i]))
+        assert b.sweeps_done(i) == done[i]
+        assert np.array_equal(b.measure(i, 0, int(done[i])), rows), (i, r)
+        assert np.array_equal(b.spins(i), ref.s), (i, r)
+    b.close()
