@@ -330,3 +330,69 @@ def test_lattices_that_fit_lds_whole_or_by_tiles(L, null_stream):
             ref.sweep()
             assert np.array_equal(lat.spins(), ref.s), "spins after a replay"
     lat.close()
+
+
+def sums_of(labels):
+    sizes = np.unique(labels, return_counts=True)[1]
+    return [sum(int(c) ** 2 for c in sizes), sum(int(c) ** 4 for c in sizes)]
+
+
+# (L, q, with cluster sums): large and small lattices, with the sums and without
+MIXED = [(200, 2, True), (200, 2, False), (64, 3, False), (97, 2, True), (300, 4, False), (33, 2, True)]
+
+
+def test_batch_with_cluster_sums_in_some_replicas():
+    """One flip for all of them: those without the sums leave it early."""
+    reps = [dict(L=L, q=q, K=wl.critical_coupling(q), seed=20 + i, random_start=True, cluster_sums=cs)
+            for i, (L, q, cs) in enumerate(MIXED)]
+    print("case mixed cluster sums, batch", flush=True)
+    b = binding.Batch(reps, obs_capacity=16)
+    b.sweep_all(2)
+    b.sweep([i % 3 for i in range(len(reps))])
+    b.sweep_all(1)
+    for i, r in enumerate(reps):
+        n = 3 + i % 3
+        ref = oracle.OracleLattice(r["L"], r["q"], r["K"], r["seed"], random_start=True)
+        outs = [ref.sweep() for _ in range(n)]
+        assert np.array_equal(b.measure(i, 0, n), np.array([o["obs"] for o in outs])), i
+        assert np.array_equal(b.spins(i), ref.s), i
+        if r["cluster_sums"]:
+            assert b.cluster_sums(i, 0, n).tolist() == [sums_of(o["labels"]) for o in outs], i
+        else:
+            with pytest.raises(binding.SwError):
+                b.cluster_sums(i, 0, n)
+    b.close()
+
+
+def test_group_with_cluster_sums_in_some_lattices():
+    print("case mixed cluster sums, group", flush=True)
+    lats = [binding.Lattice(L, q, wl.critical_coupling(q), seed=20 + i, obs_capacity=16, cluster_sums=cs)
+            for i, (L, q, cs) in enumerate(MIXED)]
+    refs = [oracle.OracleLattice(L, q, wl.critical_coupling(q), 20 + i) for i, (L, q, cs) in enumerate(MIXED)]
+    group = binding.Group(len(lats), sum(binding.tile_count(L, q) for L, q, _ in MIXED))
+    outs = [[] for _ in lats]
+    for each in ([2] * 6, [0, 1, 1, 3, 1, 2], [1, 0, 2, 0, 1, 1]):
+        group.sweep(lats, each)
+        for i, n in enumerate(each):
+            outs[i] += [refs[i].sweep() for _ in range(n)]
+    for i, (lat, (L, q, cs)) in enumerate(zip(lats, MIXED)):
+        n = len(outs[i])
+        assert np.array_equal(lat.measure(0, n), np.array([o["obs"] for o in outs[i]])), i
+        assert np.array_equal(lat.spins(), refs[i].s) and np.array_equal(lat.labels(), outs[i][-1]["labels"]), i
+        if cs:
+            assert lat.cluster_sums(0, n).tolist() == [sums_of(o["labels"]) for o in outs[i]], i
+    group.close()
+    for lat in lats:
+        lat.close()
+
+
+# launch_merge picks the hooks that climb both chains from 144 tiles on (and up to
+# 25600, at a coupling where clusters span the lattice); the flip takes sixteen
+# waves a tile up to 256 tiles, eight up to 1024, four above.
+@pytest.mark.parametrize("L,tile_rows,tiles", [(512, 32, 128), (513, 32, 153), (1024, 128, 128), (1025, 128, 153),
+                                               (704, 64, 121), (705, 64, 144)])
+def test_lower_line_of_the_two_chain_merge(L, tile_rows, tiles):
+    """Both sides of 144 tiles at every tile height."""
+    assert binding.tile_count(L, 2, tile_rows) == tiles
+    for f in (1.0, 1.3):
+        check(L, 2, K=f * wl.critical_coupling(2), tile_rows=tile_rows, calls=(1, 2), random_start=f == 1.0)
