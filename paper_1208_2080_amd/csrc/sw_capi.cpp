@@ -58,14 +58,20 @@ struct Geometry {
     bool chosen = false;     // ... by the default rule, not because the caller asked for it
     uint32_t dir_bits = 0;   // XY: bits of the direction draw kept
     double K = 0.0;          // XY: the coupling
-    bool spans = false;      // the coupling is where clusters span the lattice
+    bool spans = false;      // the coupling is where clusters span the lattice in long chains
 };
 
 // Clusters span the lattice from the transition on: e^K - 1 >= sqrt(q) for
 // Potts (less a rounding's worth, so that K_c itself is in); for XY, whose
 // clusters are those of one direction, from a little below the
-// Kosterlitz-Thouless coupling 1.12.  The merge takes another form there.
-bool spans_potts(double K, uint32_t q) { return std::expm1(K) >= 0.999 * std::sqrt((double)q); }
+// Kosterlitz-Thouless coupling 1.12.  The merge takes another form there
+// (launch_merge, with the times), but for Potts lattices at K >= 2.2, nine bonds in
+// ten active: a tile is one cluster then and the chains are short again, unless
+// there are more than 8192 tiles (measured at 4096 and 16384).
+bool spans_potts(double K, uint32_t q, uint32_t ntiles)
+{
+    return std::expm1(K) >= 0.999 * std::sqrt((double)q) && (K < 2.2 || ntiles > 8192);
+}
 bool spans_xy(double K) { return K >= 1.04; }
 
 // Words of a ring record and of one partial copy's stride, for either model.
@@ -133,7 +139,7 @@ int check_params(const sw_params* p, Geometry* g)
         return fail(SW_EINVAL, "cluster sums need L <= 32768 and obs_capacity > 0");
     g->q = p->q;
     g->thr = threshold_of(p->K);
-    g->spans = spans_potts(p->K, p->q);
+    g->spans = spans_potts(p->K, p->q, g->ntiles);
     g->csum = (p->flags & SW_CLUSTER_SUMS) != 0;
     const bool fits = p->L <= WHOLE_LMAX && !g->csum;
     if (p->tile_rows == SW_TILE_WHOLE && !fits)

@@ -1686,7 +1686,12 @@ hipError_t launch_merge(const Work& w, uint32_t bump)
     //   q = 8, 2048    0.99 K_c 36.3 / 36.6, 1.00 37.4 / 37.8, 1.01 52.4 / 45.2
     //   XY, 2048       K = 1.01 60.8 / 61.9, 1.05 67.8 / 65.6, 1.12 72.2 / 65.9
     // the merge alone, q = 2, K_c, 8192 77 / 48, 10000 81 / 68, 11585 87 / 94, 16384
-    // 133 / 141; 32 uneven jobs 292 / 300.
+    // 133 / 141; 32 uneven jobs 292 / 300.  Far above the transition, whole sweeps:
+    //   q = 2, 4096    K = 1.6 104.5 / 91.1, 2.0 100.7 / 94.8, 2.2 99.2 / 99.1,
+    //                  2.4 97.9 / 101.6, 4 96.0 / 102.0 (q = 4, 8, 20 alike)
+    //   q = 2, 2048    K = 2.0 45.5 / 44.0, 2.2 44.7 / 44.8, 2.4 44.1 / 45.3
+    //   q = 2, 8192    K = 2.2 289 / 266, 2.7 280 / 273, 4 274 / 277
+    //   XY, 2048       K = 2 69.5 / 63.0, 6 67.2 / 64.2, 30 64.6 / 64.3
     const bool both = w.spans && !w.map && w.nitems >= 144 && w.nitems <= 25600;
     auto go = [&](auto ty) {
         constexpr int TY = decltype(ty)::value;

@@ -396,3 +396,10 @@ def test_lower_line_of_the_two_chain_merge(L, tile_rows, tiles):
     assert binding.tile_count(L, 2, tile_rows) == tiles
     for f in (1.0, 1.3):
         check(L, 2, K=f * wl.critical_coupling(2), tile_rows=tile_rows, calls=(1, 2), random_start=f == 1.0)
+
+
+@pytest.mark.parametrize("K", [2.19, 2.2, 3.0])
+def test_merges_far_above_the_transition(K):
+    """Both sides of K = 2.2, from where the hooks climb one chain again."""
+    check(900, 3, K=K, calls=(2, 2))
+    check(900, 3, K=K, calls=(2,), random_start=False)
