@@ -503,8 +503,12 @@ def main():
                                f"{'random' if cfg['random_start'] else 'cold'} start, "
                                f"{'update only' if args.update_only else 'update + measurement'}",
                    "L": L, "q": q, "K": K, "seed": cfg["seed"], "tile_rows": ty},
+        # "bound" names the roof that the bytes are held against; what limits the
+        # kernel in fact is beside it
         "roofline": {"bound": "hbm", "kernel": dominant, "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
+                     "limited_by": {"k_bond_label": "vector issue",
+                                    "k_flip": "load latency at full occupancy"}[dominant],
                      "traffic": traffic,
                      "alg_bytes_per_launch": alg_bytes,
                      "avg_launch_ms": per_launch_ms[dominant]},

@@ -66,11 +66,13 @@ typedef struct sw_params {
     uint32_t tile_rows;    /* labelling tile height: 32, 64 or 128; SW_TILE_WHOLE
                               (L <= 128, no cluster sums): the whole lattice in
                               one workgroup's LDS, many sweeps per launch; 0
-                              (default): whole where that applies and is faster
-                              (a plain lattice of L <= 96; in a batch up to 128,
-                              unless other replicas need the tile launches anyway
-                              or such replicas are too many for one a compute
-                              unit), else 64; results do not depend on it */
+                              (default): whole where that applies and is faster,
+                              else 64: a plain lattice of L <= 96, of L <= 128 in
+                              calls of fewer than 100 sweeps on a stream that has
+                              no graphs of its steps yet and in a call that the
+                              caller captures; in a batch up to L = 128 by the
+                              number and sizes of the replicas a call moves;
+                              results do not depend on it */
     uint32_t flags;        /* 0, or SW_CLUSTER_SUMS */
 } sw_params;
 
@@ -222,10 +224,9 @@ int sw_batch_init(const sw_params* params, uint32_t n, void* dev_ws, size_t ws_b
  * uint32.  Asynchronous. */
 int sw_batch_sweep(sw_batch* b, const uint32_t* n_sweeps);
 
-/* Same sweep count for every replica, captured once per count as a HIP graph
- * and replayed (a few counts are cached per batch; the count is a constant of
- * its graph).  On the legacy NULL stream, which cannot be captured, the kernels
- * are launched directly.  Asynchronous. */
+/* Same sweep count for every replica, replayed from HIP graphs of one step and
+ * of several that are built on first use and serve any count.  On the legacy NULL
+ * stream the kernels are launched directly.  Asynchronous. */
 int sw_batch_sweep_all(sw_batch* b, uint32_t n_sweeps);
 
 /* sw_measure, sw_read_spins, sw_cluster_sums, sw_sweeps_done and sw_destroy

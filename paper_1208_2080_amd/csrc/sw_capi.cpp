@@ -640,7 +640,7 @@ static int whole_sweeps(sw_lattice* h, uint32_t n)
 {
     for (uint32_t done = 0; done < n;) {
         const uint32_t k = std::min(WHOLE_CHUNK, n - done);
-        HIP_TRY(launch_whole(h->d_desc, nullptr, 1, h->g.L, 0, k, nullptr, 1u, h->g.ty, h->stream));
+        HIP_TRY(launch_whole(h->d_desc, nullptr, 1, h->g.L, k, nullptr, 1u, h->g.ty, h->stream));
         done += k;
     }
     h->done += n;
@@ -1180,8 +1180,8 @@ int batch_whole(sw_batch* b, const uint32_t* d_list, uint32_t n64, uint32_t n128
                 const uint32_t* d_n_each, bool bump)
 {
     const uint32_t flags = bump ? 0u : 2u;
-    HIP_TRY(launch_whole(b->d_descs, d_list, n64, 64, 0, n_uniform, d_n_each, flags, b->ty, b->stream));
-    HIP_TRY(launch_whole(b->d_descs, d_list + n64, n128, WHOLE_LMAX, 0, n_uniform, d_n_each, flags, b->ty, b->stream));
+    HIP_TRY(launch_whole(b->d_descs, d_list, n64, 64, n_uniform, d_n_each, flags, b->ty, b->stream));
+    HIP_TRY(launch_whole(b->d_descs, d_list + n64, n128, WHOLE_LMAX, n_uniform, d_n_each, flags, b->ty, b->stream));
     return SW_OK;
 }
 

@@ -771,8 +771,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
     // carries its key), writes the node's word (a root of its own, keyed by its
     // site index) and makes the root's LDS entry ROOT16 + 2 (slot + 1), which halved
     // like an offset, as a signed number, is NODE16 + slot: that the labels
-    // and the edge record carry on.  Walks stop at tagged entries (all walks end
-    // before the first claim).
+    // and the edge record carry on.  One wave claims while others still walk: only
+    // roots are ever tagged, and a walk that meets a tagged entry stops there, at
+    // the root it was looking for.
     // a site index fits 32 bits (N <= 2^32) and y, L fit 24 bits
     auto global_index = [&](uint32_t la) { return __umul24(y0 + la / TX, L) + x0 + la % TX; };
     const uint32_t node0 = tile * nslot(TY);
@@ -1591,8 +1592,16 @@ uint32_t init_grid(size_t N)
 //   1024 tiles (L = 2048)  44.1 / 50.6    44.1 / 43.2 / 46.2
 //   2116 tiles (L = 2900)  65.2 / 84.6    65.2 / 66.7 / 72.2
 // so the lines lie at one workgroup per CU (256 tiles) and, for the flip, four.
-// (Labelling with 8 waves, when the line was drawn: between the other two at 256
-// and 529 tiles, no better than four at 1024.)
+// Labelling and flip both with 4 / 8 / 16 waves, for the other kernels and for
+// mapped work (us):
+//   XY, K = 1.12   256 tiles 42.3 / 38.3 / 37.0, 289 48.2 / 44.4 / 45.0, 529 55.4 / 52.7 / 56.5,
+//                  1024 64.3 / 62.9 / 70.0, 1089 71.6 / 72.3 / 79.3
+//   cluster sums   256 tiles 45.0 / 40.7 / 39.7, 289 47.2 / 43.2 / 44.1,
+//                  1024 82.8 / 82.2 / 84.3, 1089 88.3 / 89.6 / 96.3
+//   batches of L = 128   256 tiles 30.3 / 26.8 / 26.0, 400 33.1 / 30.5 / 31.8,
+//                  1024 42.0 / 41.7 / 49.6, 1600 53.3 / 57.3 / 73.3
+// so the same lines hold for them (eight waves for the labelling of 257 to about
+// 500 tiles too would take 2 to 3 % off a sweep there).
 
 template <int TY, bool PRESET>
 hipError_t start_bond_label(const Work& w, uint32_t k, uint32_t flags)

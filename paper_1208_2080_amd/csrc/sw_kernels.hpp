@@ -80,11 +80,11 @@ hipError_t launch_flip_xy(const Work& w, uint32_t k);
 hipError_t launch_xy_init(const LatDesc* descs, size_t N, uint32_t random_start, hipStream_t s);
 // Lattices of L <= WHOLE_LMAX swept whole in one workgroup each (descs[list[b]]
 // for workgroup b, or descs[b] without a list), n_each[lattice] (or n_uniform)
-// sweeps each from sweep counter + k0; lmax: the largest L among them.  flags
+// sweeps each from the sweep counter on; lmax: the largest L among them.  flags
 // bit 0: also write the last sweep's labels (smallest site indices) and bond
 // words (tile-major, ty rows per tile); bit 1: leave the sweep counters (else
 // set past the last sweep).
-hipError_t launch_whole(const LatDesc* descs, const uint32_t* list, uint32_t count, uint32_t lmax, uint32_t k0,
+hipError_t launch_whole(const LatDesc* descs, const uint32_t* list, uint32_t count, uint32_t lmax,
                         uint32_t n_uniform, const uint32_t* n_each, uint32_t flags, uint32_t ty, hipStream_t s);
 // Labels of rows [ya, yb) of the last sweep resolved to smallest site
 // indices, written from the base of the label region ((yb - ya) L <= N / 2), or

@@ -8,8 +8,9 @@
 
 namespace swmi {
 
-// Waves of a tile workgroup: every wave owns 16 rows of a 64- or 128-row tile
-// (8 of a 32-row tile), one column per lane.
+// Waves of a tile workgroup where tiles are many: every wave owns 16 rows of a 64-
+// or 128-row tile (8 of a 32-row tile), one column per lane.  64-row tiles have up
+// to sixteen waves, of four rows, where tiles are few (start_bond_label, start_flip).
 template <int TY>
 constexpr uint32_t waves_of() { return TY == 128 ? 8u : 4u; }
 template <int TY>

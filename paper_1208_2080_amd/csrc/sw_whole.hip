@@ -58,12 +58,12 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Sweeps counter + k0 .. counter + k0 + n - 1.  flags bit 0: write the labels
+// Sweeps counter .. counter + n - 1.  flags bit 0: write the labels
 // and bond words of the last sweep; bit 1: leave the sweep counter (the caller
 // advances it), else set it past the last sweep.  ty: tile height of the
 // lattice's bond-word layout.
 template <int LMAX, uint32_t NW>
-__global__ __launch_bounds__(64 * NW) void k_whole(const LatDesc* descs, const uint32_t* list, uint32_t k0,
+__global__ __launch_bounds__(64 * NW) void k_whole(const LatDesc* descs, const uint32_t* list,
                                                     uint32_t n_uniform, const uint32_t* n_each, uint32_t flags,
                                                     uint32_t ty)
 {
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(64 * NW) void k_whole(const LatDesc* descs, const u
         if (tid == 0) flag_error(d.err);
         return;
     }
-    const uint32_t t0 = *glb(d.counter) + k0;
+    const uint32_t t0 = *glb(d.counter);
     const bool meas = d.cap != 0;
     bool bad = false;
 
@@ -421,12 +421,12 @@ __global__ __launch_bounds__(64 * NW) void k_whole(const LatDesc* descs, const u
 
 }  // namespace
 
-hipError_t launch_whole(const LatDesc* descs, const uint32_t* list, uint32_t count, uint32_t lmax, uint32_t k0,
+hipError_t launch_whole(const LatDesc* descs, const uint32_t* list, uint32_t count, uint32_t lmax,
                         uint32_t n_uniform, const uint32_t* n_each, uint32_t flags, uint32_t ty, hipStream_t s)
 {
     if (count == 0) return hipSuccess;
     const auto go = [&](auto kernel, uint32_t nw) {
-        hipLaunchKernelGGL(kernel, dim3(count), dim3(64 * nw), 0, s, descs, list, k0, n_uniform, n_each, flags, ty);
+        hipLaunchKernelGGL(kernel, dim3(count), dim3(64 * nw), 0, s, descs, list, n_uniform, n_each, flags, ty);
         return hipGetLastError();
     };
     if (lmax > WHOLE_LMAX) return hipErrorInvalidValue;
