@@ -894,7 +894,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8))) vo
 // joins the edge-forest nodes of the two sites' tile-local roots.
 //
 // bump: sweeps to advance each lattice's counter by (0: leave it), done by the
-// wave of its tile 0.  This kernel alone does not read the counter, so a
+// wave of its tile 0, which also notes the labels' form.  This kernel alone does not read the counter, so a
 // step's graph needs no launch of its own to move on to the next sweep; the
 // kernels after it in the step see the counter already moved.
 template <int TY, bool BOTH>
@@ -908,7 +908,10 @@ __global__ __launch_bounds__(256) void k_merge(const LatDesc* descs, const WorkI
     uint32_t tile, lat;
     if (!pick(descs, map, idx, false, d, tile, lat)) return;
     SW_PHASE_START(pc);
-    if (bump && tile == 0 && lane == 0) *glb(d.counter) += bump;
+    if (bump && tile == 0 && lane == 0) {
+        *glb(d.counter) += bump;
+        *glb(d.labels) = LABELS_TILE;
+    }
     const TileGeom g = tile_geom(d, tile, TY);
     const uint32_t EW = edge_words(TY), NS = nslot(TY);
     const uint32_t n = d.ntiles * NS;
@@ -1340,7 +1343,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(CS ? 4 
     if (bad) flag_error(d.err);
     SW_PHASE_FLUSH(pc, phase_table(XY ? 4u : 2u));
 
-    if (tile == 0 && tid == 0) *glb(d.labels) = LABELS_TILE;
     // The ring record of the next sweep starts from zero.
     if (d.cap && tile == 0) {
         const uint32_t words = NCOPY * (XY ? XY_STRIDE : ring_stride(d.q));
@@ -1504,13 +1506,17 @@ __global__ __launch_bounds__(256) void k_read_out(const uint32_t* src, uint32_t 
     }
 }
 
-// Advance sweep counters: lattice i by n (or by n_each[i] when given).
+// Advance sweep counters: lattice i by n (or by n_each[i] when given), after
+// sweeps by tiles (or sweeps of a batch, whose labels are not read).
 __global__ void k_bump(const LatDesc* descs, uint32_t count, const uint32_t* n_each, uint32_t n)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) {
         const uint32_t add = n_each ? n_each[i] : n;
-        if (add) *glb(descs[i].counter) += add;
+        if (add) {
+            *glb(descs[i].counter) += add;
+            *glb(descs[i].labels) = LABELS_TILE;
+        }
     }
 }
 

@@ -91,7 +91,7 @@ constexpr uint32_t XY_STRIDE = (XY_WORDS + 1u + 31u) & ~31u;
 // Kernels keep the form, not the host: a call that a stream capture records runs
 // only when its graph is replayed.
 constexpr uint32_t LABELS_NONE = 0;    // no sweep since the start or a load
-constexpr uint32_t LABELS_TILE = 1;    // tile labels (written by k_flip)
+constexpr uint32_t LABELS_TILE = 1;    // tile labels (written where the counter moves on)
 constexpr uint32_t LABELS_SITE = 2;    // all N smallest site indices (k_whole)
 
 struct DevState {
