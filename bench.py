@@ -182,7 +182,7 @@ def huge_lattices(warmup: int, steps: int) -> dict:
 def small_lattice(sweeps: int) -> dict:
     """The small correctness configuration (L = 64, q = 2, K_c, random start,
     measurement every sweep) timed on its own: launch-bound at this size, so
-    the sweeps replay captured HIP graphs."""
+    the sweeps replay HIP graphs."""
     import torch
     from paper_1208_2080_amd import binding
     cfg = workloads()["L64"]
@@ -287,7 +287,7 @@ def batched_vs_plain(n_replicas: int, sweeps: int, tile_rows: int) -> dict:
     flips = sum(r["L"] ** 2 for r in reps) * sweeps
     b = binding.Batch(reps, obs_capacity=2, tile_rows=tile_rows or "auto")
     tile_rows = b.tile_rows
-    b.sweep_all(2)                                   # warm-up (and graph capture)
+    b.sweep_all(2)                                   # warm-up (and the steps' graphs)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     done = 0

@@ -166,8 +166,8 @@ _streams = {}
 def default_stream(device):
     """The stream lattices and groups use when none is given: one per device,
     of default priority, shared so that groups can sweep any lattice made
-    without an explicit stream.  (Not the legacy NULL stream, which the
-    library cannot capture in HIP graphs.)"""
+    without an explicit stream.  (Not the legacy NULL stream, on which the
+    library launches every kernel by itself instead of replaying HIP graphs.)"""
     device = torch.device(device)
     if device not in _streams:
         _streams[device] = torch.cuda.Stream(device)
@@ -437,7 +437,7 @@ class Batch:
         self.replicas = [dict(r) for r in replicas]
         n = len(self.replicas)
         self.device = torch.device("cuda", 0) if device is None else torch.device(device)
-        # a stream of its own (default priority): HIP graphs cannot capture the NULL stream
+        # a stream of its own (default priority): the library replays HIP graphs there, not on the NULL stream
         self.stream = stream if stream is not None else torch.cuda.Stream(self.device)
         self.tuned_ms = None
         if tile_rows == "auto":

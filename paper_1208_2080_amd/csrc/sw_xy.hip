@@ -164,7 +164,7 @@ __device__ __forceinline__ int64_t* xy_record(const LatDesc& d, uint32_t sweep, 
 // bond plane the labeller reads.
 //
 // Bound by vector issue: 138 instructions per row of 64 sites (36 Philox, 35
-// sin and cos, 20 the two bond tests, 20 the six sums), 1.14 ms at L = 16384
+// sin and cos, 20 the two bond tests, 20 the six sums), 1.12 ms at L = 16384
 // with measurement; 172 and 1.50 ms with the tests' estimates formed in FP64
 // from 53-bit uniforms, projections computed twice and three instructions per
 // term of the sums.
