@@ -138,10 +138,10 @@ int sw_cluster_sums(sw_lattice* h, uint32_t first, uint32_t n, uint64_t* host_ou
  * labels (+ measurement of the incoming configuration), [1] tile-edge merge,
  * [2] flip, [3] final measurement and counter update, [4] the part of [0]
  * spent in the model's bond kernel (the XY model's k_xy_bonds; for the Potts
- * model, whose bonds and labels are one kernel, [0] but for what an event costs).  A lattice is
- * swept whole or by tiles as sw_sweep would for so many sweeps; whole, one kernel
- * does every phase and its time is [0] and [4].  The results are the same as
- * sw_sweep's. */
+ * model, whose bonds and labels are one kernel, [0] but for what an event
+ * costs).  A lattice is swept whole or by tiles as sw_sweep would for so many
+ * sweeps; whole, one kernel does every phase and its time is [0] and [4].  The
+ * results are the same as sw_sweep's. */
 int sw_sweep_profiled(sw_lattice* h, uint32_t n_sweeps, double* phase_ms);
 
 /* sw_measure and sw_read_spins on a stream other than the handle's, for a
